@@ -118,7 +118,7 @@ int validate(const dw_config* c, Layout* lay) {
   lay->P = P;
   lay->Pp = round_up(P, 64);
   lay->z_stride = round_up(2 * ((P + 63) / 64), 64);
-  lay->n_upd_blocks = (lay->Pp + kUpdChunk - 1) / kUpdChunk;
+  lay->n_upd_blocks = update_blocks(lay->Pp);
   size_t pos = 0;
   auto take = [&](size_t bytes) { size_t at = pos; pos += (size_t)round_up((int64_t)bytes, 256); return at; };
   const size_t vec = (size_t)k * lay->Pp * sizeof(float);

@@ -8,9 +8,9 @@
 //                   piecewise-linear weights h1(a), h2(a).
 //   pull_kernel     Section V-B eq.(12)-(13): elastic pull of every participating worker and of the centre.
 //
-// All three are bound by HBM bandwidth.  One thread owns the same four consecutive parameters of every
-// worker: the centre values stay in registers while the block walks over the k replicas, so the centre is
-// read once per launch, and the reduction over workers into the centre needs no atomics.
+// All three are bound by HBM bandwidth.  In the pull one thread owns the same four consecutive parameters of every
+// worker, so the centre is read once and the reduction over workers into it needs no atomics; the update, which
+// only reads the centre, goes worker by worker (see there).
 #include <cstddef>
 #include <type_traits>
 
@@ -57,176 +57,139 @@ __device__ __forceinline__ float denom_pow(float vhat, float hpow) {
 // OPT: the local step (DW_OPT_*).  The baselines' first-order steps (Section II eq.(3); Section VI) move 12 bytes
 // (SGD: g and theta read, theta written) or 20 bytes (momentum: also the velocity read and written) per parameter
 // and worker where the AdaHessian step moves 32.
+//
+// Bound by HBM, and the rate HBM gives depends on the order in which the addresses come.  A lane owns one float4 of one
+// worker, a wave a piece of 256 consecutive parameters; the blocks of a launch go through a stretch of 2^20 parameters
+// of worker 0, then the same stretch of worker 1, ..., then the next stretch, so that at any time the chip streams
+// through eight arrays front to back (and the stretch of the centre, 4 MB, is read from the caches by every worker but the first).
+// Within a stretch the four waves of a block take pieces eight apart: blocks go to the eight XCDs in turn, and with
+// this spacing the piece after the last one in memory is on the next XCD.  k = 16 replicas of 1e8 parameters (5 reads,
+// 3 writes), streaming alone: 5.76 TB/s; one-wave blocks without the spacing 5.82, 256 contiguous float4 per block 5.56,
+// stretches of 2^18 parameters 5.15, a block that walks over the workers with its centre in registers 5.28, two or four
+// float4 per lane 5.3 to 5.5.  This kernel: 9.91 -> 9.25 ms (5.2 -> 5.5 TB/s); 1.2e6 parameters, seven workers: 58 -> 49 us.
 template <bool HAS_B16, int OPT>
 __global__ __launch_bounds__(kUpdThreads) void update_kernel(UpdateArgs a) {
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int64_t nq = (a.P + 3) >> 2;      // caller-supplied g / Hz rows end at P
-  // which chunk of kUpdChunk parameters: the block index, or an entry of the list (read from the kernel-argument
-  // block by a scalar load: indexing the by-value argument with a variable would copy it to scratch memory)
-  int blk = blockIdx.x;
+  // this block's worker i, its slot among the worker's partial sums, and this wave's piece
+  int i, slot;
+  int64_t piece;
   if (a.n_list > 0) {
+    // four blocks per listed chunk of kUpdChunk parameters (the list is read from the kernel-argument block by a scalar
+    // load: indexing the by-value argument with a variable would copy it to scratch memory)
     typedef const char __attribute__((address_space(4)))* karg_bytes;
     typedef const int __attribute__((address_space(4)))* karg_ints;
     const karg_bytes ka = (karg_bytes)__builtin_amdgcn_kernarg_segment_ptr();
-    blk = ((karg_ints)(ka + offsetof(UpdateArgs, block_list)))[blockIdx.x];
+    const int chunk = ((karg_ints)(ka + offsetof(UpdateArgs, block_list)))[blockIdx.x >> 2];
+    i = blockIdx.y;
+    slot = chunk * 4 + (blockIdx.x & 3);
+    piece = (int64_t)slot * 4 + wave;
+  } else {
+    const unsigned b = blockIdx.y * gridDim.x + blockIdx.x;  // (more than one row: a row is a multiple of eight blocks)
+    if (b >= (unsigned)a.n_blocks * (unsigned)a.k) return;
+    const unsigned full = a.n_blocks / kUpdStretch, per = a.k * (unsigned)kUpdStretch;
+    unsigned st = b / per, r = b % per, width = kUpdStretch;
+    if (st >= full) { st = full; r = b - full * per; width = a.n_blocks - full * kUpdStretch; }
+    i = r / width;
+    slot = st * kUpdStretch + r % width;                     // (widths are multiples of eight: slot % 8 is blockIdx.x % 8)
+    piece = (int64_t)(slot >> 3) * 32 + wave * 8 + (slot & 7);
   }
-  const int64_t qbase = (int64_t)blk * (kUpdThreads * kUpdQuads) + tid;
-  __shared__ double wave_part[DW_MAX_K][kUpdThreads / 64];
+  const int64_t q = piece * 64 + lane;
+  const bool valid = q < nq;
+  const bool active = (a.active_mask >> i) & 1ull;
+  // updated by a weight-gradient kernel (a frozen worker's distance is measured here all the same)
+  const bool skip = a.fused.n > 0 && active && in_fused(a.fused, q << 2);
+  const bool on = valid && !skip;
 
-  // a block whose parameters were all updated by a weight-gradient kernel has nothing to do unless some worker
-  // is frozen (then it still reports that worker's distance to the centre)
-  if (a.fused.n > 0) {
-    const int64_t j0 = (int64_t)blk * kUpdChunk, j1 = j0 + kUpdChunk;
-    bool inside = false;
-    for (int l = 0; l < a.fused.n; ++l) inside = inside || (j0 >= a.fused.begin[l] && j1 <= a.fused.end[l]);
-    const uint64_t all = a.k >= 64 ? ~0ull : ((1ull << a.k) - 1ull);
-    if (inside && (a.active_mask & all) == all) {
-      if (tid < a.k) a.partials[(int64_t)tid * a.n_blocks + blk] = 0.0;
-      return;
+  float nsum = 0.f;
+  float4* th4 = reinterpret_cast<float4*>(a.theta + (int64_t)i * a.Pp);
+  if (active) {
+    float4* m4 = reinterpret_cast<float4*>(a.m + (int64_t)i * a.Pp);
+    float4* v4 = reinterpret_cast<float4*>(a.v + (int64_t)i * a.Pp);
+    const float4* g4 = reinterpret_cast<const float4*>(a.g + (int64_t)i * a.g_stride);
+    const float4* h4 = reinterpret_cast<const float4*>(a.hz + (int64_t)i * a.g_stride);
+    float4 G = make_float4(0.f, 0.f, 0.f, 0.f), H = G, T = G, M = G, V = G, C = G;
+    uint32_t Z = 0;
+    if (on) {
+      G = nt_load4(g4 + q); T = nt_load4(th4 + q);
+      if (OPT != DW_OPT_SGD) M = nt_load4(m4 + q);
+      if (OPT == DW_OPT_ADAHESSIAN) {
+        H = nt_load4(h4 + q); V = nt_load4(v4 + q);
+        Z = a.zbits[(int64_t)i * a.z_stride + (q >> 3)] >> (uint32_t)((q << 2) & 31);
+      }
+      C = reinterpret_cast<const float4*>(a.centre)[q];
     }
-  }
-
-  float4 cen[kUpdQuads];
-  bool valid[kUpdQuads], avg[kUpdQuads], fz[kUpdQuads];
-  uint32_t zshift[kUpdQuads];
-#pragma unroll
-  for (int u = 0; u < kUpdQuads; ++u) {
-    const int64_t q = qbase + (int64_t)u * kUpdThreads;
-    fz[u] = a.fused.n > 0 && in_fused(a.fused, q << 2);
-    valid[u] = q < nq;
-    cen[u] = valid[u] ? reinterpret_cast<const float4*>(a.centre)[q] : make_float4(0.f, 0.f, 0.f, 0.f);
-    avg[u] = a.avg_block > 1 && !in_bias(a.bias, q << 2);
-    zshift[u] = (uint32_t)((q << 2) & 31);
-  }
-  const float inv_b = 1.0f / (float)a.avg_block;
-  const int group_lanes = a.avg_block >> 2;           // lanes that share one averaging block (when b > 4)
-
-  // a launch of few chunks spreads the workers over the grid's second dimension: the chain of k dependent memory
-  // round trips per block would otherwise set the kernel's duration
-  const int i0 = gridDim.y > 1 ? (int)blockIdx.y : 0, i1 = gridDim.y > 1 ? i0 + 1 : a.k;
-  for (int i = i0; i < i1; ++i) {
-    const bool active = (a.active_mask >> i) & 1ull;
-    float nsum = 0.f;
-    float4* th4 = reinterpret_cast<float4*>(a.theta + (int64_t)i * a.Pp);
-    if (active) {
-      float4* m4 = reinterpret_cast<float4*>(a.m + (int64_t)i * a.Pp);
-      float4* v4 = reinterpret_cast<float4*>(a.v + (int64_t)i * a.Pp);
-      const float4* g4 = reinterpret_cast<const float4*>(a.g + (int64_t)i * a.g_stride);
-      const float4* h4 = reinterpret_cast<const float4*>(a.hz + (int64_t)i * a.g_stride);
-      const uint32_t* zb = a.zbits + (int64_t)i * a.z_stride;
+    const float g[4] = {G.x, G.y, G.z, G.w};
+    const float cc[4] = {C.x, C.y, C.z, C.w};
+    float th[4] = {T.x, T.y, T.z, T.w};
+    float mm[4] = {M.x, M.y, M.z, M.w};
+    if (OPT == DW_OPT_ADAHESSIAN) {
       const float ib1 = a.sc.inv_bc1[i], ib2 = a.sc.inv_bc2[i];
-      float4 G[kUpdQuads], H[kUpdQuads], T[kUpdQuads], M[kUpdQuads], V[kUpdQuads];
-      uint32_t Z[kUpdQuads];
+      const float hz[4] = {H.x, H.y, H.z, H.w};
+      float vv[4] = {V.x, V.y, V.z, V.w};
+      float D[4];
 #pragma unroll
-      for (int u = 0; u < kUpdQuads; ++u) {
-        const int64_t q = qbase + (int64_t)u * kUpdThreads;
-        G[u] = H[u] = T[u] = M[u] = V[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        Z[u] = 0;
-        if (valid[u] && !fz[u]) {
-          G[u] = nt_load4(g4 + q); T[u] = nt_load4(th4 + q);
-          if (OPT != DW_OPT_SGD) M[u] = nt_load4(m4 + q);
-          if (OPT == DW_OPT_ADAHESSIAN) {
-            H[u] = nt_load4(h4 + q); V[u] = nt_load4(v4 + q);
-            Z[u] = zb[q >> 3] >> zshift[u];
-          }
-        }
-      }
-      if (OPT != DW_OPT_ADAHESSIAN) {
-        // first-order step of a baseline: theta -= lr * g, or the same through the velocity b = momentum * b + g
-#pragma unroll
-        for (int u = 0; u < kUpdQuads; ++u) {
-          const int64_t q = qbase + (int64_t)u * kUpdThreads;
-          float g[4] = {G[u].x, G[u].y, G[u].z, G[u].w};
-          float th[4] = {T[u].x, T[u].y, T[u].z, T[u].w};
-          float bb[4] = {M[u].x, M[u].y, M[u].z, M[u].w};
-          const float cc[4] = {cen[u].x, cen[u].y, cen[u].z, cen[u].w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if (OPT == DW_OPT_MOMENTUM) { bb[e] = a.momentum * bb[e] + g[e]; th[e] = th[e] - a.lr * bb[e]; }
-            else th[e] = th[e] - a.lr * g[e];
-            const float d = th[e] - cc[e];
-            nsum += d * d;
-          }
-          if (valid[u]) {
-            nt_store4(th4 + q, make_float4(th[0], th[1], th[2], th[3]));
-            if (OPT == DW_OPT_MOMENTUM) nt_store4(m4 + q, make_float4(bb[0], bb[1], bb[2], bb[3]));
-            if (HAS_B16) {
-              ushort4 w;
-              w.x = f32_to_bf16_rne(th[0]); w.y = f32_to_bf16_rne(th[1]);
-              w.z = f32_to_bf16_rne(th[2]); w.w = f32_to_bf16_rne(th[3]);
-              reinterpret_cast<ushort4*>(a.wb16 + (int64_t)i * a.Pp)[q] = w;
-            }
-          }
-        }
-      }
-#pragma unroll
-      for (int u = 0; OPT == DW_OPT_ADAHESSIAN && u < kUpdQuads; ++u) {
-        const int64_t q = qbase + (int64_t)u * kUpdThreads;
-        float g[4] = {G[u].x, G[u].y, G[u].z, G[u].w};
-        float hz[4] = {H[u].x, H[u].y, H[u].z, H[u].w};
-        float th[4] = {T[u].x, T[u].y, T[u].z, T[u].w};
-        float mm[4] = {M[u].x, M[u].y, M[u].z, M[u].w};
-        float vv[4] = {V[u].x, V[u].y, V[u].z, V[u].w};
-        // quads updated elsewhere run on zeros and add nothing to the distance
-        const float cc[4] = {fz[u] ? 0.f : cen[u].x, fz[u] ? 0.f : cen[u].y, fz[u] ? 0.f : cen[u].z, fz[u] ? 0.f : cen[u].w};
-        float D[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e)                                              // Hutchinson: z * Hz, or its mean
-          D[e] = a.d_scale > 0.f ? hz[e] * a.d_scale : sign_from_bit(Z[u], e) * hz[e];
-        // spatial average over avg_block consecutive parameters (all lanes take part in the shuffles)
-        float Ds[4] = {D[0], D[1], D[2], D[3]};
+      for (int e = 0; e < 4; ++e)                                              // Hutchinson: z * Hz, or its mean
+        D[e] = a.d_scale > 0.f ? hz[e] * a.d_scale : sign_from_bit(Z, e) * hz[e];
+      // spatial average over avg_block consecutive parameters (all lanes take part in the shuffles; a block never
+      // leaves its wave's piece, whose start is a multiple of 256)
+      if (a.avg_block > 1) {
+        const bool avg = !in_bias(a.bias, q << 2);
         if (a.avg_block == 2) {
           const float p0 = 0.5f * (D[0] + D[1]), p1 = 0.5f * (D[2] + D[3]);
-          if (avg[u]) { Ds[0] = Ds[1] = p0; Ds[2] = Ds[3] = p1; }
-        } else if (a.avg_block >= 4) {
+          if (avg) { D[0] = D[1] = p0; D[2] = D[3] = p1; }
+        } else {
+          const int group_lanes = a.avg_block >> 2;         // lanes that share one averaging block
           float s = (D[0] + D[1]) + (D[2] + D[3]);
           for (int off = 1; off < group_lanes; off <<= 1) s += __shfl_xor(s, off);
-          s *= inv_b;
-          if (avg[u]) { Ds[0] = Ds[1] = Ds[2] = Ds[3] = s; }
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          mm[e] = a.beta1 * mm[e] + (1.0f - a.beta1) * g[e];
-          vv[e] = a.beta2 * vv[e] + (1.0f - a.beta2) * (Ds[e] * Ds[e]);
-          const float mhat = mm[e] * ib1;
-          const float vhat = vv[e] * ib2;
-          th[e] = th[e] - a.lr * (mhat / (denom_pow(vhat, a.hpow) + a.eps));
-          const float d = th[e] - cc[e];
-          nsum += d * d;
-        }
-        if (valid[u] && !fz[u]) {
-          nt_store4(th4 + q, make_float4(th[0], th[1], th[2], th[3]));
-          nt_store4(m4 + q, make_float4(mm[0], mm[1], mm[2], mm[3]));
-          nt_store4(v4 + q, make_float4(vv[0], vv[1], vv[2], vv[3]));
-          if (HAS_B16) {
-            ushort4 w;
-            w.x = f32_to_bf16_rne(th[0]); w.y = f32_to_bf16_rne(th[1]);
-            w.z = f32_to_bf16_rne(th[2]); w.w = f32_to_bf16_rne(th[3]);
-            reinterpret_cast<ushort4*>(a.wb16 + (int64_t)i * a.Pp)[q] = w;
-          }
+          s *= 1.0f / (float)a.avg_block;
+          if (avg) { D[0] = D[1] = D[2] = D[3] = s; }
         }
       }
-    } else {
 #pragma unroll
-      for (int u = 0; u < kUpdQuads; ++u) {
-        const int64_t q = qbase + (int64_t)u * kUpdThreads;
-        if (valid[u]) {
-          const float4 t = th4[q];
-          const float d0 = t.x - cen[u].x, d1 = t.y - cen[u].y, d2 = t.z - cen[u].z, d3 = t.w - cen[u].w;
-          nsum += (d0 * d0 + d1 * d1) + (d2 * d2 + d3 * d3);
-        }
+      for (int e = 0; e < 4; ++e) {
+        mm[e] = a.beta1 * mm[e] + (1.0f - a.beta1) * g[e];
+        vv[e] = a.beta2 * vv[e] + (1.0f - a.beta2) * (D[e] * D[e]);
+        const float mhat = mm[e] * ib1;
+        const float vhat = vv[e] * ib2;
+        th[e] = th[e] - a.lr * (mhat / (denom_pow(vhat, a.hpow) + a.eps));
+      }
+      if (on) nt_store4(v4 + q, make_float4(vv[0], vv[1], vv[2], vv[3]));
+    } else {
+      // first-order step of a baseline: theta -= lr * g, or the same through the velocity b = momentum * b + g
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (OPT == DW_OPT_MOMENTUM) { mm[e] = a.momentum * mm[e] + g[e]; th[e] = th[e] - a.lr * mm[e]; }
+        else th[e] = th[e] - a.lr * g[e];
       }
     }
-    const double ws = wave_sum((double)nsum);
-    if (lane == 0) wave_part[i][wave] = ws;
+    if (on) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { const float d = th[e] - cc[e]; nsum += d * d; }
+      nt_store4(th4 + q, make_float4(th[0], th[1], th[2], th[3]));
+      if (OPT != DW_OPT_SGD) nt_store4(m4 + q, make_float4(mm[0], mm[1], mm[2], mm[3]));
+      if (HAS_B16) {
+        ushort4 w;
+        w.x = f32_to_bf16_rne(th[0]); w.y = f32_to_bf16_rne(th[1]);
+        w.z = f32_to_bf16_rne(th[2]); w.w = f32_to_bf16_rne(th[3]);
+        reinterpret_cast<ushort4*>(a.wb16 + (int64_t)i * a.Pp)[q] = w;
+      }
+    }
+  } else if (valid) {
+    const float4 t = th4[q], c = reinterpret_cast<const float4*>(a.centre)[q];
+    const float d0 = t.x - c.x, d1 = t.y - c.y, d2 = t.z - c.z, d3 = t.w - c.w;
+    nsum = (d0 * d0 + d1 * d1) + (d2 * d2 + d3 * d3);
   }
+  __shared__ double wave_part[kUpdThreads / 64];
+  const double ws = wave_sum((double)nsum);
+  if (lane == 0) wave_part[wave] = ws;
   __syncthreads();
-  if (tid >= i0 && tid < i1) {
+  if (tid == 0) {
     double s = 0.0;
 #pragma unroll
-    for (int w = 0; w < kUpdThreads / 64; ++w) s += wave_part[tid][w];
-    a.partials[(int64_t)tid * a.n_blocks + blk] = s;
+    for (int w = 0; w < kUpdThreads / 64; ++w) s += wave_part[w];
+    a.partials[(int64_t)i * a.n_blocks + slot] = s;
   }
 }
 
@@ -234,14 +197,17 @@ hipError_t launch_update(const UpdateArgs& args, int n_blocks, hipStream_t s) {
   KernelScope ks(KC_UPDATE, s);
   UpdateArgs a = args;
   a.n_blocks = n_blocks; a.n_list = 0;
-  int grid = n_blocks, grid_y = 1;
+  constexpr unsigned kRow = 1u << 22;                        // a grid dimension holds fewer than 2^32 threads
+  const unsigned blocks = (unsigned)n_blocks * (unsigned)a.k;
+  dim3 g3(blocks < kRow ? blocks : kRow, (blocks + kRow - 1) / kRow);
   // When weight-gradient kernels have updated most ranges and no worker is frozen, only the chunks that touch
   // other parameters (biases, small layers) have work: launch those, after clearing everybody's partial sums.
   const uint64_t all = a.k >= 64 ? ~0ull : ((1ull << a.k) - 1ull);
   if (a.fused.n > 0 && (a.active_mask & all) == all) {
+    const int n_chunks = (int)((a.Pp + kUpdChunk - 1) / kUpdChunk);
     int n = 0;
     bool fits = true;
-    for (int b = 0; b < n_blocks && fits; ++b) {
+    for (int b = 0; b < n_chunks && fits; ++b) {
       const int64_t j0 = (int64_t)b * kUpdChunk, j1 = j0 + kUpdChunk;
       bool inside = false;
       for (int l = 0; l < a.fused.n; ++l) {
@@ -259,13 +225,10 @@ hipError_t launch_update(const UpdateArgs& args, int n_blocks, hipStream_t s) {
     if (fits && n > 0) {
       hipError_t e = launch_fill_zero(a.partials, (size_t)(((int64_t)a.k * n_blocks * sizeof(double) + 15) / 16 * 16), s);   // the array is carved in 256-byte units
       if (e != hipSuccess) return e;
-      a.n_list = n; grid = n; grid_y = a.k;
+      a.n_list = n; g3 = dim3((unsigned)n * 4u, (unsigned)a.k);
     }
   }
-  // few chunks (small models): one worker per block row as well; with many chunks a block walks through the workers
-  // and reads its piece of the centre once
-  if (a.n_list == 0 && n_blocks < 1024 && a.k > 1) grid_y = a.k;
-  const dim3 g3(grid, grid_y), b3(kUpdThreads);
+  const dim3 b3(kUpdThreads);
   auto launch = [&](auto b16, auto opt) {
     hipLaunchKernelGGL((update_kernel<decltype(b16)::value, decltype(opt)::value>), g3, b3, 0, s, a);
   };
@@ -326,26 +289,37 @@ __device__ __forceinline__ void weight_scalars(const WeightArgs& a, int i, doubl
   }
 }
 
-__global__ __launch_bounds__(256) void weight_kernel(WeightArgs a) {
+// A large model has 1e5 partial sums per worker and one block to add them: four loads of every thread in flight
+// (1e8 parameters: 18 us against 33 us for 256 threads with one, at a quarter of the partial sums).
+constexpr int kWeightThreads = 1024;
+__global__ __launch_bounds__(kWeightThreads) void weight_kernel(WeightArgs a) {
   const int i = blockIdx.x;
   const int tid = threadIdx.x;
-  __shared__ double red[256 / 64];
-  double s = 0.0;
-  for (int b = tid; b < a.n_blocks; b += 256) s += a.partials[(int64_t)i * a.n_blocks + b];
-  for (int b = tid; b < a.n_blocks_f; b += 256) s += a.partials_f[(int64_t)i * a.n_blocks_f + b];
+  __shared__ double red[kWeightThreads / 64];
+  auto sum_of = [&](const double* p, int n) {
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    int b = tid;
+    for (; b + 3 * kWeightThreads < n; b += 4 * kWeightThreads) {
+      s0 += p[b]; s1 += p[b + kWeightThreads]; s2 += p[b + 2 * kWeightThreads]; s3 += p[b + 3 * kWeightThreads];
+    }
+    for (; b < n; b += kWeightThreads) s0 += p[b];
+    return (s0 + s1) + (s2 + s3);
+  };
+  double s = sum_of(a.partials + (int64_t)i * a.n_blocks, a.n_blocks);
+  if (a.n_blocks_f > 0) s += sum_of(a.partials_f + (int64_t)i * a.n_blocks_f, a.n_blocks_f);
   s = wave_sum(s);
   if ((tid & 63) == 0) red[tid >> 6] = s;
   __syncthreads();
   if (tid != 0) return;
   double S = 0.0;
-  for (int w = 0; w < 256 / 64; ++w) S += red[w];
+  for (int w = 0; w < kWeightThreads / 64; ++w) S += red[w];
   float o, w;
   weight_scalars(a, i, S, a.man_h1[i], a.man_h2[i], true, &o, &w);      // (i is uniform: scalar loads)
 }
 
 hipError_t launch_weights(const WeightArgs& a, hipStream_t s) {
   KernelScope ks(KC_WEIGHTS, s);
-  hipLaunchKernelGGL(weight_kernel, dim3(a.k), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(weight_kernel, dim3(a.k), dim3(kWeightThreads), 0, s, a);
   return hipGetLastError();
 }
 
@@ -355,113 +329,109 @@ hipError_t launch_weights(const WeightArgs& a, hipStream_t s) {
 // Sequential rounds apply eq.(13) after every worker instead: the thread that owns a parameter keeps the
 // centre in a register and walks the workers in index order, so the bytes moved are the same.
 // ---------------------------------------------------------------------------------------------------
+// Bound by HBM (one read, one write).  A block is one wave that owns 256 consecutive parameters of every worker (one float4 per
+// lane) and asks for four workers' values at a time; k = 16 replicas of 1e8 parameters, streaming alone: 5.77 TB/s; 256 threads
+// with four float4 per lane, one worker at a time 5.46; one float4 per lane in blocks of 256 threads 5.4 to 5.5.  This kernel: 2.53 -> 2.40 ms; 1.2e6 parameters, seven workers: 15.4 -> 10.5 us.
 // FUSED_W: a model with few partial sums computes the weights inside the pull (every block for itself, in the same
 // order, so all blocks pull with the same values; block 0 records them): one launch per round instead of two.
+constexpr int kPullThreads = 64, kPullBatch = 4;
 template <bool HAS_B16, bool FUSED_W>
-__global__ __launch_bounds__(kUpdThreads) void pull_kernel(PullArgs a, WeightArgs wa) {
+__global__ __launch_bounds__(kPullThreads) void pull_kernel(PullArgs a, WeightArgs wa) {
   __shared__ float s_omh1[DW_MAX_K], s_h2[DW_MAX_K];
+  const int lane = threadIdx.x;
+  const int64_t q = (int64_t)blockIdx.x * kPullThreads + lane;
+  const bool valid = q < (a.Pp >> 2);
+  float4 cen = valid ? reinterpret_cast<const float4*>(a.centre)[q] : make_float4(0.f, 0.f, 0.f, 0.f);
   if (FUSED_W) {
-    const int i = threadIdx.x;
-    if (i < wa.k) {
-      double S = 0.0;
-      for (int b = 0; b < wa.n_blocks; ++b) S += wa.partials[(int64_t)i * wa.n_blocks + b];
-      for (int b = 0; b < wa.n_blocks_f; ++b) S += wa.partials_f[(int64_t)i * wa.n_blocks_f + b];
+    static_assert(kPullThreads >= DW_MAX_K, "a lane per worker");
+    double S = 0.0;                                        // lane i: the squared distance of worker i
+    for (int i = 0; i < wa.k; ++i) {
+      double s = 0.0;
+      for (int b = lane; b < wa.n_blocks; b += 64) s += wa.partials[(int64_t)i * wa.n_blocks + b];
+      for (int b = lane; b < wa.n_blocks_f; b += 64) s += wa.partials_f[(int64_t)i * wa.n_blocks_f + b];
+      s = wave_sum(s);
+      if (lane == i) S = s;
+    }
+    if (lane < wa.k) {
       // the caller's weights sit in the kernel-argument block behind the first argument; they are read from there by
       // address (indexing the by-value argument with the thread index would copy it to scratch memory)
       typedef const char __attribute__((address_space(4)))* karg_bytes;
       typedef const float __attribute__((address_space(4)))* karg_floats;
       constexpr size_t wa_at = (sizeof(PullArgs) + alignof(WeightArgs) - 1) / alignof(WeightArgs) * alignof(WeightArgs);
       const karg_bytes ka = (karg_bytes)__builtin_amdgcn_kernarg_segment_ptr();
-      const float man1 = ((karg_floats)(ka + wa_at + offsetof(WeightArgs, man_h1)))[i];
-      const float man2 = ((karg_floats)(ka + wa_at + offsetof(WeightArgs, man_h2)))[i];
-      weight_scalars(wa, i, S, man1, man2, blockIdx.x == 0, &s_omh1[i], &s_h2[i]);
+      const float man1 = ((karg_floats)(ka + wa_at + offsetof(WeightArgs, man_h1)))[lane];
+      const float man2 = ((karg_floats)(ka + wa_at + offsetof(WeightArgs, man_h2)))[lane];
+      weight_scalars(wa, lane, S, man1, man2, blockIdx.x == 0, &s_omh1[lane], &s_h2[lane]);
     }
     __syncthreads();
   }
-  const int64_t nq = a.Pp >> 2;
-  const int64_t qbase = (int64_t)blockIdx.x * (kUpdThreads * kUpdQuads) + threadIdx.x;
-  float4 cen[kUpdQuads], acc[kUpdQuads];
-  bool valid[kUpdQuads];
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  uint64_t rest = a.part_mask;                             // the participating workers, in index order
+  while (rest) {
+    int who[kPullBatch];
+    float4 T[kPullBatch];
 #pragma unroll
-  for (int u = 0; u < kUpdQuads; ++u) {
-    const int64_t q = qbase + (int64_t)u * kUpdThreads;
-    valid[u] = q < nq;
-    cen[u] = valid[u] ? reinterpret_cast<const float4*>(a.centre)[q] : make_float4(0.f, 0.f, 0.f, 0.f);
-    acc[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-  for (int i = 0; i < a.k; ++i) {
-    if (!((a.part_mask >> i) & 1ull)) continue;
-    const float o = FUSED_W ? s_omh1[i] : a.omh1[i], w = FUSED_W ? s_h2[i] : a.h2[i];
-    float4* th4 = reinterpret_cast<float4*>(a.theta + (int64_t)i * a.Pp);
-    float4 T[kUpdQuads];
-#pragma unroll
-    for (int u = 0; u < kUpdQuads; ++u) {
-      const int64_t q = qbase + (int64_t)u * kUpdThreads;
-      T[u] = valid[u] ? nt_load4(th4 + q) : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int j = 0; j < kPullBatch; ++j) {
+      who[j] = rest ? __builtin_ctzll(rest) : -1;
+      rest &= rest - 1;                                    // (0 stays 0)
+      T[j] = who[j] >= 0 && valid ? nt_load4(a.theta + (int64_t)who[j] * a.Pp + (q << 2)) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
 #pragma unroll
-    for (int u = 0; u < kUpdQuads; ++u) {
-      const int64_t q = qbase + (int64_t)u * kUpdThreads;
-      const float d0 = T[u].x - cen[u].x, d1 = T[u].y - cen[u].y, d2 = T[u].z - cen[u].z, d3 = T[u].w - cen[u].w;
+    for (int j = 0; j < kPullBatch; ++j) {
+      if (who[j] < 0) break;
+      const float o = FUSED_W ? s_omh1[who[j]] : a.omh1[who[j]], w = FUSED_W ? s_h2[who[j]] : a.h2[who[j]];
+      const float d0 = T[j].x - cen.x, d1 = T[j].y - cen.y, d2 = T[j].z - cen.z, d3 = T[j].w - cen.w;
       float4 r;
-      r.x = fmaf(o, d0, cen[u].x); r.y = fmaf(o, d1, cen[u].y);
-      r.z = fmaf(o, d2, cen[u].z); r.w = fmaf(o, d3, cen[u].w);
+      r.x = fmaf(o, d0, cen.x); r.y = fmaf(o, d1, cen.y);
+      r.z = fmaf(o, d2, cen.z); r.w = fmaf(o, d3, cen.w);
       if (a.sequential) {     // eq.(13) takes effect at once: the next worker of the round sees the moved centre
-        cen[u].x = fmaf(w, d0, cen[u].x); cen[u].y = fmaf(w, d1, cen[u].y);
-        cen[u].z = fmaf(w, d2, cen[u].z); cen[u].w = fmaf(w, d3, cen[u].w);
+        cen.x = fmaf(w, d0, cen.x); cen.y = fmaf(w, d1, cen.y);
+        cen.z = fmaf(w, d2, cen.z); cen.w = fmaf(w, d3, cen.w);
       } else {
-        acc[u].x = fmaf(w, d0, acc[u].x); acc[u].y = fmaf(w, d1, acc[u].y);
-        acc[u].z = fmaf(w, d2, acc[u].z); acc[u].w = fmaf(w, d3, acc[u].w);
+        acc.x = fmaf(w, d0, acc.x); acc.y = fmaf(w, d1, acc.y);
+        acc.z = fmaf(w, d2, acc.z); acc.w = fmaf(w, d3, acc.w);
       }
-      if (valid[u]) {
-        nt_store4(th4 + q, r);
+      if (valid) {
+        nt_store4(a.theta + (int64_t)who[j] * a.Pp + (q << 2), r);
         if (HAS_B16) {
           ushort4 b;
           b.x = f32_to_bf16_rne(r.x); b.y = f32_to_bf16_rne(r.y);
           b.z = f32_to_bf16_rne(r.z); b.w = f32_to_bf16_rne(r.w);
-          reinterpret_cast<ushort4*>(a.wb16 + (int64_t)i * a.Pp)[q] = b;
+          reinterpret_cast<ushort4*>(a.wb16 + (int64_t)who[j] * a.Pp)[q] = b;
         }
       }
     }
   }
-#pragma unroll
-  for (int u = 0; u < kUpdQuads; ++u) {
-    const int64_t q = qbase + (int64_t)u * kUpdThreads;
-    if (valid[u]) {
-      float4 c = cen[u];
-      c.x += acc[u].x; c.y += acc[u].y; c.z += acc[u].z; c.w += acc[u].w;
-      reinterpret_cast<float4*>(a.centre)[q] = c;
-    }
+  if (valid) {
+    cen.x += acc.x; cen.y += acc.y; cen.z += acc.z; cen.w += acc.w;
+    reinterpret_cast<float4*>(a.centre)[q] = cen;
   }
 }
 
+static unsigned pull_blocks(const PullArgs& a) { return (unsigned)(((a.Pp >> 2) + kPullThreads - 1) / kPullThreads); }
+
 hipError_t launch_pull(const PullArgs& a, hipStream_t s) {
   KernelScope ks(KC_PULL, s);
-  const int64_t nq = a.Pp >> 2;
-  const int n_blocks = (int)((nq + kUpdThreads * kUpdQuads - 1) / (kUpdThreads * kUpdQuads));
   WeightArgs none{};
   if (a.wb16)
-    hipLaunchKernelGGL((pull_kernel<true, false>), dim3(n_blocks), dim3(kUpdThreads), 0, s, a, none);
+    hipLaunchKernelGGL((pull_kernel<true, false>), dim3(pull_blocks(a)), dim3(kPullThreads), 0, s, a, none);
   else
-    hipLaunchKernelGGL((pull_kernel<false, false>), dim3(n_blocks), dim3(kUpdThreads), 0, s, a, none);
+    hipLaunchKernelGGL((pull_kernel<false, false>), dim3(pull_blocks(a)), dim3(kPullThreads), 0, s, a, none);
   return hipGetLastError();
 }
 
-// the round of a model with few partial sums per worker in one launch: weights and pull together
+// the round of a model with few partial sums per worker in one launch: weights and pull together (up to 64 partial sums
+// of the update, i.e. 65536 parameters)
 bool sync_fusable(const WeightArgs& w, const PullArgs& p) {
-  const int64_t nq = p.Pp >> 2;
-  const int64_t n_blocks = (nq + kUpdThreads * kUpdQuads - 1) / (kUpdThreads * kUpdQuads);
-  return w.n_blocks + w.n_blocks_f <= 16 && n_blocks <= 64;
+  return w.n_blocks + w.n_blocks_f <= 64 && pull_blocks(p) <= 256;
 }
 
 hipError_t launch_weights_and_pull(const WeightArgs& w, const PullArgs& a, hipStream_t s) {
   KernelScope ks(KC_PULL, s);
-  const int64_t nq = a.Pp >> 2;
-  const int n_blocks = (int)((nq + kUpdThreads * kUpdQuads - 1) / (kUpdThreads * kUpdQuads));
   if (a.wb16)
-    hipLaunchKernelGGL((pull_kernel<true, true>), dim3(n_blocks), dim3(kUpdThreads), 0, s, a, w);
+    hipLaunchKernelGGL((pull_kernel<true, true>), dim3(pull_blocks(a)), dim3(kPullThreads), 0, s, a, w);
   else
-    hipLaunchKernelGGL((pull_kernel<false, true>), dim3(n_blocks), dim3(kUpdThreads), 0, s, a, w);
+    hipLaunchKernelGGL((pull_kernel<false, true>), dim3(pull_blocks(a)), dim3(kPullThreads), 0, s, a, w);
   return hipGetLastError();
 }
 

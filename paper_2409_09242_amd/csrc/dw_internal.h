@@ -10,9 +10,11 @@
 
 namespace dw {
 
-constexpr int kUpdThreads = 256;      // threads per block of the streaming update / pull kernels
-constexpr int kUpdQuads = 4;          // float4 groups per thread and worker
-constexpr int64_t kUpdChunk = (int64_t)kUpdThreads * kUpdQuads * 4;   // parameters per block
+constexpr int kUpdThreads = 256;      // threads per block of the streaming update, one float4 each: 1024 parameters
+constexpr int kUpdStretch = 1024;     // blocks that go through one worker's parameters before the next worker's turn
+constexpr int64_t kUpdChunk = 4096;   // parameters per entry of UpdateArgs::block_list (four blocks)
+// partial sums of the squared distance per worker: one per block, blocks in groups of eight (8192 parameters)
+inline int64_t update_blocks(int64_t Pp) { return (Pp + 8191) / 8192 * 8; }
 
 // per-launch scalars of the fused AdaHessian update (Section IV-B), one entry per worker
 struct UpdateScalars {
@@ -58,7 +60,7 @@ struct UpdateArgs {
   // several probes per step with fused weight gradients (see FuseArgs): mode, first probe, running sum [k][Pp]
   int probe_mode, probe_first;
   float* dacc;
-  // filled by launch_update: the launch covers all n_blocks chunks (n_list == 0) or only the listed ones
+  // filled by launch_update: the launch covers all n_blocks blocks of every worker (n_list == 0) or only the listed chunks
   int n_blocks, n_list;
   int block_list[64];
 };
