@@ -10,10 +10,28 @@
 // R-companion.  The +-1 operand V is never stored as a matrix: its tile is expanded from the sign bits of
 // z while the W tile is staged.
 //
-// Tiling: 256 threads = 4 waves; block tile BM x BN x 16; tiles are staged k-major in LDS so that each
-// lane's MFMA operand (v_mfma_f32_32x32x2_f32: lane l supplies A[l%32][l/32] and B[l/32][l%32]) is one
-// conflict-free 32-bit LDS read; global loads are 16-byte and prefetched into registers one tile ahead.
+// The products run on the bf16 matrix cores in three pieces.  A float is the exact sum of three bf16 numbers
+// (3 x 8 significant bits); of the nine products of two such sums the six that reach 2^-24 are multiplied
+// (x1y1, x1y2, x2y1, x2y2, x1y3, x3y1), three with the +-1 operand, whose one piece is exact.  Six
+// v_mfma_f32_32x32x16_bf16 (32 cycles each) replace eight v_mfma_f32_32x32x2_f32 (64 cycles each), 2.7 times less matrix
+// time; with +-1 5.3 times less.  The products of the first pieces have a chain of accumulation of their own, the others,
+// 2^-8 of them and less, another, and the two are added at the end: in one chain the instruction cuts small products off
+// below the last bit of the running sum, always downwards (measured: -1e-8 to -4e-7 of the result's root mean square, which
+// the sums over thousands of positions that follow add up).  Error of one product against 64 bits (2-norm, K = 64 / 1024 /
+// 9216, normal operands): 5e-8 / 1.8e-7 / 5.9e-7, no bias; v_mfma_f32_32x32x2_f32 1.5e-7 / 5.7e-7 / 1.7e-6.
+// Tiles with infinities or NaN are computed again on the fp32 instruction (below).
+//
+// Tiling: waves of 32 rows by 32 or 64 columns; tiles of 32 k are split into their pieces once per block while they are
+// stored to LDS (planes [row][32 k] of bf16, 64-byte rows, 16-byte units XOR-swizzled so that both the
+// reads of 8 consecutive rows and the stores of every fourth row spread over the banks); global loads are 16-byte and one
+// tile ahead in registers.  Before -> now: eight workers, 256 samples, 3072-1024-1024-1024: forward 295 / 135 -> 158 / 74 us
+// (first / later layers), data gradient 94 -> 62, fused weight gradients 346 / 154 -> 235 / 104; eight workers, 64 maps of
+// 26 x 26 x 32 -> 24 x 24 x 64: forward 328 -> 214, data gradient 465 -> 369, weight gradient 370 -> 240.  What bounds them now (64 x
+// 64 tiles, counters): matrix cores 25 to 35 % busy, vector arithmetic (splitting, 6 instructions per element and block that loads
+// it) 35 %, LDS 30 to 50 % (six bytes stored and read per element), and between them the two barriers a tile, with two blocks
+// a compute unit to hide them.  Two tiles in flight instead of one: no change.
 #include <cstddef>
+#include <type_traits>
 
 #include "dw_internal.h"
 #include "dw_fused_update.h"
@@ -21,135 +39,361 @@
 namespace dw {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
 
-constexpr int BK = 16;
-constexpr int PAD = 4;
-constexpr int NT = 256;
+constexpr int BK = 32;                     // k per tile
+constexpr int kRowBytes = 64;              // of a plane
 
 enum RyMode { RY_NONE = 0, RY_MEM = 1, RY_BITS = 2 };
 
-template <int ROWS>                      // ROWS = extent of the non-contraction index in the tile (BM or BN)
+// byte offset inside a plane of the 16-byte unit holding k = 8*oct .. 8*oct+7 of `row`: four rows share the 256 bytes that
+// the 64 banks serve at once, and the unit's place in them is XORed with the group's number, so that 16 consecutive rows
+// (operand reads), 4 rows with their 4 units (stores, k contiguous) and every fourth row of 64 (stores, k-major) all
+// use 16 different places
+__device__ __forceinline__ int unit_at(int row, int oct) {
+  const int m = row >> 2;
+  return m * 256 + ((((row & 3) * 4 + oct) ^ (m & 15)) << 4);
+}
+
+__device__ __forceinline__ uint32_t to_bf16x2(float a, float b) {        // round to nearest even, a in the low half
+  const floatx2 v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+// the three pieces of a pair of floats, packed: the first is cut off (never overflows), the others are rounded
+template <bool INF>
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t& p1, uint32_t& p2, uint32_t& p3) {
+  const uint32_t au = __float_as_uint(a), bu = __float_as_uint(b);
+  p1 = __builtin_amdgcn_perm(bu, au, 0x07060302u);
+  float ra = a - __uint_as_float(au & 0xFFFF0000u), rb = b - __uint_as_float(bu & 0xFFFF0000u);
+  if (INF) {                                                 // inf - inf would be a NaN
+    if ((au & 0x7FFFFFFFu) == 0x7F800000u) ra = 0.f;
+    if ((bu & 0x7FFFFFFFu) == 0x7F800000u) rb = 0.f;
+  }
+  p2 = to_bf16x2(ra, rb);
+  ra -= __uint_as_float(p2 << 16); rb -= __uint_as_float(p2 & 0xFFFF0000u);
+  p3 = to_bf16x2(ra, rb);
+}
+template <bool INF, int N>                                   // N pairs
+__device__ __forceinline__ void split_pairs(const float (&x)[2 * N], uint32_t (&p)[3][N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) split_pair<INF>(x[2 * i], x[2 * i + 1], p[0][i], p[1][i], p[2][i]);
+}
+// +-1 as a pair of bf16 from two bits (bit set: +1)
+__device__ __forceinline__ uint32_t sign_pair(uint32_t b0, uint32_t b1) {
+  return 0xBF80BF80u ^ ((b0 & 1u) << 15) ^ ((b1 & 1u) << 31);
+}
+
+// Loads the tiles of one operand (NOPS = 1) or of an operand and its R-companion, laid out alike (NOPS = 2), and stores
+// their pieces.  A unit of work is 8 consecutive k of one row when k is contiguous in memory (KC), else 4 k of 4 consecutive rows.
+// Rows past the end repeat the last ones (their results are never stored); k past the end is zero.
+// VIEW: OperandView, the operand is read out of a map.
+template <int NT, int ROWS, bool KC, int NOPS, int VIEW>
 struct TileLoader {
-  static constexpr int CNT = ROWS * BK / 4;            // float4 per tile
-  static constexpr int NL = (CNT + NT - 1) / NT;       // float4 per thread
+  static constexpr int PER = KC ? ROWS * 4 : ROWS * 2;       // units per operand
+  static constexpr int NU = (PER * NOPS + NT - 1) / NT;
+  static constexpr int NV = KC ? 2 : 4;                      // float4 per unit
+  static constexpr int PLANE = ROWS * kRowBytes;
 
-  // position of float4 number idx inside the tile: (r = non-contraction index, kk = contraction index)
-  template <bool KC>
-  __device__ static __forceinline__ void pos(int idx, int& r, int& kk) {
-    if (KC) { r = idx / (BK / 4); kk = (idx % (BK / 4)) * 4; }      // 4 consecutive kk at one r
-    else    { kk = idx / (ROWS / 4); r = (idx % (ROWS / 4)) * 4; }  // 4 consecutive r at one kk
+  using Pieces = uint32_t[NU][3][NV * 2];                    // in pairs: k by k (KC), or row by row
+  float4 v[NU][NV];                                          // the tile on its way from memory
+  const float* p[NU];                                        // KC: the unit's row; else its four rows at k = 0
+  int a0[NU], a1[NU];                                        // views: what the unit keeps about its row or its k
+  int ld; uint32_t magic;
+  ConvView cv;
+
+  __device__ __forceinline__ static bool unit(int u, int t, int& op, int& w) {
+    const int idx = u * NT + t;
+    op = NOPS == 2 ? idx / PER : 0;
+    w = idx - op * PER;
+    return NU * NT == PER * NOPS || idx < PER * NOPS;
   }
 
-  // Element offset of the float4 at row `row` (non-contraction index), contraction index `kq` of the operand, and
-  // whether it exists: a matrix in memory (ld), or a view of a map (see OperandView)
-  template <bool KC, int VIEW>
-  __device__ static __forceinline__ int64_t offset(int row, int kq, int ld, const ConvView& cv, bool& ok) {
-    if (VIEW == VIEW_NONE) return KC ? (int64_t)row * ld + kq : (int64_t)kq * ld + row;
-    // the operand's own (row, column) whichever of them the product contracts
-    const int mrow = KC ? row : kq, col = KC ? kq : row;
-    if (VIEW == VIEW_PATCH) {
-      const int Wo = cv.W - 2, Ho = cv.H - 2;
-      const int x = mrow % Wo, t = mrow / Wo, y = t % Ho, b = t / Ho;
-      const int tap = col / cv.Cin, ci = col - tap * cv.Cin, dy = tap / 3, dx = tap - dy * 3;
-      return (((int64_t)b * cv.H + (y + dy)) * cv.W + (x + dx)) * cv.Cin + ci;
-    }
-    if (VIEW == VIEW_SHIFTED) {
-      const int Wo = cv.W - 2, Ho = cv.H - 2;
-      const int xx = mrow % cv.W, t = mrow / cv.W, yy = t % cv.H, b = t / cv.H;
-      const int tap = col / cv.Cout, co = col - tap * cv.Cout, dy = tap / 3, dx = tap - dy * 3;
-      const int y = yy - dy, x = xx - dx;
-      ok = ok && y >= 0 && y < Ho && x >= 0 && x < Wo;
-      return (((int64_t)b * Ho + y) * Wo + x) * cv.Cout + co;
-    }
-    // VIEW_TAPS: operand row = tap*Cout + co (the contraction index of the data gradient), column = ci
-    const int tap = mrow / cv.Cout, co = mrow - tap * cv.Cout;
-    return (int64_t)co * (9 * cv.Cin) + tap * cv.Cin + col;
-  }
-
-  template <bool KC, int VIEW = VIEW_NONE>
-  __device__ static __forceinline__ void load(const float* __restrict__ src, int ld, int r0, int k0, int R, int K,
-                                              float4 (&reg)[NL], const ConvView& cv = ConvView{}) {
+  // t: the thread's place among the loader's; r0, R: first row of the tile and rows of the operand
+  __device__ __forceinline__ void begin(const float* src, const float* rsrc, int ld_, int r0, int R, int kbeg, const ConvView& c, int t) {
+    ld = ld_; cv = c;
+    if (VIEW != VIEW_NONE) magic = 0xFFFFFFFFu / (uint32_t)(VIEW == VIEW_PATCH ? c.Cin : c.Cout) + 1u;
 #pragma unroll
-    for (int it = 0; it < NL; ++it) {
-      const int idx = it * NT + (int)threadIdx.x;
-      int r, kk; pos<KC>(idx, r, kk);
-      bool ok = idx < CNT && (r0 + r) < R && (k0 + kk) < K;
-      const int64_t off = ok ? offset<KC, VIEW>(r0 + r, k0 + kk, ld, cv, ok) : 0;
-      reg[it] = ok ? *reinterpret_cast<const float4*>(src + off) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  }
-
-  // sign bits of the four elements that load<KC> would read (0 when out of range)
-  template <bool KC, int VIEW = VIEW_NONE>
-  __device__ static __forceinline__ void load_bits(const uint32_t* __restrict__ zb, int64_t z_off, int ld, int r0,
-                                                   int k0, int R, int K, uint32_t (&reg)[NL], const ConvView& cv = ConvView{}) {
-#pragma unroll
-    for (int it = 0; it < NL; ++it) {
-      const int idx = it * NT + (int)threadIdx.x;
-      int r, kk; pos<KC>(idx, r, kk);
-      bool ok = idx < CNT && (r0 + r) < R && (k0 + kk) < K;
-      const int64_t off = z_off + (ok ? offset<KC, VIEW>(r0 + r, k0 + kk, ld, cv, ok) : 0);
-      reg[it] = ok ? (zb[off >> 5] >> (off & 31)) & 0xFu : 0u;
-    }
-  }
-
-  template <bool KC>
-  __device__ static __forceinline__ void store(float (*lds)[ROWS + PAD], const float4 (&reg)[NL]) {
-#pragma unroll
-    for (int it = 0; it < NL; ++it) {
-      const int idx = it * NT + (int)threadIdx.x;
-      if (idx < CNT) {
-        int r, kk; pos<KC>(idx, r, kk);
-        if (KC) {
-          lds[kk + 0][r] = reg[it].x; lds[kk + 1][r] = reg[it].y;
-          lds[kk + 2][r] = reg[it].z; lds[kk + 3][r] = reg[it].w;
+    for (int u = 0; u < NU; ++u) {
+      int op, w;
+      if (!unit(u, t, op, w)) { op = 0; w = 0; }
+      const float* s = op ? rsrc : src;
+      if (KC) {
+        const int row = r0 + (w >> 2) < R ? r0 + (w >> 2) : R - 1;
+        if (VIEW == VIEW_PATCH) {
+          const int Wo = c.W - 2, Ho = c.H - 2;
+          const int x = row % Wo, tt = row / Wo, y = tt % Ho, b = tt / Ho;
+          p[u] = s + (((int64_t)b * c.H + y) * c.W + x) * c.Cin;
+        } else if (VIEW == VIEW_SHIFTED) {
+          const int xx = row % c.W, tt = row / c.W, yy = tt % c.H, b = tt / c.H;
+          p[u] = s + (int64_t)b * (c.H - 2) * (c.W - 2) * c.Cout;
+          a0[u] = yy; a1[u] = xx;
         } else {
-          *reinterpret_cast<float4*>(&lds[kk][r]) = reg[it];
+          p[u] = s + (int64_t)row * ld + (w & 3) * 8;
+        }
+      } else {
+        const int rg = w % (ROWS / 4), last = (R - 1) & ~3;
+        const int r = r0 + rg * 4 < R ? r0 + rg * 4 : last;
+        if (VIEW == VIEW_PATCH) {                            // r is a column of the patch matrix: a tap and a channel
+          const int tap = (int)__umulhi((uint32_t)r, magic), ci = r - tap * c.Cin, dy = (tap * 11) >> 5, dx = tap - dy * 3;
+          p[u] = s + ((int64_t)dy * c.W + dx) * c.Cin + ci;
+          // the position of the unit's first k: row of the map (over all images) and column
+          const int pos = kbeg + (w / (ROWS / 4)) * 4, Wo = c.W - 2, Ho = c.H - 2;
+          const int x = pos % Wo, tt = pos / Wo, y = tt % Ho, b = tt / Ho;
+          a0[u] = b * c.H + y; a1[u] = x | (y << 16);
+        } else {
+          p[u] = s + r;
         }
       }
     }
   }
 
-  template <bool KC>
-  __device__ static __forceinline__ void store_bits(float (*lds)[ROWS + PAD], const uint32_t (&reg)[NL]) {
+  // the tile at k0; called for k0 = kbeg, kbeg + BK, ... in order
+  // WHOLE: no k of the tile is past the end
+  template <bool WHOLE>
+  __device__ __forceinline__ void load(int k0, int kend, int t) {
+    const bool whole = WHOLE || k0 + BK <= kend;             // (uniform)
 #pragma unroll
-    for (int it = 0; it < NL; ++it) {
-      const int idx = it * NT + (int)threadIdx.x;
-      if (idx < CNT) {
-        int r, kk; pos<KC>(idx, r, kk);
-        float4 v;
-        v.x = (reg[it] & 1u) ? 1.f : -1.f; v.y = (reg[it] & 2u) ? 1.f : -1.f;
-        v.z = (reg[it] & 4u) ? 1.f : -1.f; v.w = (reg[it] & 8u) ? 1.f : -1.f;
-        if (KC) {
-          lds[kk + 0][r] = v.x; lds[kk + 1][r] = v.y; lds[kk + 2][r] = v.z; lds[kk + 3][r] = v.w;
-        } else {
-          *reinterpret_cast<float4*>(&lds[kk][r]) = v;
+    for (int u = 0; u < NU; ++u) {
+      int op, w;
+      if (!unit(u, t, op, w)) continue;
+      const int kk = k0 + (KC ? (w & 3) * 8 : (w / (ROWS / 4)) * 4);
+      if (KC) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int k = kk + q * 4;
+          bool ok = whole || k < kend;
+          const float* a;
+          if (VIEW == VIEW_PATCH) {
+            const int tap = (int)__umulhi((uint32_t)k, magic), ci = k - tap * cv.Cin, dy = (tap * 11) >> 5, dx = tap - dy * 3;
+            a = p[u] + (dy * cv.W + dx) * cv.Cin + ci;
+          } else if (VIEW == VIEW_SHIFTED) {
+            const int tap = (int)__umulhi((uint32_t)k, magic), co = k - tap * cv.Cout, dy = (tap * 11) >> 5, dx = tap - dy * 3;
+            const int y = a0[u] - dy, x = a1[u] - dx;
+            ok = ok && y >= 0 && y < cv.H - 2 && x >= 0 && x < cv.W - 2;
+            a = p[u] + ((int64_t)y * (cv.W - 2) + x) * cv.Cout + co;
+          } else {
+            a = p[u] + k0 + q * 4;
+          }
+          v[u][q] = ok ? *reinterpret_cast<const float4*>(a) : make_float4(0.f, 0.f, 0.f, 0.f);
         }
+      } else if (VIEW == VIEW_PATCH) {
+        int x = a1[u] & 0xFFFF, y = a1[u] >> 16, row = a0[u];
+        const int Wo = cv.W - 2, Ho = cv.H - 2;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const bool ok = whole || kk + j < kend;
+          v[u][j] = ok ? *reinterpret_cast<const float4*>(p[u] + ((int64_t)row * cv.W + x) * cv.Cin) : make_float4(0.f, 0.f, 0.f, 0.f);
+          if (j < 3 && ++x == Wo) { x = 0; ++row; if (++y == Ho) { y = 0; row += 2; } }
+        }
+        x = (a1[u] & 0xFFFF) + BK; y = a1[u] >> 16; row = a0[u];
+        while (x >= Wo) { x -= Wo; ++row; if (++y == Ho) { y = 0; row += 2; } }
+        a0[u] = row; a1[u] = x | (y << 16);
+      } else {
+        const float* a;
+        int64_t step;
+        if (VIEW == VIEW_TAPS) {                             // four channels of one tap (channel counts are multiples of 4)
+          const int tap = (int)__umulhi((uint32_t)kk, magic), co = kk - tap * cv.Cout;
+          step = 9 * cv.Cin;
+          a = p[u] + co * step + tap * cv.Cin;
+        } else {
+          step = ld;
+          a = p[u] + kk * step;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          v[u][j] = (whole || kk + j < kend) ? *reinterpret_cast<const float4*>(a + j * step) : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+    }
+  }
+
+  // unit u of v into its pieces.  sums: [NU][4], receives the column sums of the unit's rows (k-major operands; bias
+  // gradients)
+  template <bool INF>
+  __device__ __forceinline__ void split_unit(int u, uint32_t (&s)[3][NV * 2], bool want_sums, float (&sums)[NU][4]) const {
+    if constexpr (KC) {
+      const float x[8] = {v[u][0].x, v[u][0].y, v[u][0].z, v[u][0].w, v[u][1].x, v[u][1].y, v[u][1].z, v[u][1].w};
+      split_pairs<INF, 4>(x, s);
+    } else {
+      const float x[16] = {v[u][0].x, v[u][1].x, v[u][2].x, v[u][3].x, v[u][0].y, v[u][1].y, v[u][2].y, v[u][3].y,
+                           v[u][0].z, v[u][1].z, v[u][2].z, v[u][3].z, v[u][0].w, v[u][1].w, v[u][2].w, v[u][3].w};
+      if (want_sums) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sums[u][r] += (x[4 * r] + x[4 * r + 1]) + (x[4 * r + 2] + x[4 * r + 3]);
+      }
+      split_pairs<INF, 8>(x, s);
+    }
+  }
+  __device__ __forceinline__ static void store_unit(char* lds, int op, int w, const uint32_t (&s)[3][NV * 2]) {
+    char* base = lds + op * 3 * PLANE;
+    if constexpr (KC) {
+      char* at = base + unit_at(w >> 2, w & 3);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) *reinterpret_cast<uint4*>(at + c * PLANE) = make_uint4(s[c][0], s[c][1], s[c][2], s[c][3]);
+    } else {
+      const int rg = w % (ROWS / 4), kq = w / (ROWS / 4);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        char* at = base + unit_at(rg * 4 + r, kq >> 1) + (kq & 1) * 8;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) *reinterpret_cast<uint2*>(at + c * PLANE) = make_uint2(s[c][2 * r], s[c][2 * r + 1]);
+      }
+    }
+  }
+  // the two together, unit by unit
+  template <bool INF>
+  __device__ __forceinline__ void split_store(char* lds, int t, bool want_sums, float (&sums)[NU][4]) const {
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      int op, w;
+      if (!unit(u, t, op, w)) continue;
+      uint32_t s[3][NV * 2];
+      split_unit<INF>(u, s, want_sums, sums);
+      store_unit(lds, op, w, s);
+    }
+  }
+};
+
+// The same units for the +-1 operand: sign bits in, one plane of bf16 out.  k past the end need not be zero (the other
+// operand's is); its bits are not read.
+template <int NT, int ROWS, bool KC, int VIEW>
+struct SignLoader {
+  static constexpr int PER = KC ? ROWS * 4 : ROWS * 2;
+  static constexpr int NU = (PER + NT - 1) / NT;
+  uint32_t b[NU];                                            // KC: 8 bits; else 4 x 4 bits, k by k
+  int64_t p[NU];                                             // bit offset: KC the unit's row; else its rows at k = 0
+  int ld; uint32_t magic; ConvView cv;
+
+  __device__ __forceinline__ void begin(int64_t z_off, int ld_, int r0, int R, const ConvView& c, int t) {
+    ld = ld_; cv = c;
+    if (VIEW == VIEW_TAPS) magic = 0xFFFFFFFFu / (uint32_t)c.Cout + 1u;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int w = u * NT + t < PER ? u * NT + t : 0;
+      if (KC) {
+        const int row = r0 + (w >> 2) < R ? r0 + (w >> 2) : R - 1;
+        p[u] = z_off + (int64_t)row * ld;
+      } else {
+        const int rg = w % (ROWS / 4);
+        p[u] = z_off + (r0 + rg * 4 < R ? r0 + rg * 4 : (R - 1) & ~3);
+      }
+    }
+  }
+  __device__ __forceinline__ void load(const uint32_t* zb, int k0, int kend, int t) {
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int w = u * NT + t;
+      if (NU * NT != PER && w >= PER) continue;
+      if (KC) {
+        const int k = k0 + (w & 3) * 8;
+        // two groups of four bits (K is a multiple of 4, so a group lies in one word)
+        const int64_t o0 = p[u] + (k < kend ? k : kend - 4), o1 = p[u] + (k + 4 < kend ? k + 4 : kend - 4);
+        b[u] = ((zb[o0 >> 5] >> (o0 & 31)) & 0xFu) | (((zb[o1 >> 5] >> (o1 & 31)) & 0xFu) << 4);
+      } else {
+        const int k = k0 + (w / (ROWS / 4)) * 4;
+        uint32_t x = 0;
+        int64_t o, step;
+        if (VIEW == VIEW_TAPS) {
+          const int kc = k < kend ? k : kend - 4;
+          const int tap = (int)__umulhi((uint32_t)kc, magic), co = kc - tap * cv.Cout;
+          step = 9 * cv.Cin;
+          o = p[u] + co * step + tap * cv.Cin;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) { const int64_t q = o + j * step; x |= ((zb[q >> 5] >> (q & 31)) & 0xFu) << (4 * j); }
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int64_t q = p[u] + (int64_t)(k + j < kend ? k + j : kend - 1) * ld;
+            x |= ((zb[q >> 5] >> (q & 31)) & 0xFu) << (4 * j);
+          }
+        }
+        b[u] = x;
+      }
+    }
+  }
+  __device__ __forceinline__ void store(char* lds, int t) const {
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int w = u * NT + t;
+      if (NU * NT != PER && w >= PER) continue;
+      const uint32_t x = b[u];
+      if (KC) {
+        *reinterpret_cast<uint4*>(lds + unit_at(w >> 2, w & 3)) =
+            make_uint4(sign_pair(x, x >> 1), sign_pair(x >> 2, x >> 3), sign_pair(x >> 4, x >> 5), sign_pair(x >> 6, x >> 7));
+      } else {
+        const int rg = w % (ROWS / 4), kq = w / (ROWS / 4);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          *reinterpret_cast<uint2*>(lds + unit_at(rg * 4 + r, kq >> 1) + (kq & 1) * 8) =
+              make_uint2(sign_pair(x >> r, x >> (4 + r)), sign_pair(x >> (8 + r), x >> (12 + r)));
       }
     }
   }
 };
 
-// XV, YV: OperandView of X/RX and of Y/RY (convolutions without a patch matrix in memory)
+// rows of 64 bytes the operand planes take: three per element and operand, one for signs
+constexpr int gemm_f32_rows(int bm, int bn, bool has_rx, int rym) {
+  return 3 * bm * (has_rx ? 2 : 1) + 3 * bn * (rym == RY_MEM ? 2 : 1) + (rym == RY_BITS ? bn : 0);
+}
+constexpr int gemm_f32_lds(int bm, int bn, int wm, int wn, bool has_rx, int rym, int epi) {
+  const int tiles = gemm_f32_rows(bm, bn, has_rx, rym) * kRowBytes;
+  const int upd = epi == EPI_WGRAD_FUSED ? wm * wn * fused_update_lds_floats() * 4 : 0;    // the epilogue reuses the space
+  return tiles > upd ? tiles : upd;
+}
+
+// the products of one k-step of 16 of two numbers in three pieces: those of the first pieces to m, the others to t
+__device__ __forceinline__ void mfma6(const bf16x8 (&x)[3], const bf16x8 (&y)[3], floatx16& m, floatx16& t) {
+  m = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[0], m, 0, 0, 0);
+  t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[2], y[0], t, 0, 0, 0);
+  t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[2], t, 0, 0, 0);
+  t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], y[1], t, 0, 0, 0);
+  t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], y[0], t, 0, 0, 0);
+  t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[1], t, 0, 0, 0);
+}
+__device__ __forceinline__ void mfma3(const bf16x8 (&x)[3], const bf16x8& v, floatx16& m, floatx16& t) {
+  m = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], v, m, 0, 0, 0);
+  t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[2], v, t, 0, 0, 0);
+  t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], v, t, 0, 0, 0);
+}
+// the same on the fp32 matrix instruction, from the numbers the pieces add up to
+__device__ __forceinline__ float joined(const bf16x8 (&x)[3], int j) { return (float)x[0][j] + ((float)x[1][j] + (float)x[2][j]); }
+__device__ __forceinline__ void mfma_whole(const bf16x8 (&x)[3], const bf16x8 (&y)[3], floatx16& t) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) t = __builtin_amdgcn_mfma_f32_32x32x2f32(joined(x, j), joined(y, j), t, 0, 0, 0);
+}
+__device__ __forceinline__ void mfma_whole(const bf16x8 (&x)[3], const bf16x8& v, floatx16& t) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) t = __builtin_amdgcn_mfma_f32_32x32x2f32(joined(x, j), (float)v[j], t, 0, 0, 0);
+}
+
+// XV, YV: OperandView of X/RX and of Y/RY (convolutions without a patch matrix in memory).  FM == 1: a Hutchinson probe
+// other than the step's last (fused) or first (forward, data gradient): the R-products alone.
 template <int BM, int BN, int WM, int WN, bool X_KC, bool Y_KC, bool HAS_RX, int RYM, int EPI, int FM = 0, int XV = VIEW_NONE,
           int YV = VIEW_NONE>
-__global__ __launch_bounds__(NT) void dual_gemm_f32(GemmArgs a) {
-  static_assert(WM * WN == 4, "four waves per block");
+__global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
+  constexpr int NT = WM * WN * 64;
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
   static_assert(TM >= 1 && TN >= 1, "wave tile must hold at least one 32x32 MFMA tile");
+  constexpr bool HAS_C = FM != 1;                            // the plain product is computed
+  constexpr bool HAS_R = HAS_RX || RYM != RY_NONE;           // the R-companion is
+  constexpr bool STAGED = X_KC && Y_KC && BM == 64 && BN == 64;
   const int worker = nth_active_worker(a.active_mask, blockIdx.y);    // grid y covers the active workers
 
   const int tiles_m = (a.M + BM - 1) / BM;
   const int tm = blockIdx.x % tiles_m, tn = blockIdx.x / tiles_m;
   const int row0 = tm * BM, col0 = tn * BN;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm0 = (wave % WM) * (BM / WM), wn0 = (wave / WM) * (BN / WN);
   const int l32 = lane & 31, lhalf = lane >> 5;
 
-  __shared__ __attribute__((aligned(16))) float Xs[BK][BM + PAD];
-  __shared__ __attribute__((aligned(16))) float RXs[HAS_RX ? BK : 1][BM + PAD];
-  __shared__ __attribute__((aligned(16))) float Ys[BK][BN + PAD];
-  __shared__ __attribute__((aligned(16))) float RYs[RYM != RY_NONE ? BK : 1][BN + PAD];
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  using LX = TileLoader<NT, BM, X_KC, HAS_RX ? 2 : 1, XV>;
+  using LY = TileLoader<NT, BN, Y_KC, RYM == RY_MEM ? 2 : 1, YV>;
+  using LS = SignLoader<NT, BN, Y_KC, YV>;
+  char* Xl = lds;
+  char* Yl = Xl + 3 * (HAS_RX ? 2 : 1) * LX::PLANE;
+  char* Sl = Yl + 3 * LY::PLANE;                             // signs, or the planes of RY
 
   const float* X = reinterpret_cast<const float*>(a.X) + (int64_t)worker * a.x_wstride;
   const float* RX = HAS_RX ? reinterpret_cast<const float*>(a.RX) + (int64_t)worker * a.x_wstride : nullptr;
@@ -157,87 +401,196 @@ __global__ __launch_bounds__(NT) void dual_gemm_f32(GemmArgs a) {
   const float* RY = RYM == RY_MEM ? reinterpret_cast<const float*>(a.RY) + (int64_t)worker * a.y_wstride : nullptr;
   const uint32_t* zb = a.zbits + (int64_t)worker * a.z_stride;
 
-  using LX = TileLoader<BM>;
-  using LY = TileLoader<BN>;
-  float4 xr[LX::NL], rxr[LX::NL], yr[LY::NL], ryr[LY::NL];
-  uint32_t zr[LY::NL];
-
-  floatx16 acc[TM][TN], racc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) { acc[i][j][r] = 0.f; racc[i][j][r] = 0.f; }
-
-  float gb_acc = 0.f, hzb_acc = 0.f;     // EPI_WGRAD: column sums of X and RX (bias gradients)
-
-  // the slice of the contraction this block covers (all of it unless the weight gradient is cut along k)
+  // the slice of the contraction this block covers (all of it unless the product is cut along k)
   const bool sliced = (EPI == EPI_WGRAD || EPI == EPI_RELU || EPI == EPI_LINEAR || EPI == EPI_MASK) && a.ksplit > 1;
   const int kchunk = sliced ? ((a.K + a.ksplit - 1) / a.ksplit + BK - 1) / BK * BK : a.K;
   const int kbeg = sliced ? (int)blockIdx.z * kchunk : 0;
   const int kend = sliced ? (kbeg + kchunk < a.K ? kbeg + kchunk : a.K) : a.K;
   const int nkt = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
-  auto fetch = [&](int kt) {
+
+  // acc, racc: the chains of the first pieces' products, then the results; t, tr: those of the others
+  floatx16 acc[TM][TN], racc[TM][TN], t[TM][TN], tr[TM][TN];
+  const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  LX lx; LY ly; LS ls;
+  // a k-major Y that keeps half the block busy leaves the signs to the other half
+  constexpr int S0 = RYM == RY_BITS && LY::PER * 2 == NT && LS::PER * 2 == NT ? NT / 2 : 0;
+  const int ts = S0 ? (tid + NT - S0) % NT : tid;
+  constexpr bool SUMS = EPI == EPI_WGRAD || EPI == EPI_WGRAD_FUSED;      // bias gradients: column sums of X and RX
+  const bool want_sums = SUMS && tn == 0;
+  float sums[LX::NU][4], none[LY::NU][4];
+
+  // this lane's unit of k-step 0 in row l32 of each tile; k-step 1 is 32 bytes further under the swizzle
+  int xat[TM], yat[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) xat[i] = unit_at(wm0 + i * 32 + l32, lhalf);
+#pragma unroll
+  for (int j = 0; j < TN; ++j) yat[j] = unit_at(wn0 + j * 32 + l32, lhalf);
+
+  auto fetch = [&](int kt, auto whole) {
     const int k0 = kbeg + kt * BK;
-    LX::template load<X_KC, XV>(X, a.ldx, row0, k0, a.M, kend, xr, a.cv);
-    if (HAS_RX) LX::template load<X_KC, XV>(RX, a.ldx, row0, k0, a.M, kend, rxr, a.cv);
-    LY::template load<Y_KC, YV>(Y, a.ldy, col0, k0, a.N, kend, yr, a.cv);
-    if (RYM == RY_MEM) LY::template load<Y_KC, YV>(RY, a.ldy, col0, k0, a.N, kend, ryr, a.cv);
-    if (RYM == RY_BITS) LY::template load_bits<Y_KC, YV>(zb, a.z_off, a.ldy, col0, k0, a.N, kend, zr, a.cv);
+    lx.template load<decltype(whole)::value>(k0, kend, tid);
+    ly.template load<decltype(whole)::value>(k0, kend, tid);
+    if (RYM == RY_BITS && !STAGED) ls.load(zb, k0, kend, ts);
   };
-
-  if (nkt > 0) fetch(0);
-  for (int kt = 0; kt < nkt; ++kt) {
-    LX::template store<X_KC>(Xs, xr);
-    if (HAS_RX) LX::template store<X_KC>(RXs, rxr);
-    LY::template store<Y_KC>(Ys, yr);
-    if (RYM == RY_MEM) LY::template store<Y_KC>(RYs, ryr);
-    if (RYM == RY_BITS) LY::template store_bits<Y_KC>(RYs, zr);
-    __syncthreads();
-    if (kt + 1 < nkt) fetch(kt + 1);
-
-    if ((EPI == EPI_WGRAD || EPI == EPI_WGRAD_FUSED) && tn == 0 && (int)threadIdx.x < BM) {
+  auto fetch_signs = [&](int kt) { if (RYM == RY_BITS) ls.load(zb, kbeg + kt * BK, kend, ts); };   // (one tile ahead of the products)
+  typename LX::Pieces xs;                                    // STAGED: the pieces of the next tile
+  typename LY::Pieces ys;
+  auto split = [&](auto inf) {
 #pragma unroll
-      for (int kk = 0; kk < BK; ++kk) {
-        gb_acc += Xs[kk][threadIdx.x];
-        if (HAS_RX) hzb_acc += RXs[kk][threadIdx.x];
+    for (int u = 0; u < LX::NU; ++u) lx.template split_unit<decltype(inf)::value>(u, xs[u], want_sums, sums);
+#pragma unroll
+    for (int u = 0; u < LY::NU; ++u) ly.template split_unit<decltype(inf)::value>(u, ys[u], false, none);
+  };
+  // Tile kt: its pieces go to LDS, then its products run.  STAGED (64 x 64 tiles of k-contiguous operands): the next tile
+  // has arrived meanwhile, is split into pieces while the products run, and the one after it is asked for.  MAIN: that
+  // one exists and is whole, so the step is straight-line code and the splitting is issued between the multiplies (forward,
+  // 1024 wide: 92 -> 75 us).  Otherwise the next tile is asked for before the products and split after them: k-major
+  // operands and larger tiles have no registers for the pieces (spills, half the speed).
+  auto step = [&](int kt, auto main, auto inf) {
+    constexpr bool MAIN = decltype(main)::value;
+    constexpr bool INF = decltype(inf)::value;
+    if constexpr (STAGED) {
+#pragma unroll
+      for (int u = 0; u < LX::NU; ++u) {
+        int op, w;
+        if (LX::unit(u, tid, op, w)) LX::store_unit(Xl, op, w, xs[u]);
       }
+#pragma unroll
+      for (int u = 0; u < LY::NU; ++u) {
+        int op, w;
+        if (LY::unit(u, tid, op, w)) LY::store_unit(Yl, op, w, ys[u]);
+      }
+    } else {
+      lx.template split_store<INF>(Xl, tid, want_sums, sums);
+      ly.template split_store<INF>(Yl, tid, false, none);
     }
-
+    if (RYM == RY_BITS) ls.store(Sl, ts);
+    __syncthreads();
+    if (!STAGED) {
+      if (kt + 1 < nkt) fetch(kt + 1, std::false_type{});
+    } else if (MAIN || kt + 1 < nkt) {
+      split(inf);
+      fetch_signs(kt + 1);
+      if (MAIN) fetch(kt + 2, std::true_type{});
+      else if (kt + 2 < nkt) fetch(kt + 2, std::false_type{});
+    }
 #pragma unroll
-    for (int kk = 0; kk < BK; kk += 2) {
-      const int ks = kk + lhalf;
-      float xa[TM], rxa[TM], yb[TN], ryb[TN];
+    for (int s = 0; s < 2; ++s) {
+      bf16x8 x[TM][3], rx[TM][3], y[TN][3], ry[TN][3];
+      auto piece = [](const char* at) { return *reinterpret_cast<const bf16x8*>(at); };
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        xa[i] = Xs[ks][wm0 + i * 32 + l32];
-        if (HAS_RX) rxa[i] = RXs[ks][wm0 + i * 32 + l32];
-      }
+      for (int c = 0; c < 3; ++c) {
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        yb[j] = Ys[ks][wn0 + j * 32 + l32];
-        if (RYM != RY_NONE) ryb[j] = RYs[ks][wn0 + j * 32 + l32];
+        for (int i = 0; i < TM; ++i) {
+          x[i][c] = piece(Xl + c * LX::PLANE + (xat[i] ^ (s * 32)));
+          if (HAS_RX) rx[i][c] = piece(Xl + (3 + c) * LX::PLANE + (xat[i] ^ (s * 32)));
+        }
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          if (HAS_C || HAS_RX) y[j][c] = piece(Yl + c * LY::PLANE + (yat[j] ^ (s * 32)));
+          if (RYM == RY_MEM || (RYM == RY_BITS && c == 0)) ry[j][c] = piece(Sl + c * LY::PLANE + (yat[j] ^ (s * 32)));
+        }
       }
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-          // (a Hutchinson probe before the last, FM == 1, only needs the R-products)
-          if (FM != 1) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[i], yb[j], acc[i][j], 0, 0, 0);
-          if (HAS_RX) racc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(rxa[i], yb[j], racc[i][j], 0, 0, 0);
-          if (RYM != RY_NONE) racc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[i], ryb[j], racc[i][j], 0, 0, 0);
+          if constexpr (INF) {
+            if (HAS_C) mfma_whole(x[i], y[j], acc[i][j]);
+            if (HAS_RX) mfma_whole(rx[i], y[j], racc[i][j]);
+            if (RYM == RY_MEM) mfma_whole(x[i], ry[j], racc[i][j]);
+            if (RYM == RY_BITS) mfma_whole(x[i], ry[j][0], racc[i][j]);
+          } else {
+            if (HAS_C) mfma6(x[i], y[j], acc[i][j], t[i][j]);
+            if (HAS_RX) mfma6(rx[i], y[j], racc[i][j], tr[i][j]);
+            if (RYM == RY_MEM) mfma6(x[i], ry[j], racc[i][j], tr[i][j]);
+            if (RYM == RY_BITS) mfma3(x[i], ry[j][0], racc[i][j], tr[i][j]);
+          }
         }
     }
     __syncthreads();
+  };
+  // the whole contraction; returns whether a result is not a number
+  auto contract = [&](auto with_main, auto inf) {
+    lx.begin(X, RX, a.ldx, row0, a.M, kbeg, a.cv, tid);
+    ly.begin(Y, RY, a.ldy, col0, a.N, kbeg, a.cv, tid);
+    if (RYM == RY_BITS) ls.begin(a.z_off, a.ldy, col0, a.N, a.cv, ts);
+#pragma unroll
+    for (int u = 0; u < LX::NU; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sums[u][r] = 0.f;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) { acc[i][j] = zero; racc[i][j] = zero; t[i][j] = zero; tr[i][j] = zero; }
+    if (nkt > 0) fetch(0, std::false_type{});
+    if (STAGED) {
+      if (nkt > 0) { fetch_signs(0); split(inf); }
+      if (nkt > 1) fetch(1, std::false_type{});
+    }
+    int kt = 0;
+    if (STAGED && decltype(with_main)::value)
+      for (; kbeg + (kt + 3) * BK <= kend; ++kt) step(kt, std::true_type{}, inf);
+    for (; kt < nkt; ++kt) step(kt, std::false_type{}, inf);
+    bool nan = false;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        if (HAS_C) acc[i][j] += t[i][j];
+        if (HAS_R) racc[i][j] += tr[i][j];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          if (HAS_C) nan |= __builtin_isunordered(acc[i][j][r], acc[i][j][r]);
+          if (HAS_R) nan |= __builtin_isunordered(racc[i][j][r], racc[i][j][r]);
+        }
+      }
+    return nan;
+  };
+  // An infinity has no pieces (inf - inf), and inf * (y1 + y2 + y3) would be none either where y2 is 0 or of the other sign:
+  // should a result be no number, the block starts over with the fp32 matrix instruction on whole numbers, which gives
+  // what such operands give.
+  if (__syncthreads_or(contract(std::true_type{}, std::false_type{}))) contract(std::false_type{}, std::true_type{});
+
+  if constexpr (SUMS) {
+    // the units of a row lie with eight threads, 4 k each: their sums are added in order of k (the loop's last barrier is
+    // behind the last read of the tiles)
+    if (tn == 0) {
+      float* part = reinterpret_cast<float*>(lds);           // [operand][8][BM]
+#pragma unroll
+      for (int u = 0; u < LX::NU; ++u) {
+        int op, w;
+        if (!LX::unit(u, tid, op, w)) continue;
+        const int rg = w % (BM / 4), kq = w / (BM / 4);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[(op * 8 + kq) * BM + rg * 4 + r] = sums[u][r];
+      }
+      __syncthreads();
+      const int m = row0 + tid;
+      if (tid < BM && m < a.M) {
+        float gb = 0.f, hzb = 0.f;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          gb += part[q * BM + tid];
+          if (HAS_RX) hzb += part[(8 + q) * BM + tid];
+        }
+        if (sliced) {
+          float* pb = a.part_b + (((int64_t)blockIdx.z * a.k + worker) * 2) * a.M;
+          pb[m] = gb; pb[a.M + m] = hzb;
+        } else {
+          a.gb[(int64_t)worker * a.c_wstride + m] = gb;
+          a.hzb[(int64_t)worker * a.c_wstride + m] = hzb;
+        }
+      }
+      __syncthreads();
+    }
   }
 
   if constexpr (EPI == EPI_WGRAD_FUSED) {
     // The update of Section IV-B applied to the tile instead of storing gW and HzW (see dw_fused_update.h): whole
-    // 128 x 128 tiles, wave tiles of 64 x 64; a private LDS region per wave (dynamic shared memory; the operand
-    // tiles above are static).
-    static_assert(TM == 2 && TN == 2, "four waves of 64 x 64");
-    extern __shared__ __attribute__((aligned(16))) float fused_lds[];
+    // tiles, wave tiles of 32 x 64; a private LDS region per wave where the operand tiles were.
+    static_assert(TN == 2, "waves of 64 columns");
+    float* fused_lds = reinterpret_cast<float*>(lds);
     const FuseArgs& f = a.fu;
     typedef const char __attribute__((address_space(4)))* karg_bytes;
     typedef const float __attribute__((address_space(4)))* karg_floats;
@@ -262,12 +615,13 @@ __global__ __launch_bounds__(NT) void dual_gemm_f32(GemmArgs a) {
     __shared__ double red[NT / 64];
     if (lane == 0) red[wave] = ws;
     __syncthreads();
-    if (threadIdx.x == 0 && f.dist) {
-      double t = 0.0;
+    if (tid == 0 && f.dist) {
+      double sum = 0.0;
 #pragma unroll
-      for (int w = 0; w < NT / 64; ++w) t += red[w];
-      f.partials[(int64_t)worker * f.part_stride + f.part_base + blockIdx.x] = t;
+      for (int w = 0; w < NT / 64; ++w) sum += red[w];
+      f.partials[(int64_t)worker * f.part_stride + f.part_base + blockIdx.x] = sum;
     }
+    return;
   }
   // epilogue: lane holds column n = l32 of each 32x32 tile, rows (r/4)*8 + lhalf*4 + r%4
   float* C = reinterpret_cast<float*>(a.C) + (int64_t)worker * a.c_wstride;
@@ -277,7 +631,7 @@ __global__ __launch_bounds__(NT) void dual_gemm_f32(GemmArgs a) {
     RC = C + a.part_stride;
   }
 #pragma unroll
-  for (int j = 0; j < (EPI == EPI_WGRAD_FUSED ? 0 : TN); ++j) {
+  for (int j = 0; j < TN; ++j) {
     const int n = col0 + wn0 + j * 32 + l32;
     const bool n_ok = n < a.N;
     float bias = 0.f, cz = 0.f;
@@ -315,18 +669,6 @@ __global__ __launch_bounds__(NT) void dual_gemm_f32(GemmArgs a) {
           C[o] = c;
           RC[o] = rc;
         }
-      }
-    }
-  }
-  if ((EPI == EPI_WGRAD || EPI == EPI_WGRAD_FUSED) && tn == 0 && (int)threadIdx.x < BM) {
-    const int m = row0 + threadIdx.x;
-    if (m < a.M) {
-      if (sliced) {
-        float* pb = a.part_b + (((int64_t)blockIdx.z * a.k + worker) * 2) * a.M;
-        pb[m] = gb_acc; pb[a.M + m] = hzb_acc;
-      } else {
-        a.gb[(int64_t)worker * a.c_wstride + m] = gb_acc;
-        a.hzb[(int64_t)worker * a.c_wstride + m] = hzb_acc;
       }
     }
   }
@@ -369,49 +711,59 @@ __global__ __launch_bounds__(256) void sum_slices_kernel(GemmArgs a) {
   }
 }
 
+// a kernel instance with its dynamic LDS
+template <int BM, int BN, int WM, int WN, bool X_KC, bool Y_KC, bool HAS_RX, int RYM, int EPI, int FM = 0, int XV = VIEW_NONE,
+          int YV = VIEW_NONE>
+static hipError_t launch_instance(const GemmArgs& a, dim3 grid, hipStream_t s) {
+  constexpr int smem = gemm_f32_lds(BM, BN, WM, WN, HAS_RX, RYM, EPI);
+  static_assert(smem <= 160 * 1024 - 256, "a compute unit's LDS");
+  auto kern = dual_gemm_f32<BM, BN, WM, WN, X_KC, Y_KC, HAS_RX, RYM, EPI, FM, XV, YV>;
+  if (smem > 64 * 1024) {
+    static LdsLimitOnce lim;
+    const hipError_t e = lim.raise(reinterpret_cast<const void*>(kern), smem);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kern, grid, dim3(WM * WN * 64), smem, s, a);
+  return hipGetLastError();
+}
+
 template <int BM, int BN, int WM, int WN>
 static hipError_t launch_shape(const GemmArgs& a, hipStream_t s) {
   const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
   const bool sliced = (a.epi == EPI_WGRAD || a.epi == EPI_RELU || a.epi == EPI_LINEAR || a.epi == EPI_MASK) && a.ksplit > 1;
-  const dim3 grid((unsigned)tiles, (unsigned)active_count(a.active_mask, a.k), (unsigned)(sliced ? a.ksplit : 1)), block(NT);
-#define DW_LAUNCH(XKC, YKC, RX, RYM, EPI) \
-  hipLaunchKernelGGL((dual_gemm_f32<BM, BN, WM, WN, XKC, YKC, RX, RYM, EPI>), grid, block, 0, s, a)
-#define DW_LAUNCH_R(XKC, YKC, RX, RYM, EPI) \
-  hipLaunchKernelGGL((dual_gemm_f32<BM, BN, WM, WN, XKC, YKC, RX, RYM, EPI, 1>), grid, block, 0, s, a)
-#define DW_LAUNCH_V(XKC, YKC, RX, RYM, EPI, XV, YV) \
-  hipLaunchKernelGGL((dual_gemm_f32<BM, BN, WM, WN, XKC, YKC, RX, RYM, EPI, 0, XV, YV>), grid, block, 0, s, a)
+  const dim3 grid((unsigned)tiles, (unsigned)active_count(a.active_mask, a.k), (unsigned)(sliced ? a.ksplit : 1));
   const bool rx = a.RX != nullptr;
+  hipError_t e;
+#define DW_GO(...) e = launch_instance<BM, BN, WM, WN, __VA_ARGS__>(a, grid, s)
   if (a.x_view != VIEW_NONE || a.y_view != VIEW_NONE) {
     // a convolution on a map: forward (patches as X), weight gradient (patches as Y), data gradient (the gradient
     // map seen from the input positions as X, the taps of W in the contraction index)
     if (a.epi == EPI_RELU && rx && a.x_view == VIEW_PATCH && a.y_view == VIEW_NONE)
-      DW_LAUNCH_V(true, true, true, RY_BITS, EPI_RELU, VIEW_PATCH, VIEW_NONE);
+      DW_GO(true, true, true, RY_BITS, EPI_RELU, 0, VIEW_PATCH, VIEW_NONE);
     else if (a.epi == EPI_WGRAD && a.RY && a.x_view == VIEW_NONE && a.y_view == VIEW_PATCH)
-      DW_LAUNCH_V(false, false, true, RY_MEM, EPI_WGRAD, VIEW_NONE, VIEW_PATCH);
+      DW_GO(false, false, true, RY_MEM, EPI_WGRAD, 0, VIEW_NONE, VIEW_PATCH);
     else if (a.epi == EPI_MASK && a.x_view == VIEW_SHIFTED && a.y_view == VIEW_TAPS)
-      DW_LAUNCH_V(true, false, true, RY_BITS, EPI_MASK, VIEW_SHIFTED, VIEW_TAPS);
-
+      DW_GO(true, false, true, RY_BITS, EPI_MASK, 0, VIEW_SHIFTED, VIEW_TAPS);
     else
       return hipErrorInvalidValue;
   } else if (a.r_only && !sliced && a.epi == EPI_RELU) {
     // a later Hutchinson probe of the same minibatch: the plain product is in memory, only the R-products are computed
-    if (rx) DW_LAUNCH_R(true, true, true, RY_BITS, EPI_RELU); else DW_LAUNCH_R(true, true, false, RY_BITS, EPI_RELU);
+    if (rx) DW_GO(true, true, true, RY_BITS, EPI_RELU, 1); else DW_GO(true, true, false, RY_BITS, EPI_RELU, 1);
   } else if (a.r_only && !sliced && a.epi == EPI_MASK) {
-    DW_LAUNCH_R(true, false, true, RY_BITS, EPI_MASK);
+    DW_GO(true, false, true, RY_BITS, EPI_MASK, 1);
   } else if (a.epi == EPI_RELU) {              // forward, hidden layer
-    if (rx) DW_LAUNCH(true, true, true, RY_BITS, EPI_RELU); else DW_LAUNCH(true, true, false, RY_BITS, EPI_RELU);
+    if (rx) DW_GO(true, true, true, RY_BITS, EPI_RELU); else DW_GO(true, true, false, RY_BITS, EPI_RELU);
   } else if (a.epi == EPI_LINEAR) {            // forward, output layer
-    if (rx) DW_LAUNCH(true, true, true, RY_BITS, EPI_LINEAR); else DW_LAUNCH(true, true, false, RY_BITS, EPI_LINEAR);
+    if (rx) DW_GO(true, true, true, RY_BITS, EPI_LINEAR); else DW_GO(true, true, false, RY_BITS, EPI_LINEAR);
   } else if (a.epi == EPI_MASK) {              // data gradient
-    DW_LAUNCH(true, false, true, RY_BITS, EPI_MASK);
+    DW_GO(true, false, true, RY_BITS, EPI_MASK);
   } else if (a.epi == EPI_PLAIN) {             // data gradient stored unmasked (the mask follows a col2im)
-    DW_LAUNCH(true, false, true, RY_BITS, EPI_PLAIN);
+    DW_GO(true, false, true, RY_BITS, EPI_PLAIN);
   } else {                                     // weight gradient
-    if (a.RY) DW_LAUNCH(false, false, true, RY_MEM, EPI_WGRAD); else DW_LAUNCH(false, false, true, RY_NONE, EPI_WGRAD);
+    if (a.RY) DW_GO(false, false, true, RY_MEM, EPI_WGRAD); else DW_GO(false, false, true, RY_NONE, EPI_WGRAD);
   }
-#undef DW_LAUNCH
-#undef DW_LAUNCH_R
-#undef DW_LAUNCH_V
+#undef DW_GO
+  if (e != hipSuccess) return e;
   if (sliced) {
     const int64_t n_out = (int64_t)a.M * a.ldc;
     hipLaunchKernelGGL(sum_slices_kernel, dim3((unsigned)((n_out + 255) / 256), grid.y), dim3(256), 0, s, a);
@@ -419,21 +771,14 @@ static hipError_t launch_shape(const GemmArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// weight gradient that applies the update itself: 128 x 128 tiles, dynamic LDS for the epilogue's per-wave regions
+// Weight gradient that applies the update itself: 64 x 128 tiles, four waves of 32 x 64, so that two blocks share a compute
+// unit (74 KB of LDS, 256 registers) and one's update traffic runs under the other's products.
+constexpr int kFuseBM = 64, kFuseBN = 128;
 template <int FM>
 static hipError_t launch_fused_wgrad_mode(const GemmArgs& a, hipStream_t s) {
-  const int tiles = (a.M / 128) * (a.N / 128);
-  const dim3 grid((unsigned)tiles, (unsigned)active_count(a.active_mask, a.k)), block(NT);
-  constexpr int smem = (NT / 64) * fused_update_lds_floats() * (int)sizeof(float);
-  auto with_ry = dual_gemm_f32<128, 128, 2, 2, false, false, true, RY_MEM, EPI_WGRAD_FUSED, FM>;
-  auto without_ry = dual_gemm_f32<128, 128, 2, 2, false, false, true, RY_NONE, EPI_WGRAD_FUSED, FM>;
-  static LdsLimitOnce lim_with, lim_without;
-  hipError_t e = lim_with.raise(reinterpret_cast<const void*>(with_ry), smem);
-  if (e == hipSuccess) e = lim_without.raise(reinterpret_cast<const void*>(without_ry), smem);
-  if (e != hipSuccess) return e;
-  if (a.RY) hipLaunchKernelGGL(with_ry, grid, block, smem, s, a);
-  else hipLaunchKernelGGL(without_ry, grid, block, smem, s, a);
-  return hipGetLastError();
+  const dim3 grid((unsigned)((a.M / kFuseBM) * (a.N / kFuseBN)), (unsigned)active_count(a.active_mask, a.k));
+  if (a.RY) return launch_instance<kFuseBM, kFuseBN, 2, 2, false, false, true, RY_MEM, EPI_WGRAD_FUSED, FM>(a, grid, s);
+  return launch_instance<kFuseBM, kFuseBN, 2, 2, false, false, true, RY_NONE, EPI_WGRAD_FUSED, FM>(a, grid, s);
 }
 
 // several Hutchinson probes: own instances for the probes before the last and for the last one
@@ -450,16 +795,14 @@ bool gemm_f32_wgrad_fusable(int n_out, int n_in, int k, int avg_block, float hpo
   if ((int64_t)n_out * n_in >= (1ll << 31)) return false;
   return (int64_t)(n_out / 128) * (n_in / 128) * k >= 512;
 }
-int gemm_f32_wgrad_tiles(int n_out, int n_in) { return (n_out / 128) * (n_in / 128); }
+int gemm_f32_wgrad_tiles(int n_out, int n_in) { return (n_out / kFuseBM) * (n_in / kFuseBN); }
 
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
   KernelScope ks(a.epi == EPI_WGRAD ? KC_GEMM_WGRAD : (a.epi == EPI_MASK || a.epi == EPI_PLAIN) ? KC_GEMM_DGRAD : KC_GEMM_FWD, s);
   if (a.epi == EPI_WGRAD && a.fu.on) return launch_fused_wgrad(a, s);
   if (a.N <= 32) return launch_shape<128, 32, 4, 1>(a, s);
   if (a.M <= 32) return launch_shape<32, 128, 1, 4>(a, s);
-  if (a.N <= 64 && (int64_t)((a.M + 127) / 128) * a.k >= 512) return launch_shape<128, 64, 2, 2>(a, s);   // many rows, few columns
-  const int64_t big_tiles = (int64_t)((a.M + 127) / 128) * ((a.N + 127) / 128) * a.k;
-  if (big_tiles >= 512 && a.M > 64 && a.N > 64) return launch_shape<128, 128, 2, 2>(a, s);   // (a 128-wide tile on 64 rows is half empty)
+  if (a.N <= 64 && (int64_t)((a.M + 127) / 128) * a.k >= 512) return launch_shape<128, 64, 4, 1>(a, s);   // many rows, few columns
   return launch_shape<64, 64, 2, 2>(a, s);
 }
 

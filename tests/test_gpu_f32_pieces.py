@@ -1,0 +1,79 @@
+"""The fp32 products in bf16 pieces: infinities and NaN, huge and tiny operands, and one network per edge of the tiles."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dw_oracle as O
+from paper_2409_09242_amd import binding as B
+from paper_2409_09242_amd import workloads as W
+from parity import RTOL_GRAD, RTOL_HV, close_layers, oracle_config
+
+pytestmark = pytest.mark.gpu
+
+
+def _step(dims, batch, k, theta0, x, y):
+    w = W.scaled(W.C2, k=k, dims=dims, batch=batch, input_dist="normal")
+    h = B.Handle(B.config_from_workload(w), theta0.astype(np.float32))
+    loss = torch.zeros(k, device="cuda")
+    h.worker_step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), loss=loss)
+    return w, h, loss
+
+
+def _inputs(dims, batch, k, seed):
+    w = W.scaled(W.C2, k=k, dims=dims, batch=batch, input_dist="normal", seed=seed)
+    x, y = W.minibatch_pool(w, 1)
+    return W.init_theta(dims, seed), x[0], y[0]
+
+
+@pytest.mark.parametrize("dims,batch,k", [
+    ((260, 68, 132, 10), 65, 2),         # one row, four columns past a 64 x 64 tile; contractions 4 past a tile of 32 k
+    ((132, 192, 64, 3), 31, 3),          # minibatch shorter than a tile of 32 k
+    ((1280, 256, 128, 16), 128, 2),      # whole tiles, contraction past ten chains of 128 k
+])
+def test_tile_and_chain_edges_follow_the_oracle(dims, batch, k):
+    print("pieces", dims, batch, k, flush=True)
+    theta0, x, y = _inputs(dims, batch, k, 77)
+    w, h, loss = _step(dims, batch, k, theta0, x, y)
+    tr = O.OracleTrainer(oracle_config(w), theta0.astype(np.float64))
+    tr.worker_step(x, y)
+    for i in range(k):
+        close_layers(h.get_state(B.DW_S_G, i), tr.traces[i].g, dims, RTOL_GRAD, "g[%d]" % i)
+        close_layers(h.get_state(B.DW_S_HZ, i), tr.traces[i].hz, dims, RTOL_HV, "hz[%d]" % i)
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -60, 2.0 ** 40])
+def test_scaled_weights_scale_the_products_exactly(scale):
+    """Powers of two commute with the splitting: scaling the first layer's weights and bias by one and its inputs by none
+    scales its activations bit for bit (no piece over- or underflows at 2^-60 or 2^40)."""
+    dims, batch, k = (260, 96, 68, 10), 64, 1
+    theta0, x, y = _inputs(dims, batch, k, 78)
+    n1 = dims[0] * dims[1] + dims[1]
+    _, h0, _ = _step(dims, batch, k, theta0, x, y)
+    t1 = theta0.copy(); t1[:n1] *= np.float32(scale)
+    _, h1, _ = _step(dims, batch, k, t1, x, y)
+    np.testing.assert_array_equal(h1.get_state(B.DW_S_ACT + 1, 0), h0.get_state(B.DW_S_ACT + 1, 0) * np.float32(scale))
+
+
+@pytest.mark.parametrize("dims,batch", [((256, 96, 68, 10), 64), ((256, 96, 32, 10), 130)])
+def test_infinities_stay_infinite_and_nans_stay_nans(dims, batch):
+    """One input entry is inf: the units of the first layer are +-inf there, by the sign of their weight, and the
+    activation is inf or 0, as any fp32 sum gives it; a NaN input makes the sample's pre-activations NaN, which the
+    ReLU's comparison turns into 0.  Other samples of the block are computed again on another instruction, so both are
+    sums of the same K products in some order: within 2 K 2^-24 sum |x w| of each other."""
+    k = 1
+    theta0, x, y = _inputs(dims, batch, k, 79)
+    _, h0, _ = _step(dims, batch, k, theta0, x, y)
+    a0 = h0.get_state(B.DW_S_ACT + 1, 0)
+    xb = x.copy()
+    xb[0, 5, 17] = np.inf; xb[0, 40, 3] = -np.inf; xb[0, 41, 200] = np.nan; xb[0, 42, 9] = np.finfo(np.float32).max
+    _, h1, _ = _step(dims, batch, k, theta0, xb, y)
+    a1 = h1.get_state(B.DW_S_ACT + 1, 0)
+    W1 = theta0[:dims[0] * dims[1]].reshape(dims[1], dims[0])
+    np.testing.assert_array_equal(a1[5], np.where(W1[:, 17] > 0, np.inf, 0))
+    np.testing.assert_array_equal(a1[40], np.where(W1[:, 3] < 0, np.inf, 0))
+    np.testing.assert_array_equal(a1[41], 0)
+    want = np.maximum(W1[:, 9].astype(np.float64) * np.finfo(np.float32).max, 0)      # the other terms are 1e38 times smaller
+    np.testing.assert_allclose(a1[42], want, rtol=1e-6)
+    rest = [i for i in range(batch) if i not in (5, 40, 41, 42)]
+    bound = 2 * dims[0] * 2.0 ** -24 * (np.abs(x[0][rest]) @ np.abs(W1).T + 1)
+    assert np.all(np.abs(a1[rest] - a0[rest]) <= bound)
