@@ -345,12 +345,16 @@ __global__ __launch_bounds__(kPullThreads) void pull_kernel(PullArgs a, WeightAr
   if (FUSED_W) {
     static_assert(kPullThreads >= DW_MAX_K, "a lane per worker");
     double S = 0.0;                                        // lane i: the squared distance of worker i
-    for (int i = 0; i < wa.k; ++i) {
-      double s = 0.0;
-      for (int b = lane; b < wa.n_blocks; b += 64) s += wa.partials[(int64_t)i * wa.n_blocks + b];
-      for (int b = lane; b < wa.n_blocks_f; b += 64) s += wa.partials_f[(int64_t)i * wa.n_blocks_f + b];
-      s = wave_sum(s);
-      if (lane == i) S = s;
+    if (lane < wa.k) {
+      const double* part = wa.partials + (int64_t)lane * wa.n_blocks;
+      for (int b0 = 0; b0 < wa.n_blocks; b0 += 8) {        // (a multiple of eight: eight loads in flight)
+        double v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = part[b0 + j];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) S += v[j];
+      }
+      for (int b = 0; b < wa.n_blocks_f; ++b) S += wa.partials_f[(int64_t)lane * wa.n_blocks_f + b];
     }
     if (lane < wa.k) {
       // the caller's weights sit in the kernel-argument block behind the first argument; they are read from there by

@@ -382,7 +382,8 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_step_kernel(TinyArgs a) {
     double t = 0.0;
     for (int w = 0; w < kTinyThreads / 64; ++w) t += red[w];
     a.partials[(int64_t)i * a.n_blocks] = t;
-    for (int b = 1; b < a.n_blocks; ++b) a.partials[(int64_t)i * a.n_blocks + b] = 0.0;
+  } else if (tid < a.n_blocks) {                             // (n_blocks is 16 at most)
+    a.partials[(int64_t)i * a.n_blocks + tid] = 0.0;
   }
 }
 
