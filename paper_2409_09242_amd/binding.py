@@ -223,7 +223,10 @@ class Handle:
         if nbytes == 0:
             raise DwError(-2, "dw_workspace_bytes")
         self.device = torch.device(device)
-        self.workspace = torch.empty(nbytes + 256, dtype=torch.uint8, device=self.device)
+        # torch's allocations start at multiples of 256 and more, so the tensor is the workspace and nothing beside it
+        self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+        if self.workspace.data_ptr() % 256:
+            self.workspace = torch.empty(nbytes + 256, dtype=torch.uint8, device=self.device)
         base = self.workspace.data_ptr()
         self._ws_ptr = (base + 255) // 256 * 256
         self._h = C.c_void_p()
