@@ -10,16 +10,8 @@
 // R-companion.  The +-1 operand V is never stored as a matrix: its tile is expanded from the sign bits of
 // z while the W tile is staged.
 //
-// The products run on the bf16 matrix cores in three pieces.  A float is the exact sum of three bf16 numbers
-// (3 x 8 significant bits); of the nine products of two such sums the six that reach 2^-24 are multiplied
-// (x1y1, x1y2, x2y1, x2y2, x1y3, x3y1), three with the +-1 operand, whose one piece is exact.  Six
-// v_mfma_f32_32x32x16_bf16 (32 cycles each) replace eight v_mfma_f32_32x32x2_f32 (64 cycles each), 2.7 times less matrix
-// time; with +-1 5.3 times less.  The products of the first pieces have a chain of accumulation of their own, the others,
-// 2^-8 of them and less, another, and the two are added at the end: in one chain the instruction cuts small products off
-// below the last bit of the running sum, always downwards (measured: -1e-8 to -4e-7 of the result's root mean square, which
-// the sums over thousands of positions that follow add up).  Error of one product against 64 bits (2-norm, K = 64 / 1024 /
-// 9216, normal operands): 5e-8 / 1.8e-7 / 5.9e-7, no bias; v_mfma_f32_32x32x2_f32 1.5e-7 / 5.7e-7 / 1.7e-6.
-// Tiles with infinities or NaN are computed again on the fp32 instruction (below).
+// The products run on the bf16 matrix cores, every float split into three pieces (dw_f32_pieces.h).  Tiles with infinities
+// or NaN are computed again on the fp32 matrix instruction (below).
 //
 // Tiling: waves of 32 rows by 32 or 64 columns; tiles of 32 k are split into their pieces once per block while they are
 // stored to LDS (planes [row][32 k] of bf16, 64-byte rows, 16-byte units XOR-swizzled so that both the
@@ -34,14 +26,10 @@
 #include <type_traits>
 
 #include "dw_internal.h"
+#include "dw_f32_pieces.h"
 #include "dw_fused_update.h"
 
 namespace dw {
-
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
 
 constexpr int BK = 32;                     // k per tile
 constexpr int kRowBytes = 64;              // of a plane
@@ -55,34 +43,6 @@ enum RyMode { RY_NONE = 0, RY_MEM = 1, RY_BITS = 2 };
 __device__ __forceinline__ int unit_at(int row, int oct) {
   const int m = row >> 2;
   return m * 256 + ((((row & 3) * 4 + oct) ^ (m & 15)) << 4);
-}
-
-__device__ __forceinline__ uint32_t to_bf16x2(float a, float b) {        // round to nearest even, a in the low half
-  const floatx2 v = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-// the three pieces of a pair of floats, packed: the first is cut off (never overflows), the others are rounded
-template <bool INF>
-__device__ __forceinline__ void split_pair(float a, float b, uint32_t& p1, uint32_t& p2, uint32_t& p3) {
-  const uint32_t au = __float_as_uint(a), bu = __float_as_uint(b);
-  p1 = __builtin_amdgcn_perm(bu, au, 0x07060302u);
-  float ra = a - __uint_as_float(au & 0xFFFF0000u), rb = b - __uint_as_float(bu & 0xFFFF0000u);
-  if (INF) {                                                 // inf - inf would be a NaN
-    if ((au & 0x7FFFFFFFu) == 0x7F800000u) ra = 0.f;
-    if ((bu & 0x7FFFFFFFu) == 0x7F800000u) rb = 0.f;
-  }
-  p2 = to_bf16x2(ra, rb);
-  ra -= __uint_as_float(p2 << 16); rb -= __uint_as_float(p2 & 0xFFFF0000u);
-  p3 = to_bf16x2(ra, rb);
-}
-template <bool INF, int N>                                   // N pairs
-__device__ __forceinline__ void split_pairs(const float (&x)[2 * N], uint32_t (&p)[3][N]) {
-#pragma unroll
-  for (int i = 0; i < N; ++i) split_pair<INF>(x[2 * i], x[2 * i + 1], p[0][i], p[1][i], p[2][i]);
-}
-// +-1 as a pair of bf16 from two bits (bit set: +1)
-__device__ __forceinline__ uint32_t sign_pair(uint32_t b0, uint32_t b1) {
-  return 0xBF80BF80u ^ ((b0 & 1u) << 15) ^ ((b1 & 1u) << 31);
 }
 
 // Loads the tiles of one operand (NOPS = 1) or of an operand and its R-companion, laid out alike (NOPS = 2), and stores
@@ -342,20 +302,6 @@ constexpr int gemm_f32_lds(int bm, int bn, int wm, int wn, bool has_rx, int rym,
   return tiles > upd ? tiles : upd;
 }
 
-// the products of one k-step of 16 of two numbers in three pieces: those of the first pieces to m, the others to t
-__device__ __forceinline__ void mfma6(const bf16x8 (&x)[3], const bf16x8 (&y)[3], floatx16& m, floatx16& t) {
-  m = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[0], m, 0, 0, 0);
-  t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[2], y[0], t, 0, 0, 0);
-  t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[2], t, 0, 0, 0);
-  t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], y[1], t, 0, 0, 0);
-  t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], y[0], t, 0, 0, 0);
-  t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[1], t, 0, 0, 0);
-}
-__device__ __forceinline__ void mfma3(const bf16x8 (&x)[3], const bf16x8& v, floatx16& m, floatx16& t) {
-  m = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], v, m, 0, 0, 0);
-  t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[2], v, t, 0, 0, 0);
-  t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], v, t, 0, 0, 0);
-}
 // the same on the fp32 matrix instruction, from the numbers the pieces add up to
 __device__ __forceinline__ float joined(const bf16x8 (&x)[3], int j) { return (float)x[0][j] + ((float)x[1][j] + (float)x[2][j]); }
 __device__ __forceinline__ void mfma_whole(const bf16x8 (&x)[3], const bf16x8 (&y)[3], floatx16& t) {
@@ -576,10 +522,11 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
         }
         if (sliced) {
           float* pb = a.part_b + (((int64_t)blockIdx.z * a.k + worker) * 2) * a.M;
-          pb[m] = gb; pb[a.M + m] = hzb;
+          pb[m] = gb;
+          if (HAS_RX) pb[a.M + m] = hzb;
         } else {
           a.gb[(int64_t)worker * a.c_wstride + m] = gb;
-          a.hzb[(int64_t)worker * a.c_wstride + m] = hzb;
+          if (HAS_RX) a.hzb[(int64_t)worker * a.c_wstride + m] = hzb;
         }
       }
       __syncthreads();
@@ -638,7 +585,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
     if ((EPI == EPI_RELU || EPI == EPI_LINEAR) && n_ok) {
       bias = a.bias[(int64_t)worker * a.bias_wstride + n];
       const int64_t bi = a.zb_off + n;
-      cz = ((zb[bi >> 5] >> (bi & 31)) & 1u) ? 1.f : -1.f;
+      if (HAS_R) cz = ((zb[bi >> 5] >> (bi & 31)) & 1u) ? 1.f : -1.f;
     }
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
@@ -649,25 +596,26 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
         float c = acc[i][j][r], rc = racc[i][j][r];
         const int64_t o = (int64_t)m * a.ldc + n;
         if (sliced) {                                 // raw partial products: the epilogue follows the sum of the slices
-          C[o] = c; RC[o] = rc;
+          C[o] = c;
+          if (HAS_R) RC[o] = rc;
         } else if (EPI == EPI_RELU && FM == 1) {      // a later probe: the activation is in memory, only its R-companion is new
           RC[o] = C[o] > 0.f ? rc + cz : 0.f;
         } else if (EPI == EPI_RELU) {
           c += bias; rc += cz;
           const bool on = c > 0.f;
           C[o] = on ? c : 0.f;
-          RC[o] = on ? rc : 0.f;
+          if (HAS_R) RC[o] = on ? rc : 0.f;
         } else if (EPI == EPI_LINEAR) {
           C[o] = c + bias;
-          RC[o] = rc + cz;
+          if (HAS_R) RC[o] = rc + cz;
         } else if (EPI == EPI_MASK) {
           const float* msk = reinterpret_cast<const float*>(a.mask_src) + (int64_t)worker * a.mask_wstride;
           const bool on = msk[(int64_t)m * a.ld_mask + n] > 0.f;
           if (FM != 1) C[o] = on ? c : 0.f;           // (a later probe: the plain data gradient is in memory already)
-          RC[o] = on ? rc : 0.f;
+          if (HAS_R) RC[o] = on ? rc : 0.f;
         } else {
           C[o] = c;
-          RC[o] = rc;
+          if (HAS_R) RC[o] = rc;
         }
       }
     }
@@ -685,29 +633,31 @@ __global__ __launch_bounds__(256) void sum_slices_kernel(GemmArgs a) {
     float c = 0.f, rc = 0.f;
     for (int sl = 0; sl < a.ksplit; ++sl) {
       const float* p = a.part + (((int64_t)sl * a.k + worker) * 2) * a.part_stride;
-      c += p[e]; rc += p[a.part_stride + e];
+      c += p[e];
+      if (!a.plain) rc += p[a.part_stride + e];
     }
     if (a.epi == EPI_RELU || a.epi == EPI_LINEAR) {
       const uint32_t* zb = a.zbits + (int64_t)worker * a.z_stride;
       const int64_t bi = a.zb_off + n;
       c += a.bias[(int64_t)worker * a.bias_wstride + n];
-      rc += ((zb[bi >> 5] >> (bi & 31)) & 1u) ? 1.f : -1.f;
+      if (!a.plain) rc += ((zb[bi >> 5] >> (bi & 31)) & 1u) ? 1.f : -1.f;
       if (a.epi == EPI_RELU && !(c > 0.f)) { c = 0.f; rc = 0.f; }
     } else if (a.epi == EPI_MASK) {
       const float* msk = reinterpret_cast<const float*>(a.mask_src) + (int64_t)worker * a.mask_wstride;
       if (!(msk[(e / a.ldc) * a.ld_mask + n] > 0.f)) { c = 0.f; rc = 0.f; }
     }
     reinterpret_cast<float*>(a.C)[(int64_t)worker * a.c_wstride + e] = c;
-    reinterpret_cast<float*>(a.RC)[(int64_t)worker * a.c_wstride + e] = rc;
+    if (!a.plain) reinterpret_cast<float*>(a.RC)[(int64_t)worker * a.c_wstride + e] = rc;
   }
   if (a.epi == EPI_WGRAD && e < a.M) {
     float b = 0.f, rb = 0.f;
     for (int sl = 0; sl < a.ksplit; ++sl) {
       const float* p = a.part_b + (((int64_t)sl * a.k + worker) * 2) * a.M;
-      b += p[e]; rb += p[a.M + e];
+      b += p[e];
+      if (!a.plain) rb += p[a.M + e];
     }
     a.gb[(int64_t)worker * a.c_wstride + e] = b;
-    a.hzb[(int64_t)worker * a.c_wstride + e] = rb;
+    if (!a.plain) a.hzb[(int64_t)worker * a.c_wstride + e] = rb;
   }
 }
 
@@ -746,6 +696,13 @@ static hipError_t launch_shape(const GemmArgs& a, hipStream_t s) {
       DW_GO(true, false, true, RY_BITS, EPI_MASK, 0, VIEW_SHIFTED, VIEW_TAPS);
     else
       return hipErrorInvalidValue;
+  } else if (a.plain) {
+    // a first-order step: the plain products alone
+    if (a.epi == EPI_RELU) DW_GO(true, true, false, RY_NONE, EPI_RELU);
+    else if (a.epi == EPI_LINEAR) DW_GO(true, true, false, RY_NONE, EPI_LINEAR);
+    else if (a.epi == EPI_MASK) DW_GO(true, false, false, RY_NONE, EPI_MASK);
+    else if (a.epi == EPI_WGRAD) DW_GO(false, false, false, RY_NONE, EPI_WGRAD);
+    else return hipErrorInvalidValue;
   } else if (a.r_only && !sliced && a.epi == EPI_RELU) {
     // a later Hutchinson probe of the same minibatch: the plain product is in memory, only the R-products are computed
     if (rx) DW_GO(true, true, true, RY_BITS, EPI_RELU, 1); else DW_GO(true, true, false, RY_BITS, EPI_RELU, 1);

@@ -192,6 +192,7 @@ struct GemmArgs {
   int ksplit; float* part; int64_t part_stride; float* part_b;
   int x_view, y_view;                 // fp32 kernels: OperandView of X/RX and of Y/RY (and of the sign bits of V)
   ConvView cv;
+  int plain;                          // fp32: 1: C alone is wanted (a first-order step); RX, RY and the sign bits are not read
   int r_only;                         // 1: C is in memory already (an earlier probe of this minibatch); kernels may compute RC alone
   // EPI_WGRAD with fu.probe_mode == 3 (two Hutchinson probes in one kernel): the earlier probe's R-companions of X
   // and Y (laid out like RX and RY; RYp == nullptr with RY) and its sign bits (strides and offsets as zbits)
@@ -231,6 +232,8 @@ struct LdsLimitOnce {
 
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s);
+bool gemm_f32_short_ok(const GemmArgs& a);                       // small-model kernel usable and meant for this product?
+hipError_t launch_gemm_f32_short(const GemmArgs& a, hipStream_t s);
 // can the bf16 weight-gradient kernel of a layer W[n_out][n_in] (bit/parameter offset woff) apply the update itself,
 // and how many partial-sum slots (tiles) does it then write per worker when a step has n_samples Hutchinson probes?
 bool gemm_bf16_wgrad_fusable(int n_out, int n_in, int k, int avg_block, float hpow, int64_t woff);

@@ -87,6 +87,9 @@ int run_network(const dw_config& cfg, char* ws, const Layout& lay, const void* d
   auto gemm_on = [&](const GemmArgs& a, hipStream_t st) { return b16 ? launch_gemm_bf16(a, st) : launch_gemm_f32(a, st); };
   auto gemm = [&](const GemmArgs& a) { return gemm_on(a, s); };
   hipError_t e;
+  // a baseline's first-order step of an fp32 MLP needs the plain products alone (784-512-512-10, four workers: 127 -> 100 us;
+  // bf16 and convolutional models still run the R-companions along)
+  const int plain = !b16 && lay.n_conv == 0 && cfg.optimizer != DW_OPT_ADAHESSIAN ? 1 : 0;
 
   // layers whose data gradient reads the sign bits of V_l column by column get a transposed copy of those bits
   // (when the caller's z allows 16-byte accesses; otherwise those layers take the general kernel)
@@ -125,12 +128,17 @@ int run_network(const dw_config& cfg, char* ws, const Layout& lay, const void* d
       a.epi = EPI_LINEAR;
     }
     a.k = k; a.active_mask = active;
+    if (plain) { a.plain = 1; a.RX = nullptr; a.ry_bits = 0; }
     if (!b16 && l == L && out_head_f32_ok(a)) {
       // fp32: the output layer's product and the softmax head in one kernel (the logits buffer serves as its
       // scratch for the per-block losses)
       if ((e = launch_out_head_f32(a, hd, reinterpret_cast<float*>(ws + lay.sL), s)) != hipSuccess) return DW_ERR_HIP;
       head_done = true;
       break;
+    }
+    if (!b16 && gemm_f32_short_ok(a)) {
+      if ((e = launch_gemm_f32_short(a, s)) != hipSuccess) return DW_ERR_HIP;
+      continue;
     }
     if (!b16 && lay.fwdSplit[l - 1] > 1) {             // long contraction, few output tiles
       a.ksplit = lay.fwdSplit[l - 1]; a.part = reinterpret_cast<float*>(ws + lay.cPart);
@@ -164,6 +172,7 @@ int run_network(const dw_config& cfg, char* ws, const Layout& lay, const void* d
     a.C = g + lay.woff[l - 1]; a.RC = hz + lay.woff[l - 1]; a.ldc = cfg.dims[l - 1]; a.c_wstride = lay.Pp;
     a.gb = g + lay.boff[l - 1]; a.hzb = hz + lay.boff[l - 1];
     a.epi = EPI_WGRAD; a.k = k; a.active_mask = active;
+    if (plain) { a.plain = 1; a.RX = nullptr; a.RY = nullptr; }
     if (fuse != nullptr && lay.fuse_base[l - 1] >= 0 && keep) {
       // left to the later probe's launch; the bias part of this probe's Hz is the column sum of Rd_l
       KernelScope ks(KC_GEMM_WGRAD, st);
@@ -219,11 +228,16 @@ int run_network(const dw_config& cfg, char* ws, const Layout& lay, const void* d
     a.c_wstride = act_stride(l - 1);
     a.mask_src = act(l - 1); a.ld_mask = cfg.dims[l - 1]; a.mask_wstride = act_stride(l - 1);
     a.epi = EPI_MASK; a.k = k; a.active_mask = active; a.r_only = (r_only && l > 1) ? 1 : 0;
-    if (!b16 && l > 1 && lay.dgSplit[l - 1] > 1) {      // long contraction, few output tiles
-      a.ksplit = lay.dgSplit[l - 1]; a.part = reinterpret_cast<float*>(ws + lay.cPart);
-      a.part_stride = (int64_t)B * a.ldc; a.part_b = nullptr;
+    if (plain) { a.plain = 1; a.RX = nullptr; a.ry_bits = 0; }
+    if (!b16 && gemm_f32_short_ok(a)) {
+      if ((e = launch_gemm_f32_short(a, s)) != hipSuccess) return DW_ERR_HIP;
+    } else {
+      if (!b16 && l > 1 && lay.dgSplit[l - 1] > 1) {      // long contraction, few output tiles
+        a.ksplit = lay.dgSplit[l - 1]; a.part = reinterpret_cast<float*>(ws + lay.cPart);
+        a.part_stride = (int64_t)B * a.ldc; a.part_b = nullptr;
+      }
+      if ((e = gemm(a)) != hipSuccess) return DW_ERR_HIP;
     }
-    if ((e = gemm(a)) != hipSuccess) return DW_ERR_HIP;
     if (overlap && l - 1 >= 2 && fork_wgrad(l - 1) != hipSuccess) return DW_ERR_HIP;
   }
   // weight gradients (with the side stream: only the first layer's is left; then the caller's stream waits for the others)

@@ -26,35 +26,72 @@ __global__ __launch_bounds__(NT) void out_head_f32_kernel(GemmArgs a, HeadArgs h
   const int row0 = blockIdx.x * ROWS;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, kg = lane >> 4;               // operand row (A) or column (W), and which 4 of the 16 k
-  const int kspan = a.K / NW;                              // this wave's share of the contraction
-  const int kbeg = wave * kspan;
+  const int kspan = (a.K + NW * KSTEP - 1) / (NW * KSTEP) * KSTEP;    // this wave's share of the contraction
+  const int kbeg = wave * kspan, kend = kbeg + kspan < a.K ? kbeg + kspan : a.K;
   const int arow = row0 + r16 < a.M ? row0 + r16 : a.M - 1;   // rows past the end repeat the last one (never stored)
 
-  const float* X = reinterpret_cast<const float*>(a.X) + (int64_t)worker * a.x_wstride + (int64_t)arow * a.ldx + kg * 4;
+  const float* X = reinterpret_cast<const float*>(a.X) + (int64_t)worker * a.x_wstride + (int64_t)arow * a.ldx;
   const bool has_rx = a.RX != nullptr;
-  const float* RX = has_rx ? reinterpret_cast<const float*>(a.RX) + (int64_t)worker * a.x_wstride + (int64_t)arow * a.ldx + kg * 4
+  const float* RX = has_rx ? reinterpret_cast<const float*>(a.RX) + (int64_t)worker * a.x_wstride + (int64_t)arow * a.ldx
                            : X;
   const bool col_ok = r16 < a.N;
   const int wrow = col_ok ? r16 : 0;                       // lanes of padding columns read row 0 and multiply by zero
-  const float* W = reinterpret_cast<const float*>(a.Y) + (int64_t)worker * a.y_wstride + (int64_t)wrow * a.ldy + kg * 4;
+  const float* W = reinterpret_cast<const float*>(a.Y) + (int64_t)worker * a.y_wstride + (int64_t)wrow * a.ldy;
   const uint32_t* zb = a.zbits + (int64_t)worker * a.z_stride;
-  const int64_t zbit0 = a.z_off + (int64_t)wrow * a.ldy + kg * 4;    // multiple of 4: the 4 bits sit in one word
+  const int64_t zbit0 = a.z_off + (int64_t)wrow * a.ldy;    // multiple of 4: the 4 bits sit in one word
 
   f32o_x4 acc = {0.f, 0.f, 0.f, 0.f}, racc = {0.f, 0.f, 0.f, 0.f};
 
-  for (int k0 = kbeg; k0 < kbeg + kspan; k0 += KSTEP) {
-    const float4 x4 = *reinterpret_cast<const float4*>(X + k0);
-    const float4 rx4 = has_rx ? *reinterpret_cast<const float4*>(RX + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
-    const float4 w4 = col_ok ? *reinterpret_cast<const float4*>(W + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
-    const int64_t bi = zbit0 + k0;
-    const uint32_t bits = col_ok ? (zb[bi >> 5] >> (bi & 31)) & 0xFu : 0u;
-    const float x[4] = {x4.x, x4.y, x4.z, x4.w}, rx[4] = {rx4.x, rx4.y, rx4.z, rx4.w}, w[4] = {w4.x, w4.y, w4.z, w4.w};
+  const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (a.K % (NW * KSTEP) == 0) {                           // (512 wide: 12 us, the form below 15)
+    for (int k0 = kbeg; k0 < kbeg + kspan; k0 += KSTEP) {
+      const float4 x4 = *reinterpret_cast<const float4*>(X + k0 + kg * 4);
+      const float4 rx4 = has_rx ? *reinterpret_cast<const float4*>(RX + k0 + kg * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+      const float4 w4 = col_ok ? *reinterpret_cast<const float4*>(W + k0 + kg * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+      const int64_t bi = zbit0 + k0 + kg * 4;
+      const uint32_t bits = col_ok ? (zb[bi >> 5] >> (bi & 31)) & 0xFu : 0u;
+      const float x[4] = {x4.x, x4.y, x4.z, x4.w}, rx[4] = {rx4.x, rx4.y, rx4.z, rx4.w}, w[4] = {w4.x, w4.y, w4.z, w4.w};
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float v = col_ok ? (((bits >> j) & 1u) ? 1.f : -1.f) : 0.f;
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j], w[j], acc, 0, 0, 0);
-      racc = __builtin_amdgcn_mfma_f32_16x16x4f32(rx[j], w[j], racc, 0, 0, 0);
-      racc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j], v, racc, 0, 0, 0);
+      for (int j = 0; j < 4; ++j) {
+        const float v = col_ok ? (((bits >> j) & 1u) ? 1.f : -1.f) : 0.f;
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j], w[j], acc, 0, 0, 0);
+        racc = __builtin_amdgcn_mfma_f32_16x16x4f32(rx[j], w[j], racc, 0, 0, 0);
+        racc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j], v, racc, 0, 0, 0);
+      }
+    }
+  } else {
+    // four steps' loads go out together
+    constexpr int BATCH = 4;
+    for (int kb = kbeg; kb < kend; kb += BATCH * KSTEP) {
+      float4 x4[BATCH], rx4[BATCH], w4[BATCH];
+      uint32_t bits[BATCH];
+      bool live[BATCH];
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u) {
+        // past the end (the last steps may be short or missing; K is a multiple of 4): the last four k again, times zero
+        const int k = kb + u * KSTEP + kg * 4, kc = k < kend ? k : a.K - 4;
+        x4[u] = *reinterpret_cast<const float4*>(X + kc);
+        rx4[u] = has_rx ? *reinterpret_cast<const float4*>(RX + kc) : zero4;
+        w4[u] = *reinterpret_cast<const float4*>(W + kc);
+        const int64_t bi = zbit0 + kc;
+        bits[u] = zb[bi >> 5] >> (bi & 31);
+        live[u] = k < kend;
+      }
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u) {
+        const float xs[4] = {x4[u].x, x4[u].y, x4[u].z, x4[u].w}, rxs[4] = {rx4[u].x, rx4[u].y, rx4[u].z, rx4[u].w};
+        const float ws[4] = {w4[u].x, w4[u].y, w4[u].z, w4[u].w};
+        float x[4], rx[4], w[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { x[j] = live[u] ? xs[j] : 0.f; rx[j] = live[u] ? rxs[j] : 0.f; w[j] = live[u] && col_ok ? ws[j] : 0.f; }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float v = col_ok ? (((bits[u] >> j) & 1u) ? 1.f : -1.f) : 0.f;
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j], w[j], acc, 0, 0, 0);
+          racc = __builtin_amdgcn_mfma_f32_16x16x4f32(rx[j], w[j], racc, 0, 0, 0);
+          racc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j], v, racc, 0, 0, 0);
+        }
+      }
     }
   }
 
@@ -115,12 +152,12 @@ __global__ __launch_bounds__(64) void loss_sum_kernel(const float* loss_part, in
 
 }  // namespace f32o
 
-// the fp32 output layer's forward product (linear epilogue, at most 16 columns) with a contraction that four waves
-// can share in steps of 16, operands that 16-byte loads can address and sign bits that come four to a word
+// the fp32 output layer's forward product (linear epilogue, at most 16 columns) with operands that 16-byte loads can
+// address and sign bits that come four to a word
 bool out_head_f32_ok(const GemmArgs& a) {
-  if (a.epi != EPI_LINEAR || !a.ry_bits || !a.x_kcontig || !a.y_kcontig || a.ksplit > 1) return false;
+  if (a.epi != EPI_LINEAR || !(a.ry_bits || a.plain) || !a.x_kcontig || !a.y_kcontig || a.ksplit > 1) return false;
   if (a.N < 1 || a.N > f32o::ROWS || a.M < 1) return false;
-  if (a.K < f32o::NW * f32o::KSTEP || a.K % (f32o::NW * f32o::KSTEP) != 0) return false;
+  if (a.K < 1 || a.K % 4 != 0) return false;
   if (a.ldx % 4 != 0 || a.ldy % 4 != 0 || a.x_wstride % 4 != 0 || a.y_wstride % 4 != 0 || a.z_off % 4 != 0) return false;
   if ((reinterpret_cast<uintptr_t>(a.X) & 15u) || (reinterpret_cast<uintptr_t>(a.Y) & 15u) ||
       (a.RX && (reinterpret_cast<uintptr_t>(a.RX) & 15u)))

@@ -77,3 +77,25 @@ def test_infinities_stay_infinite_and_nans_stay_nans(dims, batch):
     rest = [i for i in range(batch) if i not in (5, 40, 41, 42)]
     bound = 2 * dims[0] * 2.0 ** -24 * (np.abs(x[0][rest]) @ np.abs(W1).T + 1)
     assert np.all(np.abs(a1[rest] - a0[rest]) <= bound)
+
+
+@pytest.mark.parametrize("opt", [B.DW_OPT_SGD, B.DW_OPT_MOMENTUM])
+@pytest.mark.parametrize("dims,batch,k", [
+    ((260, 68, 132, 10), 65, 2),         # every forward product in the small-model kernel, contraction past a step of 32 k
+    ((64, 36, 4), 5, 1),                 # contractions of at most two steps
+    ((132, 1028, 260, 7), 256, 4),       # tiles of 64 x 64, whole and ragged; data gradient in slices
+])
+def test_first_order_steps_compute_the_plain_products_alone(opt, dims, batch, k):
+    print("first order", opt, dims, batch, k, flush=True)
+    theta0, x, y = _inputs(dims, batch, k, 80)
+    w = W.scaled(W.C2, k=k, dims=dims, batch=batch, input_dist="normal", optimizer=opt, seed=80)
+    h = B.Handle(B.config_from_workload(w), theta0)
+    tr = O.OracleTrainer(oracle_config(w), theta0.astype(np.float64))
+    loss = torch.zeros(k, device="cuda")
+    h.worker_step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), loss=loss)
+    np.testing.assert_allclose(loss.cpu().numpy(), tr.worker_step(x, y), rtol=1e-5)
+    for i in range(k):
+        close_layers(h.get_state(B.DW_S_G, i), tr.traces[i].g, dims, RTOL_GRAD, "g[%d]" % i)
+        # the step is lr * g with g held to 1e-4; read back as a difference of two stored parameters it carries an ulp of
+        # theta, up to 2^-24 * 0.5 = 3e-8, against lr * rms(g) of 2e-5 and more in every layer
+        close_layers(h.get_state(B.DW_S_THETA, i) - theta0, tr.theta[i] - theta0, dims, 2e-3, "update[%d]" % i)
