@@ -1,12 +1,15 @@
-// bf16 dual GEMM of the output layer's forward pass: few columns (the classes), long contraction.
+// bf16 output layer's forward product (few columns, the classes, and a long contraction) and the softmax head.
 //
 // S = A W^T + b and RS = RA W^T + A V^T + c (Section IV-B) with W [C][K], C <= 16: the product is a stream over the
 // activations A and RA ([B][K] bf16 each); W and the sign bits of V are tiny and stay in cache.  A tile kernel gives
 // this shape only B/256 blocks per worker, each walking the whole K with one tile in flight.  Here a block owns 16
 // rows and its four waves a quarter of K each, every lane keeping eight 16-byte loads of A and of RA in flight;
 // the 16 x 16 x 32 MFMA takes the lanes' loads as they come (8 consecutive k per lane, no LDS), and the four
-// partial tiles are added in wave order through LDS, so the result does not depend on timing.
-#include "dw_internal.h"
+// partial tiles are added in wave order through LDS, so the result does not depend on timing; the block's 16 samples then go
+// through the softmax head at once (dw_out_head.h) and the logits never go to memory.  Sixteen workers, 512 samples: 2048
+// wide 20 us + 27 us for the head in a launch of its own, one block per worker, -> 23 us; six workers, 200 samples, 776
+// wide 24 us (tile kernel) + 13 -> 9.7.
+#include "dw_out_head.h"
 
 namespace dw {
 
@@ -28,32 +31,36 @@ __device__ __forceinline__ bf16x8 pm1_x8(uint32_t b) {
   return __builtin_bit_cast(bf16x8, o);
 }
 
-// grid: (M / 16, active workers); requirements in gemm_bf16_out_ok
-__global__ __launch_bounds__(NT) void out_layer_fwd_bf16(GemmArgs a) {
+// grid: (ceil(M / 16), active workers); requirements in out_head_bf16_ok.  WHOLE: K is a multiple of what the four waves take
+// in a step of their loops
+template <bool WHOLE>
+__global__ __launch_bounds__(NT) void out_head_bf16_kernel(GemmArgs a, HeadArgs h, float* loss_part) {
   const int worker = nth_active_worker(a.active_mask, blockIdx.y);
   const int row0 = blockIdx.x * ROWS;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, kg = lane >> 4;              // operand row (A) or column (W), and which 8 of the 32 k
-  const int kspan = a.K / NW;                             // this wave's share of the contraction
-  const int kbeg = wave * kspan;
+  const int kspan = (a.K + NW * KSTEP - 1) / (NW * KSTEP) * KSTEP;   // this wave's share of the contraction
+  const int kbeg = wave * kspan, kend = kbeg + kspan < a.K ? kbeg + kspan : a.K;
+  const int arow = row0 + r16 < a.M ? row0 + r16 : a.M - 1;          // rows past the end repeat the last one (never stored)
 
   const uint16_t* X = reinterpret_cast<const uint16_t*>(a.X) + (int64_t)worker * a.x_wstride +
-                      (int64_t)(row0 + r16) * a.ldx + kg * 8;
+                      (int64_t)arow * a.ldx;
   const uint16_t* RX = reinterpret_cast<const uint16_t*>(a.RX) + (int64_t)worker * a.x_wstride +
-                       (int64_t)(row0 + r16) * a.ldx + kg * 8;
+                       (int64_t)arow * a.ldx;
   const bool col_ok = r16 < a.N;
   const int wrow = col_ok ? r16 : 0;                      // lanes of padding columns read row 0 and multiply by zero
-  const uint16_t* W = reinterpret_cast<const uint16_t*>(a.Y) + (int64_t)worker * a.y_wstride + (int64_t)wrow * a.ldy + kg * 8;
+  const uint16_t* W = reinterpret_cast<const uint16_t*>(a.Y) + (int64_t)worker * a.y_wstride + (int64_t)wrow * a.ldy;
   const uint32_t* zb = a.zbits + (int64_t)worker * a.z_stride;
-  const int64_t zbit0 = a.z_off + (int64_t)wrow * a.ldy + kg * 8;   // multiple of 8: the 8 bits sit in one byte
+  const int64_t zbit0 = a.z_off + (int64_t)wrow * a.ldy;            // multiple of 8: the 8 bits sit in one byte
 
   floatx4 acc = {0.f, 0.f, 0.f, 0.f}, racc = {0.f, 0.f, 0.f, 0.f};
-  for (int k0 = kbeg; k0 < kbeg + kspan; k0 += KSTEP * UNROLL) {
+  for (int k0 = kbeg; k0 < kend; k0 += KSTEP * UNROLL) {
     u32x4 xa[UNROLL], rxa[UNROLL], wb[UNROLL];
     uint32_t zw[UNROLL];
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
-      const int k = k0 + u * KSTEP;
+      // past the end (K is a multiple of 8): the last eight k again, times zero
+      const int kq = k0 + u * KSTEP + kg * 8, k = WHOLE || kq < kend ? kq : a.K - 8;
       xa[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(X + k));
       rxa[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(RX + k));
       wb[u] = *reinterpret_cast<const u32x4*>(W + k);
@@ -62,8 +69,9 @@ __global__ __launch_bounds__(NT) void out_layer_fwd_bf16(GemmArgs a) {
     }
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
-      const bf16x8 x = __builtin_bit_cast(bf16x8, xa[u]), rx = __builtin_bit_cast(bf16x8, rxa[u]);
       const u32x4 zero = {0u, 0u, 0u, 0u};
+      if (!WHOLE && k0 + u * KSTEP + kg * 8 >= kend) { xa[u] = zero; rxa[u] = zero; wb[u] = zero; }
+      const bf16x8 x = __builtin_bit_cast(bf16x8, xa[u]), rx = __builtin_bit_cast(bf16x8, rxa[u]);
       const bf16x8 w = __builtin_bit_cast(bf16x8, col_ok ? wb[u] : zero);
       const bf16x8 v = col_ok ? pm1_x8(zw[u]) : __builtin_bit_cast(bf16x8, zero);
       acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, w, acc, 0, 0, 0);
@@ -80,27 +88,15 @@ __global__ __launch_bounds__(NT) void out_layer_fwd_bf16(GemmArgs a) {
     part[wave][1][kg * 4 + r][r16] = racc[r];
   }
   __syncthreads();
-  const int m = tid >> 4, n = tid & 15;
-  if (n < a.N && row0 + m < a.M) {
-    float s = 0.f, rs = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) { s += part[w][0][m][n]; rs += part[w][1][m][n]; }
-    const int64_t bi = a.zb_off + n;
-    const float cz = ((zb[bi >> 5] >> (bi & 31)) & 1u) ? 1.f : -1.f;
-    const int64_t o = (int64_t)worker * a.c_wstride + (int64_t)(row0 + m) * a.ldc + n;
-    reinterpret_cast<float*>(a.C)[o] = s + a.bias[(int64_t)worker * a.bias_wstride + n];
-    reinterpret_cast<float*>(a.RC)[o] = rs + cz;
-  }
+  out_head_rows<NW>(part, a, h, loss_part, worker, row0, zb);
 }
 
 }  // namespace b16o
 
-// the output layer's forward product (linear epilogue, at most 16 columns) with a contraction long enough to
-// split over four waves in steps of 256, whole 16-row tiles, and operands that 16-byte loads can address
-bool gemm_bf16_out_ok(const GemmArgs& a) {
+// the output layer's forward product (linear epilogue, at most 16 columns) with operands that 16-byte loads can address
+bool out_head_bf16_ok(const GemmArgs& a) {
   if (a.epi != EPI_LINEAR || !a.ry_bits || !a.RX || !a.x_kcontig || !a.y_kcontig) return false;
-  if (a.N < 1 || a.N > b16o::ROWS || a.M % b16o::ROWS != 0) return false;
-  if (a.K % (b16o::NW * b16o::KSTEP * b16o::UNROLL) != 0) return false;
+  if (a.N < 1 || a.N > b16o::ROWS || a.M < 1 || a.K < 8 || a.K % 8 != 0) return false;
   if (a.ldx % 8 != 0 || a.ldy % 8 != 0 || a.x_wstride % 8 != 0 || a.y_wstride % 8 != 0 || a.z_off % 8 != 0) return false;
   if ((reinterpret_cast<uintptr_t>(a.X) & 15u) || (reinterpret_cast<uintptr_t>(a.RX) & 15u) ||
       (reinterpret_cast<uintptr_t>(a.Y) & 15u))
@@ -108,10 +104,17 @@ bool gemm_bf16_out_ok(const GemmArgs& a) {
   return true;
 }
 
-hipError_t launch_gemm_bf16_out(const GemmArgs& a, hipStream_t s) {
-  const dim3 grid((unsigned)(a.M / b16o::ROWS), (unsigned)active_count(a.active_mask, a.k));
-  hipLaunchKernelGGL(b16o::out_layer_fwd_bf16, grid, dim3(b16o::NT), 0, s, a);
-  return hipGetLastError();
+// loss_part: at least k * ceil(M / 16) floats; h.loss may be nullptr (then the slots are not added up)
+hipError_t launch_out_head_bf16(const GemmArgs& a, const HeadArgs& h, float* loss_part, hipStream_t s) {
+  KernelScope ks(KC_HEAD, s);
+  const int n_slots = (a.M + b16o::ROWS - 1) / b16o::ROWS;
+  const dim3 grid((unsigned)n_slots, (unsigned)active_count(a.active_mask, a.k));
+  if (a.K % (b16o::NW * b16o::KSTEP * b16o::UNROLL) == 0)
+    hipLaunchKernelGGL(b16o::out_head_bf16_kernel<true>, grid, dim3(b16o::NT), 0, s, a, h, loss_part);
+  else
+    hipLaunchKernelGGL(b16o::out_head_bf16_kernel<false>, grid, dim3(b16o::NT), 0, s, a, h, loss_part);
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : launch_loss_sum(loss_part, n_slots, h, s);
 }
 
 }  // namespace dw

@@ -245,8 +245,6 @@ int gemm_f32_wgrad_tiles(int n_out, int n_in);
 bool gemm_bf16_dgrad_dma_shape_ok(int batch, int n_out, int n_in, int k, int64_t woff);
 bool gemm_bf16_dma_ok(const GemmArgs& a);                        // large-tile forward path usable for this product?
 hipError_t launch_gemm_bf16_dma(const GemmArgs& a, hipStream_t s);
-bool gemm_bf16_out_ok(const GemmArgs& a);                        // output-layer forward kernel usable for this product?
-hipError_t launch_gemm_bf16_out(const GemmArgs& a, hipStream_t s);
 
 struct HeadArgs {                     // softmax cross-entropy on the output layer and its R-derivative
   const float* s; const float* Rs;    // [k][B][ld] logits and their directional derivative
@@ -262,6 +260,9 @@ hipError_t launch_head(const HeadArgs& a, hipStream_t s);
 // (its C and RC are not written), loss_part: k * ceil(M / 16) floats of scratch
 bool out_head_f32_ok(const GemmArgs& a);
 hipError_t launch_out_head_f32(const GemmArgs& a, const HeadArgs& h, float* loss_part, hipStream_t s);
+// the same in bf16 (dw_gemm_bf16_out.hip)
+bool out_head_bf16_ok(const GemmArgs& a);
+hipError_t launch_out_head_bf16(const GemmArgs& a, const HeadArgs& h, float* loss_part, hipStream_t s);
 
 struct Layout {            // byte offsets into the workspace, all multiples of 256
   int64_t P = 0, Pp = 0, z_stride = 0, n_upd_blocks = 0;

@@ -12,6 +12,7 @@
 #include "dw_internal.h"
 #include "dw_device_util.h"
 #include "dw_head_math.h"
+#include "dw_out_head.h"
 
 namespace dw {
 
@@ -59,6 +60,24 @@ __global__ __launch_bounds__(256) void head_kernel(HeadArgs a) {
 hipError_t launch_head(const HeadArgs& a, hipStream_t s) {
   KernelScope ks(KC_HEAD, s);
   hipLaunchKernelGGL(head_kernel, dim3(a.k), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+// a wave per worker: every lane adds the slots 64 apart, then the lanes in a fixed tree
+__global__ __launch_bounds__(64) void loss_sum_kernel(const float* loss_part, int n_slots, float* loss, int B,
+                                                      uint64_t active_mask) {
+  const int i = blockIdx.x;
+  if (!((active_mask >> i) & 1ull)) return;
+  float t = 0.f;
+  for (int b = threadIdx.x; b < n_slots; b += 64) t += loss_part[(int64_t)i * n_slots + b];
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off);
+  if (threadIdx.x == 0) loss[i] = t / (float)B;
+}
+
+hipError_t launch_loss_sum(const float* loss_part, int n_slots, const HeadArgs& h, hipStream_t s) {
+  if (!h.loss) return hipSuccess;
+  hipLaunchKernelGGL(loss_sum_kernel, dim3((unsigned)h.k), dim3(64), 0, s, loss_part, n_slots, h.loss, h.B, h.active_mask);
   return hipGetLastError();
 }
 
@@ -130,9 +149,14 @@ int run_network(const dw_config& cfg, char* ws, const Layout& lay, const void* d
     a.k = k; a.active_mask = active;
     if (plain) { a.plain = 1; a.RX = nullptr; a.ry_bits = 0; }
     if (!b16 && l == L && out_head_f32_ok(a)) {
-      // fp32: the output layer's product and the softmax head in one kernel (the logits buffer serves as its
-      // scratch for the per-block losses)
+      // the output layer's product and the softmax head in one kernel (the logits buffer serves as its scratch for the
+      // per-block losses)
       if ((e = launch_out_head_f32(a, hd, reinterpret_cast<float*>(ws + lay.sL), s)) != hipSuccess) return DW_ERR_HIP;
+      head_done = true;
+      break;
+    }
+    if (b16 && l == L && out_head_bf16_ok(a)) {
+      if ((e = launch_out_head_bf16(a, hd, reinterpret_cast<float*>(ws + lay.sL), s)) != hipSuccess) return DW_ERR_HIP;
       head_done = true;
       break;
     }

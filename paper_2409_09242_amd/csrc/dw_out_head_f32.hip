@@ -8,8 +8,7 @@
 // are added in wave order through LDS.  A 16-lane group then holds one sample's 16 logits, gathers them by shuffles
 // and runs the head's arithmetic on them.  The loss of the block's samples goes to one slot per (worker, block);
 // loss_sum_kernel adds a worker's slots in index order when the caller wants the loss.
-#include "dw_internal.h"
-#include "dw_head_math.h"
+#include "dw_out_head.h"
 
 namespace dw {
 
@@ -97,57 +96,13 @@ __global__ __launch_bounds__(NT) void out_head_f32_kernel(GemmArgs a, HeadArgs h
 
   // partial tiles of the four waves: element (row, col) of a wave sits in lane col + 16*(row/4), register row%4
   __shared__ float part[NW][2][ROWS][ROWS + 1];
-  __shared__ float row_loss[ROWS];
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     part[wave][0][kg * 4 + r][r16] = acc[r];
     part[wave][1][kg * 4 + r][r16] = racc[r];
   }
   __syncthreads();
-  const int m = tid >> 4, n = tid & 15;                   // one 16-lane group per sample, one lane per class
-  float s = 0.f, rs = 0.f;
-  if (n < a.N) {
-#pragma unroll
-    for (int w = 0; w < NW; ++w) { s += part[w][0][m][n]; rs += part[w][1][m][n]; }
-    const int64_t bi = a.zb_off + n;
-    s += a.bias[(int64_t)worker * a.bias_wstride + n];
-    rs += ((zb[bi >> 5] >> (bi & 31)) & 1u) ? 1.f : -1.f;
-  }
-  // every lane of the group gathers the sample's logits and runs the head on them; it keeps its own class
-  float sv[DW_MAX_CLASSES], rsv[DW_MAX_CLASSES], d[DW_MAX_CLASSES], rd[DW_MAX_CLASSES];
-  const int base = lane & 48;
-#pragma unroll
-  for (int c = 0; c < DW_MAX_CLASSES; ++c) { sv[c] = __shfl(s, base + c); rsv[c] = __shfl(rs, base + c); }
-  const int row = row0 + m;
-  const int yrow = row < a.M ? row : a.M - 1;
-  const int y = h.y[(int64_t)worker * h.B + yrow];
-  const float lrow = head_row(sv, rsv, y, h.C, 1.0f / (float)h.B, d, rd);
-  float dn = 0.f, rdn = 0.f;
-#pragma unroll
-  for (int c = 0; c < DW_MAX_CLASSES; ++c) { if (c == n) { dn = d[c]; rdn = rd[c]; } }
-  if (row < a.M && n < h.ld) {
-    const int64_t o = ((int64_t)worker * h.B + row) * h.ld + n;
-    h.delta[o] = dn;
-    h.Rdelta[o] = rdn;
-  }
-  if (n == 0) row_loss[m] = row < a.M ? lrow : 0.f;
-  __syncthreads();
-  if (tid == 0) {
-    float t = 0.f;
-#pragma unroll
-    for (int r = 0; r < ROWS; ++r) t += row_loss[r];
-    loss_part[(int64_t)worker * gridDim.x + blockIdx.x] = t;
-  }
-}
-
-// loss[i] = (sum of worker i's slots, in index order) / B
-__global__ __launch_bounds__(64) void loss_sum_kernel(const float* loss_part, int n_slots, float* loss, int k, int B,
-                                                      uint64_t active_mask) {
-  const int i = threadIdx.x;
-  if (i >= k || !((active_mask >> i) & 1ull)) return;
-  float t = 0.f;
-  for (int b = 0; b < n_slots; ++b) t += loss_part[(int64_t)i * n_slots + b];
-  loss[i] = t / (float)B;
+  out_head_rows<NW>(part, a, h, loss_part, worker, row0, zb);
 }
 
 }  // namespace f32o
@@ -173,8 +128,7 @@ hipError_t launch_out_head_f32(const GemmArgs& a, const HeadArgs& h, float* loss
   hipLaunchKernelGGL(f32o::out_head_f32_kernel, grid, dim3(f32o::NT), 0, s, a, h, loss_part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !h.loss) return e;
-  hipLaunchKernelGGL(f32o::loss_sum_kernel, dim3(1), dim3(64), 0, s, loss_part, n_slots, h.loss, a.k, h.B, a.active_mask);
-  return hipGetLastError();
+  return launch_loss_sum(loss_part, n_slots, h, s);
 }
 
 }  // namespace dw
