@@ -622,6 +622,29 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
   }
 }
 
+// c = the sum over the slices of p[slice * step], rc the same of p[slice * step + second], added in slice order.  One load at
+// a time this is bound by the memory's latency, slice after slice, so eight slices' loads go out together (small CNN, ten
+// workers, three weight gradients in tens of slices: 25 -> 9.4 us each; 15.3 with the loads of the bias sums still serial).
+__device__ __forceinline__ void sum_slices(const float* p, int64_t step, int64_t second, int slices, bool plain, float& c, float& rc) {
+  constexpr int kInFlight = 8;
+  c = 0.f; rc = 0.f;
+  int sl = 0;
+  for (; sl + kInFlight <= slices; sl += kInFlight) {
+    float v[kInFlight], rv[kInFlight];
+#pragma unroll
+    for (int j = 0; j < kInFlight; ++j) {
+      v[j] = p[(sl + j) * step];
+      rv[j] = plain ? 0.f : p[(sl + j) * step + second];
+    }
+#pragma unroll
+    for (int j = 0; j < kInFlight; ++j) { c += v[j]; rc += rv[j]; }
+  }
+  for (; sl < slices; ++sl) {
+    c += p[sl * step];
+    if (!plain) rc += p[sl * step + second];
+  }
+}
+
 // adds the slices of a product cut along its contraction, in slice order, and applies the epilogue the main kernel
 // left out: C, RC (M rows of ldc, columns < N) and, for a weight gradient, the bias sums gb, hzb (M)
 __global__ __launch_bounds__(256) void sum_slices_kernel(GemmArgs a) {
@@ -630,12 +653,9 @@ __global__ __launch_bounds__(256) void sum_slices_kernel(GemmArgs a) {
   const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int n = (int)(e % a.ldc);
   if (e < n_out && n < a.N) {
-    float c = 0.f, rc = 0.f;
-    for (int sl = 0; sl < a.ksplit; ++sl) {
-      const float* p = a.part + (((int64_t)sl * a.k + worker) * 2) * a.part_stride;
-      c += p[e];
-      if (!a.plain) rc += p[a.part_stride + e];
-    }
+    float c, rc;
+    sum_slices(a.part + (int64_t)worker * 2 * a.part_stride + e, (int64_t)a.k * 2 * a.part_stride, a.part_stride, a.ksplit,
+               a.plain != 0, c, rc);
     if (a.epi == EPI_RELU || a.epi == EPI_LINEAR) {
       const uint32_t* zb = a.zbits + (int64_t)worker * a.z_stride;
       const int64_t bi = a.zb_off + n;
@@ -650,12 +670,8 @@ __global__ __launch_bounds__(256) void sum_slices_kernel(GemmArgs a) {
     if (!a.plain) reinterpret_cast<float*>(a.RC)[(int64_t)worker * a.c_wstride + e] = rc;
   }
   if (a.epi == EPI_WGRAD && e < a.M) {
-    float b = 0.f, rb = 0.f;
-    for (int sl = 0; sl < a.ksplit; ++sl) {
-      const float* p = a.part_b + (((int64_t)sl * a.k + worker) * 2) * a.M;
-      b += p[e];
-      if (!a.plain) rb += p[a.M + e];
-    }
+    float b, rb;
+    sum_slices(a.part_b + (int64_t)worker * 2 * a.M + e, (int64_t)a.k * 2 * a.M, a.M, a.ksplit, a.plain != 0, b, rb);
     a.gb[(int64_t)worker * a.c_wstride + e] = b;
     if (!a.plain) a.hzb[(int64_t)worker * a.c_wstride + e] = rb;
   }
