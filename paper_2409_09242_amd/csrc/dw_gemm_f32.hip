@@ -566,7 +566,11 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
       double sum = 0.0;
 #pragma unroll
       for (int w = 0; w < NT / 64; ++w) sum += red[w];
-      f.partials[(int64_t)worker * f.part_stride + f.part_base + blockIdx.x] = sum;
+      // one slot per 128 x 128 of W, cleared before the step: two blocks add to it, and 0 + p + q is 0 + q + p
+      const int slot = row0 / 128 * (a.N / 128) + col0 / 128;
+      static_assert(EPI != EPI_WGRAD_FUSED || (128 % BM == 0 && 128 / BM <= 2 && BN == 128), "at most two blocks to a slot");
+      __hip_atomic_fetch_add(&f.partials[(int64_t)worker * f.part_stride + f.part_base + slot], sum, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
     }
     return;
   }
@@ -768,10 +772,10 @@ bool gemm_f32_wgrad_fusable(int n_out, int n_in, int k, int avg_block, float hpo
   if ((int64_t)n_out * n_in >= (1ll << 31)) return false;
   return (int64_t)(n_out / 128) * (n_in / 128) * k >= 512;
 }
-int gemm_f32_wgrad_tiles(int n_out, int n_in) { return (n_out / kFuseBM) * (n_in / kFuseBN); }
+int gemm_f32_wgrad_tiles(int n_out, int n_in) { return (n_out / 128) * (n_in / 128); }   // partial-sum slots
 
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
-  KernelScope ks(a.epi == EPI_WGRAD ? KC_GEMM_WGRAD : (a.epi == EPI_MASK || a.epi == EPI_PLAIN) ? KC_GEMM_DGRAD : KC_GEMM_FWD, s);
+  KernelScope ks(a.epi == EPI_WGRAD ? KC_GEMM_WGRAD : a.epi == EPI_MASK ? KC_GEMM_DGRAD : KC_GEMM_FWD, s);
   if (a.epi == EPI_WGRAD && a.fu.on) return launch_fused_wgrad(a, s);
   if (a.N <= 32) return launch_shape<128, 32, 4, 1>(a, s);
   if (a.M <= 32) return launch_shape<32, 128, 1, 4>(a, s);

@@ -238,7 +238,7 @@ hipError_t launch_gemm_f32_short(const GemmArgs& a, hipStream_t s);
 // and how many partial-sum slots (tiles) does it then write per worker when a step has n_samples Hutchinson probes?
 bool gemm_bf16_wgrad_fusable(int n_out, int n_in, int k, int avg_block, float hpow, int64_t woff);
 int gemm_bf16_wgrad_tiles(int n_out, int n_in, int n_samples);
-bool gemm_f32_wgrad_fusable(int n_out, int n_in, int k, int avg_block, float hpow, int64_t woff);   // same for fp32 (128 x 128 tiles)
+bool gemm_f32_wgrad_fusable(int n_out, int n_in, int k, int avg_block, float hpow, int64_t woff);   // same for fp32: a slot per 128 x 128
 int gemm_f32_wgrad_tiles(int n_out, int n_in);
 // would the data gradient through W[n_out][n_in] of a minibatch of `batch` samples take the large-tile kernel
 // (given the transposed sign bits)?
