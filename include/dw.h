@@ -142,7 +142,8 @@ typedef struct {
   /* Baseline worker steps (Section VI compares against elastic averaging SGD with and without momentum).  With
    * DW_OPT_SGD or DW_OPT_MOMENTUM the step uses the minibatch gradient alone: no z is drawn, avg_block, hpow, the
    * betas and eps are not used, n_samples must be 0 or 1 and fuse_update 0, and dw_update_only ignores d_hz (it
-   * may be NULL).  The communication round is the same call (DW_FIXED gives elastic averaging SGD). */
+   * may be NULL).  Without a z there is no Hessian-vector product: DW_S_HZ is of use after such a step only when the
+   * caller passed one.  The communication round is the same call (DW_FIXED gives elastic averaging SGD). */
   int32_t optimizer;                /* DW_OPT_ADAHESSIAN (0, default) | DW_OPT_SGD | DW_OPT_MOMENTUM          */
   float momentum;                   /* delta of DW_OPT_MOMENTUM, 0 <= momentum < 1                           */
 } dw_config;

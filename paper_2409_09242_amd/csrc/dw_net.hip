@@ -107,8 +107,9 @@ int run_network(const dw_config& cfg, char* ws, const Layout& lay, const void* d
   auto gemm = [&](const GemmArgs& a) { return gemm_on(a, s); };
   hipError_t e;
   // a baseline's first-order step of an fp32 MLP needs the plain products alone (784-512-512-10, four workers: 127 -> 100 us;
-  // bf16 and convolutional models still run the R-companions along)
-  const int plain = !b16 && lay.n_conv == 0 && cfg.optimizer != DW_OPT_ADAHESSIAN ? 1 : 0;
+  // bf16 and convolutional models still run the R-companions along); with the caller's z, Hz stays readable (DW_S_HZ)
+  const bool own_z = zbits == reinterpret_cast<const uint32_t*>(ws + lay.zbits);
+  const int plain = !b16 && lay.n_conv == 0 && cfg.optimizer != DW_OPT_ADAHESSIAN && own_z ? 1 : 0;
 
   // layers whose data gradient reads the sign bits of V_l column by column get a transposed copy of those bits
   // (when the caller's z allows 16-byte accesses; otherwise those layers take the general kernel)

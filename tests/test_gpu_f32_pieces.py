@@ -99,3 +99,17 @@ def test_first_order_steps_compute_the_plain_products_alone(opt, dims, batch, k)
         # the step is lr * g with g held to 1e-4; read back as a difference of two stored parameters it carries an ulp of
         # theta, up to 2^-24 * 0.5 = 3e-8, against lr * rms(g) of 2e-5 and more in every layer
         close_layers(h.get_state(B.DW_S_THETA, i) - theta0, tr.theta[i] - theta0, dims, 2e-3, "update[%d]" % i)
+
+
+def test_a_first_order_step_with_the_callers_z_leaves_its_hessian_vector_product_readable():
+    dims, batch, k = (132, 192, 64, 3), 31, 2
+    theta0, x, y = _inputs(dims, batch, k, 81)
+    z = torch.from_numpy(np.random.default_rng(81).integers(0, 2 ** 32, size=(k, 2 * ((len(theta0) + 63) // 64)),
+                                                            dtype=np.uint32).view(np.int32)).cuda()
+    hz = []
+    for opt in (B.DW_OPT_ADAHESSIAN, B.DW_OPT_MOMENTUM):
+        w = W.scaled(W.C2, k=k, dims=dims, batch=batch, input_dist="normal", optimizer=opt, seed=81)
+        h = B.Handle(B.config_from_workload(w), theta0.astype(np.float32))
+        h.worker_step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), zbits=z)
+        hz.append([h.get_state(B.DW_S_HZ, i) for i in range(k)])
+    np.testing.assert_array_equal(hz[0], hz[1])                       # the same products of the same kernels
