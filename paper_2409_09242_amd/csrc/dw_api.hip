@@ -182,11 +182,10 @@ int validate(const dw_config* c, Layout* lay) {
     lay->pidx = take(flat);
   }
   if (L > 0 && c->dtype == DW_F32) {
-    // fp32 forward products with a long contraction and a handful of output tiles (the output layer; the first linear
-    // layer behind a convolutional front end): same cut, slices of at least 64 (measured: 256 -> 64 takes 12 % off
-    // the step of the 784-512-512-10 configuration, nothing off the others)
+    // fp32 forward products of hidden layers with a long contraction and a handful of output tiles (the first linear
+    // layer behind a convolutional front end): same cut, slices of at least 64
     const int64_t B = c->batch;
-    for (int l = 1; l <= L; ++l) {
+    for (int l = 1; l < L; ++l) {
       const int64_t n = c->dims[l], kk = c->dims[l - 1];
       const int64_t tiles = n <= 32 ? (B + 127) / 128 : B <= 32 ? (n + 127) / 128 : ((B + 63) / 64) * ((n + 63) / 64);
       int64_t split = tiles * k < 256 ? 1024 / (tiles * k) : 1;
@@ -194,7 +193,7 @@ int validate(const dw_config* c, Layout* lay) {
       if (split > 64) split = 64;
       lay->fwdSplit[l - 1] = (int)(split < 1 ? 1 : split);
       if (lay->fwdSplit[l - 1] > 1) {
-        const size_t need = (size_t)lay->fwdSplit[l - 1] * k * 2 * B * (l == L ? DW_MAX_CLASSES : n) * 4;
+        const size_t need = (size_t)lay->fwdSplit[l - 1] * k * 2 * B * n * 4;
         part = need > part ? need : part;
       }
     }

@@ -702,8 +702,8 @@ static hipError_t launch_shape(const GemmArgs& a, hipStream_t s) {
     return rx ? launch_one<BM, BN, WM, WN, true, true, true, RY_BITS, EPI_RELU>(a, s)
               : launch_one<BM, BN, WM, WN, true, true, false, RY_BITS, EPI_RELU>(a, s);
   } else if (a.epi == EPI_LINEAR) {
-    return rx ? launch_one<BM, BN, WM, WN, true, true, true, RY_BITS, EPI_LINEAR>(a, s)
-              : launch_one<BM, BN, WM, WN, true, true, false, RY_BITS, EPI_LINEAR>(a, s);
+    if (rx) return hipErrorInvalidValue;               // (out_head_bf16 takes an output layer above hidden ones)
+    return launch_one<BM, BN, WM, WN, true, true, false, RY_BITS, EPI_LINEAR>(a, s);
   } else if (a.epi == EPI_MASK) {
     return launch_one<BM, BN, WM, WN, true, false, true, RY_BITS, EPI_MASK>(a, s);
   }

@@ -348,7 +348,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
   const uint32_t* zb = a.zbits + (int64_t)worker * a.z_stride;
 
   // the slice of the contraction this block covers (all of it unless the product is cut along k)
-  const bool sliced = (EPI == EPI_WGRAD || EPI == EPI_RELU || EPI == EPI_LINEAR || EPI == EPI_MASK) && a.ksplit > 1;
+  const bool sliced = (EPI == EPI_WGRAD || EPI == EPI_RELU || EPI == EPI_MASK) && a.ksplit > 1;
   const int kchunk = sliced ? ((a.K + a.ksplit - 1) / a.ksplit + BK - 1) / BK * BK : a.K;
   const int kbeg = sliced ? (int)blockIdx.z * kchunk : 0;
   const int kend = sliced ? (kbeg + kchunk < a.K ? kbeg + kchunk : a.K) : a.K;
@@ -586,7 +586,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
     const int n = col0 + wn0 + j * 32 + l32;
     const bool n_ok = n < a.N;
     float bias = 0.f, cz = 0.f;
-    if ((EPI == EPI_RELU || EPI == EPI_LINEAR) && n_ok) {
+    if (EPI == EPI_RELU && n_ok) {
       bias = a.bias[(int64_t)worker * a.bias_wstride + n];
       const int64_t bi = a.zb_off + n;
       if (HAS_R) cz = ((zb[bi >> 5] >> (bi & 31)) & 1u) ? 1.f : -1.f;
@@ -609,9 +609,6 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
           const bool on = c > 0.f;
           C[o] = on ? c : 0.f;
           if (HAS_R) RC[o] = on ? rc : 0.f;
-        } else if (EPI == EPI_LINEAR) {
-          C[o] = c + bias;
-          if (HAS_R) RC[o] = rc + cz;
         } else if (EPI == EPI_MASK) {
           const float* msk = reinterpret_cast<const float*>(a.mask_src) + (int64_t)worker * a.mask_wstride;
           const bool on = msk[(int64_t)m * a.ld_mask + n] > 0.f;
@@ -660,12 +657,12 @@ __global__ __launch_bounds__(256) void sum_slices_kernel(GemmArgs a) {
     float c, rc;
     sum_slices(a.part + (int64_t)worker * 2 * a.part_stride + e, (int64_t)a.k * 2 * a.part_stride, a.part_stride, a.ksplit,
                a.plain != 0, c, rc);
-    if (a.epi == EPI_RELU || a.epi == EPI_LINEAR) {
+    if (a.epi == EPI_RELU) {
       const uint32_t* zb = a.zbits + (int64_t)worker * a.z_stride;
       const int64_t bi = a.zb_off + n;
       c += a.bias[(int64_t)worker * a.bias_wstride + n];
       if (!a.plain) rc += ((zb[bi >> 5] >> (bi & 31)) & 1u) ? 1.f : -1.f;
-      if (a.epi == EPI_RELU && !(c > 0.f)) { c = 0.f; rc = 0.f; }
+      if (!(c > 0.f)) { c = 0.f; rc = 0.f; }
     } else if (a.epi == EPI_MASK) {
       const float* msk = reinterpret_cast<const float*>(a.mask_src) + (int64_t)worker * a.mask_wstride;
       if (!(msk[(e / a.ldc) * a.ld_mask + n] > 0.f)) { c = 0.f; rc = 0.f; }
@@ -700,7 +697,7 @@ static hipError_t launch_instance(const GemmArgs& a, dim3 grid, hipStream_t s) {
 template <int BM, int BN, int WM, int WN>
 static hipError_t launch_shape(const GemmArgs& a, hipStream_t s) {
   const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  const bool sliced = (a.epi == EPI_WGRAD || a.epi == EPI_RELU || a.epi == EPI_LINEAR || a.epi == EPI_MASK) && a.ksplit > 1;
+  const bool sliced = a.ksplit > 1;
   const dim3 grid((unsigned)tiles, (unsigned)active_count(a.active_mask, a.k), (unsigned)(sliced ? a.ksplit : 1));
   const bool rx = a.RX != nullptr;
   hipError_t e;
@@ -719,7 +716,6 @@ static hipError_t launch_shape(const GemmArgs& a, hipStream_t s) {
   } else if (a.plain) {
     // a first-order step: the plain products alone
     if (a.epi == EPI_RELU) DW_GO(true, true, false, RY_NONE, EPI_RELU);
-    else if (a.epi == EPI_LINEAR) DW_GO(true, true, false, RY_NONE, EPI_LINEAR);
     else if (a.epi == EPI_MASK) DW_GO(true, false, false, RY_NONE, EPI_MASK);
     else if (a.epi == EPI_WGRAD) DW_GO(false, false, false, RY_NONE, EPI_WGRAD);
     else return hipErrorInvalidValue;
@@ -730,14 +726,12 @@ static hipError_t launch_shape(const GemmArgs& a, hipStream_t s) {
     DW_GO(true, false, true, RY_BITS, EPI_MASK, 1);
   } else if (a.epi == EPI_RELU) {              // forward, hidden layer
     if (rx) DW_GO(true, true, true, RY_BITS, EPI_RELU); else DW_GO(true, true, false, RY_BITS, EPI_RELU);
-  } else if (a.epi == EPI_LINEAR) {            // forward, output layer
-    if (rx) DW_GO(true, true, true, RY_BITS, EPI_LINEAR); else DW_GO(true, true, false, RY_BITS, EPI_LINEAR);
   } else if (a.epi == EPI_MASK) {              // data gradient
     DW_GO(true, false, true, RY_BITS, EPI_MASK);
-  } else if (a.epi == EPI_PLAIN) {             // data gradient stored unmasked (the mask follows a col2im)
-    DW_GO(true, false, true, RY_BITS, EPI_PLAIN);
-  } else {                                     // weight gradient
+  } else if (a.epi == EPI_WGRAD) {             // weight gradient
     if (a.RY) DW_GO(false, false, true, RY_MEM, EPI_WGRAD); else DW_GO(false, false, true, RY_NONE, EPI_WGRAD);
+  } else {
+    return hipErrorInvalidValue;
   }
 #undef DW_GO
   if (e != hipSuccess) return e;

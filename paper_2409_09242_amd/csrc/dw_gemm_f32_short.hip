@@ -188,9 +188,6 @@ __global__ __launch_bounds__(NW * 64) void short_gemm_f32(GemmArgs a) {
       const bool on = (HAS_C ? c : C[o]) > 0.f;              // (a later probe: the activation is in memory)
       if (HAS_C) C[o] = on ? c : 0.f;
       if (HAS_R) RC[o] = on ? rc : 0.f;
-    } else if (EPI == EPI_LINEAR) {
-      C[o] = c + bias;
-      if (HAS_R) RC[o] = rc + cz;
     } else {
       const bool on = reinterpret_cast<const float*>(a.mask_src)[(int64_t)worker * a.mask_wstride + (int64_t)m * a.ld_mask + n] > 0.f;
       if (HAS_C) C[o] = on ? c : 0.f;
@@ -221,7 +218,7 @@ static hipError_t launch(const GemmArgs& a, hipStream_t s) {
 // choice must not depend on who steps.)
 bool gemm_f32_short_ok(const GemmArgs& a) {
   if (a.x_view != VIEW_NONE || a.y_view != VIEW_NONE || a.ksplit > 1 || !(a.ry_bits || a.plain)) return false;
-  if (a.epi == EPI_MASK ? a.K > f32s::kStep || (!a.plain && !a.RX) : a.epi != EPI_RELU && a.epi != EPI_LINEAR) return false;
+  if (a.epi == EPI_MASK ? a.K > f32s::kStep || (!a.plain && !a.RX) : a.epi != EPI_RELU) return false;
   if (a.K > 4096) return false;
   return (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) * a.k < 256;
 }
@@ -230,10 +227,9 @@ template <int NW>
 static hipError_t launch_forward(const GemmArgs& a, hipStream_t s) {
   using namespace f32s;
   const bool rx = a.RX != nullptr;
-  if (a.plain) return a.epi == EPI_RELU ? launch<NW, true, false, false, EPI_RELU, 0>(a, s) : launch<NW, true, false, false, EPI_LINEAR, 0>(a, s);
-  if (a.epi == EPI_RELU && a.r_only) return rx ? launch<NW, true, true, true, EPI_RELU, 1>(a, s) : launch<NW, true, false, true, EPI_RELU, 1>(a, s);
-  if (a.epi == EPI_RELU) return rx ? launch<NW, true, true, true, EPI_RELU, 0>(a, s) : launch<NW, true, false, true, EPI_RELU, 0>(a, s);
-  return rx ? launch<NW, true, true, true, EPI_LINEAR, 0>(a, s) : launch<NW, true, false, true, EPI_LINEAR, 0>(a, s);
+  if (a.plain) return launch<NW, true, false, false, EPI_RELU, 0>(a, s);
+  if (a.r_only) return rx ? launch<NW, true, true, true, EPI_RELU, 1>(a, s) : launch<NW, true, false, true, EPI_RELU, 1>(a, s);
+  return rx ? launch<NW, true, true, true, EPI_RELU, 0>(a, s) : launch<NW, true, false, true, EPI_RELU, 0>(a, s);
 }
 
 hipError_t launch_gemm_f32_short(const GemmArgs& a, hipStream_t s) {

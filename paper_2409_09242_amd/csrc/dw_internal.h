@@ -163,8 +163,8 @@ enum GemmKind { GEMM_FWD = 0, GEMM_DGRAD = 1, GEMM_WGRAD = 2 };
 // Channel counts are multiples of 4, so four consecutive columns are four consecutive floats of the map (of W).
 enum OperandView { VIEW_NONE = 0, VIEW_PATCH = 1, VIEW_SHIFTED = 2, VIEW_TAPS = 3 };
 struct ConvView { int H, W, Cin, Cout; };   // the convolution's input map and channel counts (its output map is (H-2) x (W-2) x Cout)
-// PLAIN: a data gradient stored as it is.  WGRAD_FUSED: template instance of the fp32 kernel for EPI_WGRAD with fu.on
-enum Epilogue { EPI_RELU = 0, EPI_LINEAR = 1, EPI_MASK = 2, EPI_WGRAD = 3, EPI_PLAIN = 4, EPI_WGRAD_FUSED = 5 };
+// LINEAR: an output layer.  WGRAD_FUSED: template instance of the fp32 kernel for EPI_WGRAD with fu.on
+enum Epilogue { EPI_RELU = 0, EPI_LINEAR = 1, EPI_MASK = 2, EPI_WGRAD = 3, EPI_WGRAD_FUSED = 4 };
 
 // One "dual-number" GEMM: C = X*Y and RC = RX*Y + X*RY for all workers (grid y = worker).
 // Element strides describe how the logical operands X[M][K], Y[K][N] sit in memory.
@@ -185,7 +185,7 @@ struct GemmArgs {
   int64_t zb_off;                                     // bit offset of the bias part of z
   float* gb; float* hzb;                              // EPI_WGRAD: bias-gradient outputs (g + b_off, hz + b_off)
   FuseArgs fu;                                        // EPI_WGRAD: fu.on != 0 replaces the stores of C and RC by the update
-  // fp32 forward (EPI_RELU, EPI_LINEAR) or weight gradient with a long contraction and few output tiles: the contraction is cut into ksplit slices
+  // fp32 forward product, data or weight gradient with a long contraction and few output tiles: the contraction is cut into ksplit slices
   // (grid z), slice s of worker i writes its partial products to part + ((s*k + i)*2 + {0,1})*part_stride and its
   // partial bias sums (weight gradient) to part_b + ((s*k + i)*2 + {0,1})*M; a second kernel adds the slices in order and
   // applies the epilogue (bias, ReLU) into C, RC, gb, hzb

@@ -149,7 +149,8 @@ int run_network(const dw_config& cfg, char* ws, const Layout& lay, const void* d
     }
     a.k = k; a.active_mask = active;
     if (plain) { a.plain = 1; a.RX = nullptr; a.ry_bits = 0; }
-    if (!b16 && l == L && out_head_f32_ok(a)) {
+    if (!b16 && l == L) {
+      if (!out_head_f32_ok(a)) return DW_ERR_CONFIG;   // (every configuration that was accepted passes)
       // the output layer's product and the softmax head in one kernel (the logits buffer serves as its scratch for the
       // per-block losses)
       if ((e = launch_out_head_f32(a, hd, reinterpret_cast<float*>(ws + lay.sL), s)) != hipSuccess) return DW_ERR_HIP;
