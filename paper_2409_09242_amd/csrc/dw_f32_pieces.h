@@ -7,8 +7,15 @@
 // below the last bit of the running sum, always downwards (measured: -1e-8 to -4e-7 of the result's root mean square, which
 // the sums over thousands of positions that follow add up).  Error of one product against 64 bits (2-norm, K = 64 / 1024 /
 // 9216, normal operands): 5e-8 / 1.8e-7 / 5.9e-7, no bias; v_mfma_f32_32x32x2_f32 1.5e-7 / 5.7e-7 / 1.7e-6.
-// An infinity has no pieces (inf - inf), and inf * (y1 + y2 + y3) would be no number either where y2 is 0 or of the other sign:
-// the kernels compute a tile again on the fp32 matrix instruction when a result is no number.
+//
+// The pieces are those of 2^24 times the number, so that every piece of every fp32 number, the subnormal ones among them, is a
+// normal bf16 number (the matrix cores lose subnormal ones: operands of 2^-118 and 32 k, 2^24-fold pieces 3.9e-8, pieces of the
+// number itself 8.8e-6, of 2^-130 3.6e-2); the +-1 operand is +-2^24 likewise, the results are 2^48-fold and leave through
+// kUnscale.  That takes one multiplication per element (3072-1024^3, eight workers: 935 -> 959 us a step) and leaves operands
+// below 2^104 and results below 2^80.
+//
+// A larger operand or result, an infinity (which has no pieces: inf - inf) or a NaN gives a result that is infinite or no number:
+// the kernels then compute the tile again from the whole floats on the fp32 matrix instruction, which gives what such operands give.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -25,28 +32,41 @@ __device__ __forceinline__ uint32_t to_bf16x2(float a, float b) {        // roun
   const floatx2 v = {a, b};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
-// the three pieces of a pair of floats, packed: the first is cut off (never overflows), the others are rounded
-template <bool INF>
+constexpr float kScale = 0x1p24f, kUnscale = 0x1p-48f;
+// the three pieces of a pair of floats, packed: the first is cut off, the others are rounded.  HALVES: the two halves of the
+// floats' own bits instead, for the pass on the fp32 instruction
+template <bool HALVES>
 __device__ __forceinline__ void split_pair(float a, float b, uint32_t& p1, uint32_t& p2, uint32_t& p3) {
+  if (!HALVES) { a *= kScale; b *= kScale; }
   const uint32_t au = __float_as_uint(a), bu = __float_as_uint(b);
   p1 = __builtin_amdgcn_perm(bu, au, 0x07060302u);
-  float ra = a - __uint_as_float(au & 0xFFFF0000u), rb = b - __uint_as_float(bu & 0xFFFF0000u);
-  if (INF) {                                                 // inf - inf would be a NaN
-    if ((au & 0x7FFFFFFFu) == 0x7F800000u) ra = 0.f;
-    if ((bu & 0x7FFFFFFFu) == 0x7F800000u) rb = 0.f;
+  if (HALVES) {
+    p2 = __builtin_amdgcn_perm(bu, au, 0x05040100u);
+    p3 = 0u;
+    return;
   }
+  float ra = a - __uint_as_float(au & 0xFFFF0000u), rb = b - __uint_as_float(bu & 0xFFFF0000u);
   p2 = to_bf16x2(ra, rb);
   ra -= __uint_as_float(p2 << 16); rb -= __uint_as_float(p2 & 0xFFFF0000u);
   p3 = to_bf16x2(ra, rb);
 }
-template <bool INF, int N>                                   // N pairs
+template <bool HALVES, int N>                                // N pairs
 __device__ __forceinline__ void split_pairs(const float (&x)[2 * N], uint32_t (&p)[3][N]) {
 #pragma unroll
-  for (int i = 0; i < N; ++i) split_pair<INF>(x[2 * i], x[2 * i + 1], p[0][i], p[1][i], p[2][i]);
+  for (int i = 0; i < N; ++i) split_pair<HALVES>(x[2 * i], x[2 * i + 1], p[0][i], p[1][i], p[2][i]);
 }
-// +-1 as a pair of bf16 from two bits (bit set: +1)
+// +-2^24 as a pair of bf16 from two bits (bit set: +)
 __device__ __forceinline__ uint32_t sign_pair(uint32_t b0, uint32_t b1) {
-  return 0xBF80BF80u ^ ((b0 & 1u) << 15) ^ ((b1 & 1u) << 31);
+  return 0xCB80CB80u ^ ((b0 & 1u) << 15) ^ ((b1 & 1u) << 31);
+}
+// the two chains of a result (below) put together: the result, and whether it is finite
+__device__ __forceinline__ bool join_chains(floatx16& m, const floatx16& t) {
+  m += t;
+  bool finite = true;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) finite &= __builtin_fabsf(m[r]) < __builtin_inff();
+  m *= kUnscale;
+  return finite;
 }
 
 // the products of one k-step of 16 of two numbers in three pieces: those of the first pieces to m, the others to t

@@ -10,8 +10,8 @@
 // R-companion.  The +-1 operand V is never stored as a matrix: its tile is expanded from the sign bits of
 // z while the W tile is staged.
 //
-// The products run on the bf16 matrix cores, every float split into three pieces (dw_f32_pieces.h).  Tiles with infinities
-// or NaN are computed again on the fp32 matrix instruction (below).
+// The products run on the bf16 matrix cores, every float split into three pieces (dw_f32_pieces.h).  Tiles with results that
+// are not finite are computed again on the fp32 matrix instruction (below).
 //
 // Tiling: waves of 32 rows by 32 or 64 columns; tiles of 32 k are split into their pieces once per block while they are
 // stored to LDS (planes [row][32 k] of bf16, 64-byte rows, 16-byte units XOR-swizzled so that both the
@@ -170,11 +170,11 @@ struct TileLoader {
 
   // unit u of v into its pieces.  sums: [NU][4], receives the column sums of the unit's rows (k-major operands; bias
   // gradients)
-  template <bool INF>
+  template <bool HALVES>
   __device__ __forceinline__ void split_unit(int u, uint32_t (&s)[3][NV * 2], bool want_sums, float (&sums)[NU][4]) const {
     if constexpr (KC) {
       const float x[8] = {v[u][0].x, v[u][0].y, v[u][0].z, v[u][0].w, v[u][1].x, v[u][1].y, v[u][1].z, v[u][1].w};
-      split_pairs<INF, 4>(x, s);
+      split_pairs<HALVES, 4>(x, s);
     } else {
       const float x[16] = {v[u][0].x, v[u][1].x, v[u][2].x, v[u][3].x, v[u][0].y, v[u][1].y, v[u][2].y, v[u][3].y,
                            v[u][0].z, v[u][1].z, v[u][2].z, v[u][3].z, v[u][0].w, v[u][1].w, v[u][2].w, v[u][3].w};
@@ -182,7 +182,7 @@ struct TileLoader {
 #pragma unroll
         for (int r = 0; r < 4; ++r) sums[u][r] += (x[4 * r] + x[4 * r + 1]) + (x[4 * r + 2] + x[4 * r + 3]);
       }
-      split_pairs<INF, 8>(x, s);
+      split_pairs<HALVES, 8>(x, s);
     }
   }
   __device__ __forceinline__ static void store_unit(char* lds, int op, int w, const uint32_t (&s)[3][NV * 2]) {
@@ -202,14 +202,14 @@ struct TileLoader {
     }
   }
   // the two together, unit by unit
-  template <bool INF>
+  template <bool HALVES>
   __device__ __forceinline__ void split_store(char* lds, int t, bool want_sums, float (&sums)[NU][4]) const {
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
       int op, w;
       if (!unit(u, t, op, w)) continue;
       uint32_t s[3][NV * 2];
-      split_unit<INF>(u, s, want_sums, sums);
+      split_unit<HALVES>(u, s, want_sums, sums);
       store_unit(lds, op, w, s);
     }
   }
@@ -302,15 +302,18 @@ constexpr int gemm_f32_lds(int bm, int bn, int wm, int wn, bool has_rx, int rym,
   return tiles > upd ? tiles : upd;
 }
 
-// the same on the fp32 matrix instruction, from the numbers the pieces add up to
-__device__ __forceinline__ float joined(const bf16x8 (&x)[3], int j) { return (float)x[0][j] + ((float)x[1][j] + (float)x[2][j]); }
+// the same on the fp32 matrix instruction, from the two halves of the numbers
+__device__ __forceinline__ float joined(const bf16x8 (&x)[3], int j) {
+  const uint32_t high = __builtin_bit_cast(uint16_t, x[0][j]), low = __builtin_bit_cast(uint16_t, x[1][j]);
+  return __uint_as_float(high << 16 | low);
+}
 __device__ __forceinline__ void mfma_whole(const bf16x8 (&x)[3], const bf16x8 (&y)[3], floatx16& t) {
 #pragma unroll
   for (int j = 0; j < 8; ++j) t = __builtin_amdgcn_mfma_f32_32x32x2f32(joined(x, j), joined(y, j), t, 0, 0, 0);
 }
 __device__ __forceinline__ void mfma_whole(const bf16x8 (&x)[3], const bf16x8& v, floatx16& t) {
 #pragma unroll
-  for (int j = 0; j < 8; ++j) t = __builtin_amdgcn_mfma_f32_32x32x2f32(joined(x, j), (float)v[j], t, 0, 0, 0);
+  for (int j = 0; j < 8; ++j) t = __builtin_amdgcn_mfma_f32_32x32x2f32(joined(x, j), (float)v[j] * (1.f / kScale), t, 0, 0, 0);
 }
 
 // XV, YV: OperandView of X/RX and of Y/RY (convolutions without a patch matrix in memory).  FM == 1: a Hutchinson probe
@@ -381,20 +384,20 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
   auto fetch_signs = [&](int kt) { if (RYM == RY_BITS) ls.load(zb, kbeg + kt * BK, kend, ts); };   // (one tile ahead of the products)
   typename LX::Pieces xs;                                    // STAGED: the pieces of the next tile
   typename LY::Pieces ys;
-  auto split = [&](auto inf) {
+  auto split = [&](auto halves) {
 #pragma unroll
-    for (int u = 0; u < LX::NU; ++u) lx.template split_unit<decltype(inf)::value>(u, xs[u], want_sums, sums);
+    for (int u = 0; u < LX::NU; ++u) lx.template split_unit<decltype(halves)::value>(u, xs[u], want_sums, sums);
 #pragma unroll
-    for (int u = 0; u < LY::NU; ++u) ly.template split_unit<decltype(inf)::value>(u, ys[u], false, none);
+    for (int u = 0; u < LY::NU; ++u) ly.template split_unit<decltype(halves)::value>(u, ys[u], false, none);
   };
   // Tile kt: its pieces go to LDS, then its products run.  STAGED (64 x 64 tiles of k-contiguous operands): the next tile
   // has arrived meanwhile, is split into pieces while the products run, and the one after it is asked for.  MAIN: that
   // one exists and is whole, so the step is straight-line code and the splitting is issued between the multiplies (forward,
   // 1024 wide: 92 -> 75 us).  Otherwise the next tile is asked for before the products and split after them: k-major
   // operands and larger tiles have no registers for the pieces (spills, half the speed).
-  auto step = [&](int kt, auto main, auto inf) {
+  auto step = [&](int kt, auto main, auto halves) {
     constexpr bool MAIN = decltype(main)::value;
-    constexpr bool INF = decltype(inf)::value;
+    constexpr bool HALVES = decltype(halves)::value;
     if constexpr (STAGED) {
 #pragma unroll
       for (int u = 0; u < LX::NU; ++u) {
@@ -407,15 +410,15 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
         if (LY::unit(u, tid, op, w)) LY::store_unit(Yl, op, w, ys[u]);
       }
     } else {
-      lx.template split_store<INF>(Xl, tid, want_sums, sums);
-      ly.template split_store<INF>(Yl, tid, false, none);
+      lx.template split_store<HALVES>(Xl, tid, want_sums, sums);
+      ly.template split_store<HALVES>(Yl, tid, false, none);
     }
     if (RYM == RY_BITS) ls.store(Sl, ts);
     __syncthreads();
     if (!STAGED) {
       if (kt + 1 < nkt) fetch(kt + 1, std::false_type{});
     } else if (MAIN || kt + 1 < nkt) {
-      split(inf);
+      split(halves);
       fetch_signs(kt + 1);
       if (MAIN) fetch(kt + 2, std::true_type{});
       else if (kt + 2 < nkt) fetch(kt + 2, std::false_type{});
@@ -441,7 +444,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-          if constexpr (INF) {
+          if constexpr (HALVES) {
             if (HAS_C) mfma_whole(x[i], y[j], acc[i][j]);
             if (HAS_RX) mfma_whole(rx[i], y[j], racc[i][j]);
             if (RYM == RY_MEM) mfma_whole(x[i], ry[j], racc[i][j]);
@@ -456,8 +459,8 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
     }
     __syncthreads();
   };
-  // the whole contraction; returns whether a result is not a number
-  auto contract = [&](auto with_main, auto inf) {
+  // the whole contraction; returns whether a result is not finite
+  auto contract = [&](auto with_main, auto halves) {
     lx.begin(X, RX, a.ldx, row0, a.M, kbeg, a.cv, tid);
     ly.begin(Y, RY, a.ldy, col0, a.N, kbeg, a.cv, tid);
     if (RYM == RY_BITS) ls.begin(a.z_off, a.ldy, col0, a.N, a.cv, ts);
@@ -471,31 +474,26 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
       for (int j = 0; j < TN; ++j) { acc[i][j] = zero; racc[i][j] = zero; t[i][j] = zero; tr[i][j] = zero; }
     if (nkt > 0) fetch(0, std::false_type{});
     if (STAGED) {
-      if (nkt > 0) { fetch_signs(0); split(inf); }
+      if (nkt > 0) { fetch_signs(0); split(halves); }
       if (nkt > 1) fetch(1, std::false_type{});
     }
     int kt = 0;
     if (STAGED && decltype(with_main)::value)
-      for (; kbeg + (kt + 3) * BK <= kend; ++kt) step(kt, std::true_type{}, inf);
-    for (; kt < nkt; ++kt) step(kt, std::false_type{}, inf);
-    bool nan = false;
+      for (; kbeg + (kt + 3) * BK <= kend; ++kt) step(kt, std::true_type{}, halves);
+    for (; kt < nkt; ++kt) step(kt, std::false_type{}, halves);
+    bool finite = true;
+    if constexpr (!decltype(halves)::value) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        if (HAS_C) acc[i][j] += t[i][j];
-        if (HAS_R) racc[i][j] += tr[i][j];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          if (HAS_C) nan |= __builtin_isunordered(acc[i][j][r], acc[i][j][r]);
-          if (HAS_R) nan |= __builtin_isunordered(racc[i][j][r], racc[i][j][r]);
+        for (int j = 0; j < TN; ++j) {
+          if (HAS_C) finite &= join_chains(acc[i][j], t[i][j]);
+          if (HAS_R) finite &= join_chains(racc[i][j], tr[i][j]);
         }
-      }
-    return nan;
+    }
+    return !finite;
   };
-  // An infinity has no pieces (inf - inf), and inf * (y1 + y2 + y3) would be none either where y2 is 0 or of the other sign:
-  // should a result be no number, the block starts over with the fp32 matrix instruction on whole numbers, which gives
-  // what such operands give.
+  // should a result not be finite, the block starts over with the fp32 matrix instruction on whole numbers
   if (__syncthreads_or(contract(std::true_type{}, std::false_type{}))) contract(std::false_type{}, std::true_type{});
 
   if constexpr (SUMS) {

@@ -107,7 +107,7 @@ __global__ __launch_bounds__(NW * 64) void short_gemm_f32(GemmArgs a) {
       for (int j = 0; j < 8; ++j) {
         if (HAS_C) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(s.x[h + j], s.y[h + j], acc, 0, 0, 0);
         if (HAS_RX) racc = __builtin_amdgcn_mfma_f32_32x32x2f32(s.rx[h + j], s.y[h + j], racc, 0, 0, 0);
-        if (HAS_V) racc = __builtin_amdgcn_mfma_f32_32x32x2f32(s.x[h + j], (float)v[j], racc, 0, 0, 0);
+        if (HAS_V) racc = __builtin_amdgcn_mfma_f32_32x32x2f32(s.x[h + j], (float)v[j] * (1.f / kScale), racc, 0, 0, 0);
       }
     } else {
       auto pieces = [&](const float (&f)[kLane], bf16x8 (&o)[3]) {
@@ -142,16 +142,14 @@ __global__ __launch_bounds__(NW * 64) void short_gemm_f32(GemmArgs a) {
         multiply(s[1], whole);
       }
     }
-    bool nan = false;
-    acc += t; racc += tr;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      if (HAS_C) nan |= __builtin_isunordered(acc[r], acc[r]);
-      if (HAS_R) nan |= __builtin_isunordered(racc[r], racc[r]);
+    bool finite = true;
+    if constexpr (!decltype(whole)::value) {
+      if (HAS_C) finite &= join_chains(acc, t);
+      if (HAS_R) finite &= join_chains(racc, tr);
     }
-    return nan;
+    return !finite;
   };
-  if (__syncthreads_or(contract(std::false_type{}))) contract(std::true_type{});       // (infinities; see dw_f32_pieces.h)
+  if (__syncthreads_or(contract(std::false_type{}))) contract(std::true_type{});       // (see dw_f32_pieces.h)
 
   // partial tiles: [wave][C, RC][32][32]; lane holds column l32, rows (r/4)*8 + lhalf*4 + r%4
   extern __shared__ __attribute__((aligned(16))) float part[];
