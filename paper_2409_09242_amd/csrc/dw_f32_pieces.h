@@ -26,6 +26,7 @@ namespace dw {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ uint32_t to_bf16x2(float a, float b) {        // round to nearest even, a in the low half

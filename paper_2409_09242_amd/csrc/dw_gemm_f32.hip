@@ -304,8 +304,8 @@ constexpr int gemm_f32_lds(int bm, int bn, int wm, int wn, bool has_rx, int rym,
 
 // the same on the fp32 matrix instruction, from the two halves of the numbers
 __device__ __forceinline__ float joined(const bf16x8 (&x)[3], int j) {
-  const uint32_t high = __builtin_bit_cast(uint16_t, x[0][j]), low = __builtin_bit_cast(uint16_t, x[1][j]);
-  return __uint_as_float(high << 16 | low);
+  const u16x8 high = __builtin_bit_cast(u16x8, x[0]), low = __builtin_bit_cast(u16x8, x[1]);
+  return __uint_as_float((uint32_t)high[j] << 16 | low[j]);
 }
 __device__ __forceinline__ void mfma_whole(const bf16x8 (&x)[3], const bf16x8 (&y)[3], floatx16& t) {
 #pragma unroll
