@@ -10,8 +10,8 @@
 // R-companion.  The +-1 operand V is never stored as a matrix: its tile is expanded from the sign bits of
 // z while the W tile is staged.
 //
-// The products run on the bf16 matrix cores, every float split into three pieces (dw_f32_pieces.h).  Tiles with results that
-// are not finite are computed again on the fp32 matrix instruction (below).
+// The products run on the bf16 matrix cores, every float split into three pieces (dw_f32_pieces.h).  Contractions of one or two,
+// and tiles whose results are not finite once more, run on the fp32 matrix instruction (below).
 //
 // Tiling: waves of 32 rows by 32 or 64 columns; tiles of 32 k are split into their pieces once per block while they are
 // stored to LDS (planes [row][32 k] of bf16, 64-byte rows, 16-byte units XOR-swizzled so that both the
@@ -493,8 +493,11 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
     }
     return !finite;
   };
-  // should a result not be finite, the block starts over with the fp32 matrix instruction on whole numbers
-  if (__syncthreads_or(contract(std::true_type{}, std::false_type{}))) contract(std::false_type{}, std::true_type{});
+  // should a result not be finite, the block starts over with the fp32 matrix instruction on whole numbers; so does every block of a
+  // very short contraction (asked after the pieces' pass: asked before it, what both passes share goes to scratch, fused weight
+  // gradients 5 % slower)
+  const bool again = __syncthreads_or(contract(std::true_type{}, std::false_type{}));
+  if (again | (a.K < kWholeBelow)) contract(std::false_type{}, std::true_type{});
 
   if constexpr (SUMS) {
     // the units of a row lie with eight threads, 4 k each: their sums are added in order of k (the loop's last barrier is

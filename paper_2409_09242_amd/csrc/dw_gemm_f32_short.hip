@@ -149,7 +149,7 @@ __global__ __launch_bounds__(NW * 64) void short_gemm_f32(GemmArgs a) {
     }
     return !finite;
   };
-  if (__syncthreads_or(contract(std::false_type{}))) contract(std::true_type{});       // (see dw_f32_pieces.h)
+  if (K < kWholeBelow || __syncthreads_or(contract(std::false_type{}))) contract(std::true_type{});    // (see dw_f32_pieces.h)
 
   // partial tiles: [wave][C, RC][32][32]; lane holds column l32, rows (r/4)*8 + lhalf*4 + r%4
   extern __shared__ __attribute__((aligned(16))) float part[];

@@ -65,3 +65,41 @@ def test_tiny_gradients_follow_the_oracle(dims, batch, k):
         g[below] *= up; ref[below] *= up
         close_layers(g, ref, dims, RTOL_GRAD, "g[%d]" % i)
         close_layers(h.get_state(B.DW_S_HZ, i), tr.traces[i].hz, dims, RTOL_HV, "hz[%d]" % i)
+
+
+@pytest.mark.parametrize("dims", [(260, 68, 132, 10), (260, 516, 260, 10)])
+def test_a_single_product_is_rounded_once(dims):
+    """One sample: gW_l = d_l a_{l-1}^T is one product an entry, and HzW_1 = Rd_1 x^T too (the input has no derivative).
+    d_l and Rd_l are the bias gradients then, so every entry is known to the bit."""
+    w, theta0, x, y = _problem(dims, 1, 2, 84)
+    h = _step(w, theta0, x, y)
+    offs, _ = O.layer_offsets(dims)
+    for i in range(2):
+        g, hz = h.get_state(B.DW_S_G, i), h.get_state(B.DW_S_HZ, i)
+        for l, (wo, bo) in enumerate(offs, start=1):
+            a = x[i, 0] if l == 1 else h.get_state(B.DW_S_ACT + l - 1, i).reshape(-1)
+            np.testing.assert_array_equal(g[wo:bo], np.outer(g[bo:bo + dims[l]], a).reshape(-1))
+            if l == 1:
+                np.testing.assert_array_equal(hz[wo:bo], np.outer(hz[bo:bo + dims[l]], a).reshape(-1))
+
+
+@pytest.mark.parametrize("classes", [2, 3, 4])
+def test_the_data_gradient_through_few_classes_is_as_close_as_fp32_sums(classes):
+    """One sample: d_1 = d_L W_2 is a sum of `classes` products, d_L and d_1 are the bias gradients.  A chain of K fp32
+    multiply-adds is off by at most 2^-24 at each of its K steps; in the 2-norm the library is no further off than
+    such a chain computed here."""
+    dims = (260, 2052, classes)
+    w, theta0, x, y = _problem(dims, 1, 3, 85)
+    h = _step(w, theta0, x, y)
+    (_, b1), (w2, b2) = O.layer_offsets(dims)[0]
+    W2 = theta0[w2:b2].reshape(classes, dims[1])
+    for i in range(3):
+        g, on = h.get_state(B.DW_S_G, i), h.get_state(B.DW_S_ACT + 1, i).reshape(-1) > 0
+        p = g[b2:b2 + classes, None].astype(np.float64) * W2
+        want = np.where(on, p.sum(0), 0.0)
+        err = np.abs(g[b1:b1 + dims[1]] - want)
+        assert np.all(err <= 1.001 * classes * 2.0 ** -24 * np.abs(p).sum(0)), (err / np.abs(p).sum(0)).max()
+        chain = np.zeros(dims[1], dtype=np.float32)
+        for q in p:
+            chain = (chain + q).astype(np.float32)
+        assert np.linalg.norm(err) <= 1.02 * np.linalg.norm(np.where(on, chain, 0.0) - want)     # (2 %: 1000 roundings)

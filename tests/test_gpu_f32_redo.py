@@ -104,7 +104,9 @@ def test_huge_gradients_follow_the_64_bit_network(dims, batch, k):
 
 def test_a_fused_weight_gradient_with_an_infinity_updates_as_the_unfused_one():
     """The first moment after one step is (1 - beta1) g: the fused tiles and the tiles that store g agree on where it is
-    NaN and, elsewhere, to the rounding of sums of 64 products in the two kernels' orders."""
+    NaN and elsewhere to rounding.  The tiles differ in size, so an entry may be in pieces on one side and on the fp32
+    instruction on the other: each is within 64 * 2^-24 of the sum of its 64 products' sizes, which is about five times
+    the layer's rms (64 against sqrt(64), and 0.64 for the mean size of a product of normal numbers): 2 * 64 * 2^-24 * 5."""
     dims, batch, k = (1024, 1024, 1024, 10), 64, 8
     w, theta0, x, y = _inputs(dims, batch, k, 88)
     x[2, 11, 700] = np.inf; x[5, 63, 1023] = np.nan
@@ -122,7 +124,7 @@ def test_a_fused_weight_gradient_with_an_infinity_updates_as_the_unfused_one():
             np.testing.assert_array_equal(nan[:offs[0][1]].reshape(1024, 1024).nonzero()[1], 700)
         for w0, b0 in offs:
             a, b, ok = m[1][i][w0:b0], m[0][i][w0:b0], ~nan[w0:b0]
-            close(a[ok], b[ok], 1e-6, "redo fused m[%d]/W" % i)
+            close(a[ok], b[ok], 2 * 64 * 2.0 ** -24 * 5, "redo fused m[%d]/W" % i)
 
 
 def _smooth_cnn(spec, batch, k, seed):
