@@ -63,16 +63,16 @@ hipError_t launch_head(const HeadArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// a wave per worker: every lane adds the slots 64 apart, then the lanes in a fixed tree
+// a wave per worker: every lane adds the slots 64 apart, then the lanes in a fixed tree, in 64 bits
 __global__ __launch_bounds__(64) void loss_sum_kernel(const float* loss_part, int n_slots, float* loss, int B,
                                                       uint64_t active_mask) {
   const int i = blockIdx.x;
   if (!((active_mask >> i) & 1ull)) return;
-  float t = 0.f;
-  for (int b = threadIdx.x; b < n_slots; b += 64) t += loss_part[(int64_t)i * n_slots + b];
+  double t = 0.0;
+  for (int b = threadIdx.x; b < n_slots; b += 64) t += (double)loss_part[(int64_t)i * n_slots + b];
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off);
-  if (threadIdx.x == 0) loss[i] = t / (float)B;
+  if (threadIdx.x == 0) loss[i] = (float)(t / (double)B);
 }
 
 hipError_t launch_loss_sum(const float* loss_part, int n_slots, const HeadArgs& h, hipStream_t s) {

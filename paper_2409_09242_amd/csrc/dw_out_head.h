@@ -47,10 +47,10 @@ __device__ __forceinline__ void out_head_rows(const float (&part)[NW][2][DW_MAX_
   if (n == 0) row_loss[m] = row < a.M ? lrow : 0.f;
   __syncthreads();
   if (tid == 0) {
-    float t = 0.f;
+    double t = 0.0;                                       // (16 sums in fp32 would be off by a last bit or two)
 #pragma unroll
-    for (int r = 0; r < DW_MAX_CLASSES; ++r) t += row_loss[r];
-    loss_part[(int64_t)worker * gridDim.x + blockIdx.x] = t;
+    for (int r = 0; r < DW_MAX_CLASSES; ++r) t += (double)row_loss[r];
+    loss_part[(int64_t)worker * gridDim.x + blockIdx.x] = (float)t;
   }
 }
 
