@@ -150,7 +150,8 @@ int validate(const dw_config* c, Layout* lay) {
       lay->rdelta[l] = take((size_t)k * B * c->dims[l] * es);
     }
     const size_t head = (size_t)k * B * DW_MAX_CLASSES * sizeof(float);
-    lay->sL = take(head); lay->rsL = take(head); lay->dL = take(head); lay->rdL = take(head);
+    lay->sL = take(head); lay->dL = take(head); lay->rdL = take(head);
+    lay->rsL = c->dtype == DW_BF16 && L == 1 ? take(head) : lay->sL;
     if (c->dtype == DW_BF16) { lay->dL16 = take(head / 2); lay->rdL16 = take(head / 2); }
   }
   size_t part = 0, part_b = 0;                       // scratch of products whose contraction is cut into slices
@@ -183,12 +184,12 @@ int validate(const dw_config* c, Layout* lay) {
   }
   if (L > 0 && c->dtype == DW_F32) {
     // fp32 forward products of hidden layers with a long contraction and a handful of output tiles (the first linear
-    // layer behind a convolutional front end): same cut, slices of at least 64
+    // layer behind a convolutional front end) that the small-model kernel does not take: same cut, slices of at least 64
     const int64_t B = c->batch;
     for (int l = 1; l < L; ++l) {
       const int64_t n = c->dims[l], kk = c->dims[l - 1];
       const int64_t tiles = n <= 32 ? (B + 127) / 128 : B <= 32 ? (n + 127) / 128 : ((B + 63) / 64) * ((n + 63) / 64);
-      int64_t split = tiles * k < 256 ? 1024 / (tiles * k) : 1;
+      int64_t split = tiles * k < 256 && !gemm_f32_short_shape(B, n, kk, k) ? 1024 / (tiles * k) : 1;
       if (split > kk / 64) split = kk / 64;
       if (split > 64) split = 64;
       lay->fwdSplit[l - 1] = (int)(split < 1 ? 1 : split);

@@ -210,6 +210,11 @@ static hipError_t launch(const GemmArgs& a, hipStream_t s) {
 
 }  // namespace f32s
 
+// a forward product of M x N outputs and contraction K for each of k workers (the layout asks as well: such a product needs no slices)
+bool gemm_f32_short_shape(int64_t M, int64_t N, int64_t K, int k) {
+  return K <= 4096 && ((M + 63) / 64) * ((N + 63) / 64) * k < 256;
+}
+
 // Forward product, or data gradient through a layer of at most 32 outputs (the classes), of matrices in memory, no slices,
 // whose 64 x 64 tiles over all workers would leave compute units idle.  Longer data gradients stay with the tiles: their
 // k-major operand comes in 4-byte loads here (512 -> 512: 24 us against 11.7 + 6.0).  (Whichever workers are active: the
@@ -217,8 +222,7 @@ static hipError_t launch(const GemmArgs& a, hipStream_t s) {
 bool gemm_f32_short_ok(const GemmArgs& a) {
   if (a.x_view != VIEW_NONE || a.y_view != VIEW_NONE || a.ksplit > 1 || !(a.ry_bits || a.plain)) return false;
   if (a.epi == EPI_MASK ? a.K > f32s::kStep || (!a.plain && !a.RX) : a.epi != EPI_RELU) return false;
-  if (a.K > 4096) return false;
-  return (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) * a.k < 256;
+  return gemm_f32_short_shape(a.M, a.N, a.K, a.k);
 }
 
 template <int NW>

@@ -233,6 +233,7 @@ struct LdsLimitOnce {
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s);
 bool gemm_f32_short_ok(const GemmArgs& a);                       // small-model kernel usable and meant for this product?
+bool gemm_f32_short_shape(int64_t M, int64_t N, int64_t K, int k);   // the part of the answer that a forward product's sizes give
 hipError_t launch_gemm_f32_short(const GemmArgs& a, hipStream_t s);
 // can the bf16 weight-gradient kernel of a layer W[n_out][n_in] (bit/parameter offset woff) apply the update itself,
 // and how many partial-sum slots (tiles) does it then write per worker when a step has n_samples Hutchinson probes?
@@ -270,7 +271,9 @@ struct Layout {            // byte offsets into the workspace, all multiples of 
   size_t theta = 0, m = 0, v = 0, g = 0, hz = 0, centre = 0, wb16 = 0, zbits = 0;
   size_t act[DW_MAX_LAYERS] = {0}, ract[DW_MAX_LAYERS] = {0};   // a_l, Ra_l for l = 1..L-1 (index l)
   size_t delta[DW_MAX_LAYERS] = {0}, rdelta[DW_MAX_LAYERS] = {0}; // d_l, Rd_l of the hidden layers l = 1..L-1 (index l)
-  size_t sL = 0, rsL = 0, dL = 0, rdL = 0, dL16 = 0, rdL16 = 0;  // output layer, fp32 [k][B][16] (+ bf16 copies)
+  // output layer, fp32 [k][B][16] (+ bf16 copies); sL is the output-layer kernels' scratch for partial losses, and with rsL holds
+  // the logits of a bf16 model without hidden layers (the only one with a head in a launch of its own)
+  size_t sL = 0, rsL = 0, dL = 0, rdL = 0, dL16 = 0, rdL16 = 0;
   size_t zbits_t = 0;                 // [k][z_stride] words: z with the W-parts of the layers in zt_layer transposed
   bool zt_layer[DW_MAX_LAYERS] = {false};   // index l-1: the data gradient through W_l reads the transposed bits
   size_t dacc = 0;                    // [k][Pp] floats, n_samples > 1 only: sum over the probes of z_j*Hz_j
