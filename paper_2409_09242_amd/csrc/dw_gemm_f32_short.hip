@@ -210,9 +210,17 @@ static hipError_t launch(const GemmArgs& a, hipStream_t s) {
 
 }  // namespace f32s
 
-// a forward product of M x N outputs and contraction K for each of k workers (the layout asks as well: such a product needs no slices)
+// A forward product of M x N outputs and contraction K for each of k workers (the layout asks as well: such a product needs no
+// slices).  Against the 64 x 64 tiles, in slices where there are few of them:
+//   K      whole step, models K-N-10 with one to eight workers, few tiles: up to 784 faster here (784-512-10, four workers of 128
+//          samples: 76 us against 82); at 1024 even (1024-512-10: 81 / 90, 1024-64-10, one worker: 66 / 68, 1024-32-10, two of 200: 72 /
+//          69); from there on the one block per tile walks too long (2048-64-10: the product 30 against 15 us, 4096-64-10 50 against
+//          18, the step 89 against 68)
+//   tiles  up to 128 of them faster or even; from there to 256 even at whole sizes (512-1024-10, three of 256: 108 / 103;
+//          512-640-10, two of 512: 113 / 111) and still faster where the tiles hang over the edge (512-1036-10, five of 93: 101 / 111)
+//          and in first-order steps (69 / 79); more of them fill the chip
 bool gemm_f32_short_shape(int64_t M, int64_t N, int64_t K, int k) {
-  return K <= 4096 && ((M + 63) / 64) * ((N + 63) / 64) * k < 256;
+  return K <= 1024 && ((M + 63) / 64) * ((N + 63) / 64) * k < 256;
 }
 
 // Forward product, or data gradient through a layer of at most 32 outputs (the classes), of matrices in memory, no slices,

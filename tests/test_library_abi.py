@@ -251,19 +251,21 @@ def test_bench_reads_the_traffic_figure_only_for_the_kernel_it_was_measured_on(t
     assert bench.measured_traffic() is not None
 
 
-@pytest.mark.parametrize("dims", [(784, 512, 10), (3072, 256, 132, 7)])
-def test_a_small_fp32_model_has_no_scratch_that_nothing_writes(dims):
-    """Few output tiles: the forward products run without slices of their contraction and the logits stay in the output
-    layer's kernel, so beside parameters, moments, gradients, sign bits and activations there are three arrays of 16 floats a
-    sample, the data gradients' slices (contractions of 128 and more) and the per-worker scalars."""
+@pytest.mark.parametrize("dims", [(784, 512, 10), (1024, 256, 132, 7), (1028, 256, 10), (64, 3072, 64, 10)])
+def test_a_small_fp32_model_has_scratch_for_the_slices_that_are_written(dims):
+    """Few output tiles: forward products with a contraction of at most 1024 run without slices, longer ones in slices of at
+    least 64, data gradients likewise; the logits stay in the output layer's kernel.  So beside parameters, moments, gradients,
+    sign bits and activations there are three arrays of 16 floats a sample, those slices and the per-worker scalars."""
     k, batch = 4, 128
     cfg = B.make_config(dims=dims, k=k, batch=batch)
     P = B.param_count(cfg)
-    slices = 0
-    for n, kk in zip(dims[1:-1], dims[2:]):                   # data gradient: batch x n outputs, contraction kk
+
+    def slice_bytes(n, contraction):                          # a product of batch x n outputs
         tiles = (batch + 63) // 64 * ((n + 63) // 64)
-        cut = max(1, min(1024 // (tiles * k), kk // 64, 64))
-        slices = max(slices, cut * k * 2 * batch * n * 4 if cut > 1 else 0)
+        cut = max(1, min(1024 // (tiles * k), contraction // 64, 64)) if tiles * k < 256 else 1
+        return cut * k * 2 * batch * n * 4 if cut > 1 else 0
+    slices = max([slice_bytes(n, kk) for kk, n in zip(dims[:-2], dims[1:-1]) if kk > 1024] +
+                 [slice_bytes(n, kk) for n, kk in zip(dims[1:-1], dims[2:])])
     params = 5 * k * P * 4 + P * 4 + k * P // 8
     hidden = 4 * k * batch * sum(dims[1:-1]) * 4
     head = 3 * k * batch * 16 * 4
