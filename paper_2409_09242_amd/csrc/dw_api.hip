@@ -198,6 +198,8 @@ int validate(const dw_config* c, Layout* lay) {
         part = need > part ? need : part;
       }
     }
+    const size_t head = out_head_f32_slice_bytes(B, c->dims[L - 1], k);
+    part = head > part ? head : part;
     // and the data gradients through W_l (B x d_{l-1} outputs, contraction d_l) of the same kind
     for (int l = 2; l <= L; ++l) {
       const int64_t n = c->dims[l - 1], kk = c->dims[l];

@@ -258,9 +258,11 @@ struct HeadArgs {                     // softmax cross-entropy on the output lay
 };
 hipError_t launch_head(const HeadArgs& a, hipStream_t s);
 // fp32 output layer and head in one kernel (dw_out_head_f32.hip): `a` as for the output layer's forward product
-// (its C and RC are not written), loss_part: k * ceil(M / 16) floats of scratch
+// (its C and RC are not written), loss_part: k * ceil(M / 16) floats of scratch, slices: out_head_f32_slice_bytes of it
 bool out_head_f32_ok(const GemmArgs& a);
-hipError_t launch_out_head_f32(const GemmArgs& a, const HeadArgs& h, float* loss_part, hipStream_t s);
+int out_head_f32_slices(int64_t M, int64_t K, int k);
+size_t out_head_f32_slice_bytes(int64_t M, int64_t K, int k);
+hipError_t launch_out_head_f32(const GemmArgs& a, const HeadArgs& h, float* loss_part, float* slices, hipStream_t s);
 // the same in bf16 (dw_gemm_bf16_out.hip)
 bool out_head_bf16_ok(const GemmArgs& a);
 hipError_t launch_out_head_bf16(const GemmArgs& a, const HeadArgs& h, float* loss_part, hipStream_t s);

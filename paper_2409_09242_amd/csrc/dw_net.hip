@@ -153,7 +153,7 @@ int run_network(const dw_config& cfg, char* ws, const Layout& lay, const void* d
       if (!out_head_f32_ok(a)) return DW_ERR_CONFIG;   // (every configuration that was accepted passes)
       // the output layer's product and the softmax head in one kernel (the logits buffer serves as its scratch for the
       // per-block losses)
-      if ((e = launch_out_head_f32(a, hd, reinterpret_cast<float*>(ws + lay.sL), s)) != hipSuccess) return DW_ERR_HIP;
+      if ((e = launch_out_head_f32(a, hd, reinterpret_cast<float*>(ws + lay.sL), reinterpret_cast<float*>(ws + lay.cPart), s)) != hipSuccess) return DW_ERR_HIP;
       head_done = true;
       break;
     }

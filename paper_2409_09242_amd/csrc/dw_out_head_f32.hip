@@ -8,6 +8,10 @@
 // are added in wave order through LDS.  A 16-lane group then holds one sample's 16 logits, gathers them by shuffles
 // and runs the head's arithmetic on them.  The loss of the block's samples goes to one slot per (worker, block);
 // loss_sum_kernel adds a worker's slots in index order when the caller wants the loss.
+//
+// Few samples and a long contraction leave a handful of blocks walking all of it.  There the contraction is cut into slices
+// over the grid, whose partial logits go to scratch, and a second launch adds them in order and runs the head
+// (out_head_f32_slices).
 #include "dw_out_head.h"
 
 namespace dw {
@@ -19,14 +23,20 @@ namespace f32o {
 constexpr int ROWS = 16, NT = 256, NW = NT / 64, KSTEP = 16;
 static_assert(DW_MAX_CLASSES == ROWS, "a 16-lane group holds one sample's logits, one class per lane");
 
-// grid: (ceil(M / 16), active workers); requirements in out_head_f32_ok
-__global__ __launch_bounds__(NT) void out_head_f32_kernel(GemmArgs a, HeadArgs h, float* loss_part) {
+// grid: (ceil(M / 16), active workers, slices of the contraction); requirements in out_head_f32_ok.  SLICED: partial logits to
+// slices[slice][worker][block][S, RS][sample][class]
+template <bool SLICED>
+__global__ __launch_bounds__(NT) void out_head_f32_kernel(GemmArgs a, HeadArgs h, float* loss_part, float* slices) {
   const int worker = nth_active_worker(a.active_mask, blockIdx.y);
   const int row0 = blockIdx.x * ROWS;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, kg = lane >> 4;               // operand row (A) or column (W), and which 4 of the 16 k
-  const int kspan = (a.K + NW * KSTEP - 1) / (NW * KSTEP) * KSTEP;    // this wave's share of the contraction
-  const int kbeg = wave * kspan, kend = kbeg + kspan < a.K ? kbeg + kspan : a.K;
+  // the slice (whole groups of 64 but for the last one's end) and this wave's share of it
+  const int klen = SLICED ? ((a.K + gridDim.z - 1) / gridDim.z + NW * KSTEP - 1) / (NW * KSTEP) * (NW * KSTEP) : a.K;
+  const int k0s = SLICED ? ((int)blockIdx.z * klen < a.K ? (int)blockIdx.z * klen : a.K) : 0;    // (rounding up may leave none for the last)
+  const int k1s = SLICED && k0s + klen < a.K ? k0s + klen : a.K;
+  const int kspan = (k1s - k0s + NW * KSTEP - 1) / (NW * KSTEP) * KSTEP;
+  const int kbeg = k0s + wave * kspan, kend = kbeg + kspan < k1s ? kbeg + kspan : k1s;
   const int arow = row0 + r16 < a.M ? row0 + r16 : a.M - 1;   // rows past the end repeat the last one (never stored)
 
   const float* X = reinterpret_cast<const float*>(a.X) + (int64_t)worker * a.x_wstride + (int64_t)arow * a.ldx;
@@ -42,7 +52,7 @@ __global__ __launch_bounds__(NT) void out_head_f32_kernel(GemmArgs a, HeadArgs h
   f32o_x4 acc = {0.f, 0.f, 0.f, 0.f}, racc = {0.f, 0.f, 0.f, 0.f};
 
   const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (a.K % (NW * KSTEP) == 0) {                           // (512 wide: 12 us, the form below 15)
+  if ((k1s - k0s) % (NW * KSTEP) == 0) {                   // (512 wide: 12 us, the form below 15)
     for (int k0 = kbeg; k0 < kbeg + kspan; k0 += KSTEP) {
       const float4 x4 = *reinterpret_cast<const float4*>(X + k0 + kg * 4);
       const float4 rx4 = has_rx ? *reinterpret_cast<const float4*>(RX + k0 + kg * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -102,10 +112,50 @@ __global__ __launch_bounds__(NT) void out_head_f32_kernel(GemmArgs a, HeadArgs h
     part[wave][1][kg * 4 + r][r16] = racc[r];
   }
   __syncthreads();
-  out_head_rows<NW>(part, a, h, loss_part, worker, row0, zb);
+  if (SLICED) {
+    const int m = tid >> 4, n = tid & 15;
+    float s = 0.f, rs = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) { s += part[w][0][m][n]; rs += part[w][1][m][n]; }
+    float* out = slices + (((int64_t)blockIdx.z * a.k + worker) * gridDim.x + blockIdx.x) * (2 * NT);
+    out[tid] = s;
+    out[NT + tid] = rs;
+  } else {
+    out_head_rows<NW>(part, a, h, loss_part, worker, row0, zb);
+  }
+}
+
+// the slices of a block's logits in order, then the head
+__global__ __launch_bounds__(NT) void out_head_slices_kernel(GemmArgs a, HeadArgs h, float* loss_part, const float* slices, int n_slices) {
+  const int worker = nth_active_worker(a.active_mask, blockIdx.y);
+  const int tid = threadIdx.x;
+  __shared__ float part[1][2][ROWS][ROWS + 1];
+  const float* in = slices + ((int64_t)worker * gridDim.x + blockIdx.x) * (2 * NT) + tid;
+  const int64_t step = (int64_t)a.k * gridDim.x * (2 * NT);
+  float s = 0.f, rs = 0.f;
+#pragma unroll 8
+  for (int i = 0; i < n_slices; ++i) { s += in[i * step]; rs += in[i * step + NT]; }
+  part[0][0][tid >> 4][tid & 15] = s;
+  part[0][1][tid >> 4][tid & 15] = rs;
+  __syncthreads();
+  out_head_rows<1>(part, a, h, loss_part, worker, blockIdx.x * ROWS, a.zbits + (int64_t)worker * a.z_stride);
 }
 
 }  // namespace f32o
+
+// Slices of an output layer's contraction K for k workers of M samples: enough for 512 blocks, each at least 512 long; 1: none.
+// Measured without hidden layers, whole and cut: 64 samples, one worker: 2048 wide 26 and 15 us, 8196 wide 81 and 17 (512 wide 13
+// whole); 256 blocks in two slices each: 2048 wide 27 and 24 us, 8196 wide 82 and 59.  More blocks than that are not cut.
+int out_head_f32_slices(int64_t M, int64_t K, int k) {
+  const int64_t blocks = (M + f32o::ROWS - 1) / f32o::ROWS * k;
+  if (K < 2048 || blocks > 256) return 1;
+  const int64_t fill = 512 / blocks, most = K / 512;
+  return (int)(fill < most ? fill : most);
+}
+size_t out_head_f32_slice_bytes(int64_t M, int64_t K, int k) {
+  const int s = out_head_f32_slices(M, K, k);
+  return s > 1 ? (size_t)s * k * ((M + f32o::ROWS - 1) / f32o::ROWS) * (2 * f32o::NT) * sizeof(float) : 0;
+}
 
 // the fp32 output layer's forward product (linear epilogue, at most 16 columns) with operands that 16-byte loads can
 // address and sign bits that come four to a word
@@ -120,12 +170,19 @@ bool out_head_f32_ok(const GemmArgs& a) {
   return true;
 }
 
-// loss_part: at least k * ceil(M / 16) floats; h.loss may be nullptr (then the slots are not added up)
-hipError_t launch_out_head_f32(const GemmArgs& a, const HeadArgs& h, float* loss_part, hipStream_t s) {
+// loss_part: at least k * ceil(M / 16) floats; h.loss may be nullptr (then the slots are not added up); slices: scratch of
+// out_head_f32_slice_bytes
+hipError_t launch_out_head_f32(const GemmArgs& a, const HeadArgs& h, float* loss_part, float* slices, hipStream_t s) {
   KernelScope ks(KC_HEAD, s);
   const int n_slots = (a.M + f32o::ROWS - 1) / f32o::ROWS;
   const dim3 grid((unsigned)n_slots, (unsigned)active_count(a.active_mask, a.k));
-  hipLaunchKernelGGL(f32o::out_head_f32_kernel, grid, dim3(f32o::NT), 0, s, a, h, loss_part);
+  const int n_slices = out_head_f32_slices(a.M, a.K, a.k);
+  if (n_slices > 1) {
+    hipLaunchKernelGGL(f32o::out_head_f32_kernel<true>, dim3(grid.x, grid.y, (unsigned)n_slices), dim3(f32o::NT), 0, s, a, h, loss_part, slices);
+    hipLaunchKernelGGL(f32o::out_head_slices_kernel, grid, dim3(f32o::NT), 0, s, a, h, loss_part, slices, n_slices);
+  } else {
+    hipLaunchKernelGGL(f32o::out_head_f32_kernel<false>, grid, dim3(f32o::NT), 0, s, a, h, loss_part, slices);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !h.loss) return e;
   return launch_loss_sum(loss_part, n_slots, h, s);
