@@ -334,16 +334,17 @@ hipError_t launch_weights(const WeightArgs& a, hipStream_t s) {
 // with four float4 per lane, one worker at a time 5.46; one float4 per lane in blocks of 256 threads 5.4 to 5.5.  This kernel: 2.53 -> 2.40 ms; 1.2e6 parameters, seven workers: 15.4 -> 10.5 us.
 // FUSED_W: a model with few partial sums computes the weights inside the pull (every block for itself, in the same
 // order, so all blocks pull with the same values; block 0 records them): one launch per round instead of two.
-constexpr int kPullThreads = 64, kPullBatch = 4;
-template <bool HAS_B16, bool FUSED_W>
-__global__ __launch_bounds__(kPullThreads) void pull_kernel(PullArgs a, WeightArgs wa) {
+// NT: 64, or one block of 1024 for the whole of a small model of few workers (launch_weights_and_pull).
+constexpr int kPullThreads = 64, kPullBatch = 4, kPullOne = 1024;
+template <bool HAS_B16, bool FUSED_W, int NT>
+__global__ __launch_bounds__(NT) void pull_kernel(PullArgs a, WeightArgs wa) {
   __shared__ float s_omh1[DW_MAX_K], s_h2[DW_MAX_K];
   const int lane = threadIdx.x;
-  const int64_t q = (int64_t)blockIdx.x * kPullThreads + lane;
+  const int64_t q = (int64_t)blockIdx.x * NT + lane;
   const bool valid = q < (a.Pp >> 2);
   float4 cen = valid ? reinterpret_cast<const float4*>(a.centre)[q] : make_float4(0.f, 0.f, 0.f, 0.f);
   if (FUSED_W) {
-    static_assert(kPullThreads >= DW_MAX_K, "a lane per worker");
+    static_assert(NT >= DW_MAX_K, "a lane per worker");
     double S = 0.0;                                        // lane i: the squared distance of worker i
     if (lane < wa.k) {
       const double* part = wa.partials + (int64_t)lane * wa.n_blocks;
@@ -418,9 +419,9 @@ hipError_t launch_pull(const PullArgs& a, hipStream_t s) {
   KernelScope ks(KC_PULL, s);
   WeightArgs none{};
   if (a.wb16)
-    hipLaunchKernelGGL((pull_kernel<true, false>), dim3(pull_blocks(a)), dim3(kPullThreads), 0, s, a, none);
+    hipLaunchKernelGGL((pull_kernel<true, false, kPullThreads>), dim3(pull_blocks(a)), dim3(kPullThreads), 0, s, a, none);
   else
-    hipLaunchKernelGGL((pull_kernel<false, false>), dim3(pull_blocks(a)), dim3(kPullThreads), 0, s, a, none);
+    hipLaunchKernelGGL((pull_kernel<false, false, kPullThreads>), dim3(pull_blocks(a)), dim3(kPullThreads), 0, s, a, none);
   return hipGetLastError();
 }
 
@@ -432,10 +433,19 @@ bool sync_fusable(const WeightArgs& w, const PullArgs& p) {
 
 hipError_t launch_weights_and_pull(const WeightArgs& w, const PullArgs& a, hipStream_t s) {
   KernelScope ks(KC_PULL, s);
-  if (a.wb16)
-    hipLaunchKernelGGL((pull_kernel<true, true>), dim3(pull_blocks(a)), dim3(kPullThreads), 0, s, a, w);
-  else
-    hipLaunchKernelGGL((pull_kernel<false, true>), dim3(pull_blocks(a)), dim3(kPullThreads), 0, s, a, w);
+  auto launch = [&](auto b16, auto threads, unsigned blocks) {
+    hipLaunchKernelGGL((pull_kernel<decltype(b16)::value, true, decltype(threads)::value>), dim3(blocks), dim3(decltype(threads)::value), 0, s, a, w);
+  };
+  using One = std::integral_constant<int, kPullOne>;
+  using Many = std::integral_constant<int, kPullThreads>;
+  // One block where it holds the model and up to three workers: the block of a worker's step and that of the round then share an
+  // L2, and what the one wrote the other need not fetch from memory (32-64-10, step and round, one block / blocks of 64: one worker
+  // 22.6 / 24.2 us, two at 28-32-10 20.5 / 21.1, four 24.8 / 24.7, sixteen 28.3 / 27.4).
+  if (a.Pp <= 4 * kPullOne && a.k < 4) {
+    if (a.wb16) launch(std::true_type{}, One{}, 1u); else launch(std::false_type{}, One{}, 1u);
+  } else {
+    if (a.wb16) launch(std::true_type{}, Many{}, pull_blocks(a)); else launch(std::false_type{}, Many{}, pull_blocks(a));
+  }
   return hipGetLastError();
 }
 
