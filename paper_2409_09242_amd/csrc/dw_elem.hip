@@ -289,21 +289,23 @@ __device__ __forceinline__ void weight_scalars(const WeightArgs& a, int i, doubl
   }
 }
 
-// A large model has 1e5 partial sums per worker and one block to add them: four loads of every thread in flight
-// (1e8 parameters: 18 us against 33 us for 256 threads with one, at a quarter of the partial sums).
-constexpr int kWeightThreads = 1024;
+// A large model has 1e5 partial sums per worker and one block to add them: eight loads of every thread in flight, the last ones
+// too (four, and the last ones by themselves: 4e6 parameters 7.0 us with the profiler's events, now 6.4; 1e8 parameters, a quarter
+// of the partial sums, 256 threads with one load 32 us, now 19).
+constexpr int kWeightThreads = 1024, kInFlight = 8;
 __global__ __launch_bounds__(kWeightThreads) void weight_kernel(WeightArgs a) {
   const int i = blockIdx.x;
   const int tid = threadIdx.x;
   __shared__ double red[kWeightThreads / 64];
   auto sum_of = [&](const double* p, int n) {
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int b = tid;
-    for (; b + 3 * kWeightThreads < n; b += 4 * kWeightThreads) {
-      s0 += p[b]; s1 += p[b + kWeightThreads]; s2 += p[b + 2 * kWeightThreads]; s3 += p[b + 3 * kWeightThreads];
+    double s = 0.0;
+    for (int b = tid; b < n; b += kInFlight * kWeightThreads) {
+      double v[kInFlight];
+#pragma unroll
+      for (int j = 0; j < kInFlight; ++j) v[j] = b + j * kWeightThreads < n ? p[b + j * kWeightThreads] : 0.0;
+      s += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
     }
-    for (; b < n; b += kWeightThreads) s0 += p[b];
-    return (s0 + s1) + (s2 + s3);
+    return s;
   };
   double s = sum_of(a.partials + (int64_t)i * a.n_blocks, a.n_blocks);
   if (a.n_blocks_f > 0) s += sum_of(a.partials_f + (int64_t)i * a.n_blocks_f, a.n_blocks_f);

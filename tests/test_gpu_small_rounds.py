@@ -1,4 +1,5 @@
-"""The round of a small model around the sizes where it runs in one block: up to 4096 parameters and three workers."""
+"""The round of a small model around the sizes where it runs in one block, up to 4096 parameters and three workers; the sum of a large
+model's distances around the number of partial sums that are loaded together."""
 import numpy as np
 import pytest
 import torch
@@ -50,3 +51,20 @@ def test_the_bf16_weights_follow_the_round(k):
     a.worker_step(x, y); b.worker_step(x, y)
     for i in range(k):
         np.testing.assert_array_equal(a.get_state(B.DW_S_ACT + 1, i), b.get_state(B.DW_S_ACT + 1, i))
+
+
+@pytest.mark.parametrize("P", [66 << 10, (1 << 20) + 4, 1 << 23, (1 << 23) + 4])
+def test_the_distance_of_many_partial_sums(P):
+    """72, 1032, 8192 (one load of each thread's eight) and 8200 partial sums of 1024 parameters each: u is the logarithm of the
+    distance, which fp32 squares of the stored parameters give to 2^-23."""
+    rng = W.rng_for(93, 23)
+    theta0 = rng.uniform(-0.01, 0.01, size=P).astype(np.float32)
+    cfg = B.make_config(dims=None, n_params=P, k=2, optimizer=B.DW_OPT_SGD, lr=0.1)
+    h = B.Handle(cfg, theta0)
+    g = torch.randn((2, P), generator=torch.Generator(device="cuda").manual_seed(93), device="cuda")
+    h.update_only(g, None)
+    theta = [h.get_state(B.DW_S_THETA, i).astype(np.float64) for i in range(2)]
+    assert h.elastic_sync(B.DW_FIXED, tau=1)
+    for i in range(2):
+        want = np.log(np.linalg.norm(theta[i] - theta0.astype(np.float64)))
+        assert abs(h.get_state(B.DW_S_SCORE, i)[0] - want) < 1e-6
