@@ -6,7 +6,7 @@ import torch
 from oracle import dw_oracle as O
 from paper_2409_09242_amd import binding as B
 from paper_2409_09242_amd import workloads as W
-from parity import RTOL_GRAD, RTOL_HV, close_layers, oracle_config
+from parity import RTOL_GRAD, RTOL_HV, TIE_BAND, bound_ties, check_hidden, close_layers, gpu_hidden, oracle_config, slopes_of
 
 pytestmark = pytest.mark.gpu
 
@@ -26,16 +26,22 @@ def _inputs(dims, batch, k, seed):
 
 
 @pytest.mark.parametrize("dims,batch,k", [
-    ((260, 68, 132, 10), 65, 2),         # one row, four columns past a 64 x 64 tile; contractions 4 past a tile of 32 k
+    ((260, 68, 132, 10), 65, 2),         # gradients one row, four columns past a 64 x 64 tile, the data gradient in two slices; forward
+                                         # products in the small-model kernel, 4 past a step of 32 k
     ((132, 192, 64, 3), 31, 3),          # minibatch shorter than a tile of 32 k
-    ((1280, 256, 128, 16), 128, 2),      # whole tiles, contraction past ten chains of 128 k
+    ((1280, 256, 128, 16), 128, 2),      # whole tiles, the first forward product in slices
+    ((132, 1028, 1036, 7), 193, 4),      # every hidden product in 64 x 64 tiles (272 of them): ragged rows, columns and last k-tile, with
+                                         # and without the input's derivative
 ])
 def test_tile_and_chain_edges_follow_the_oracle(dims, batch, k):
     print("pieces", dims, batch, k, flush=True)
     theta0, x, y = _inputs(dims, batch, k, 77)
     w, h, loss = _step(dims, batch, k, theta0, x, y)
     tr = O.OracleTrainer(oracle_config(w), theta0.astype(np.float64))
-    tr.worker_step(x, y)
+    hidden = gpu_hidden(h, w)                                  # (a unit within rounding of its kink may be on either side)
+    tr.worker_step(x, y, tie_band=TIE_BAND, tie_choice=slopes_of(hidden))
+    check_hidden(hidden, {i: tr.traces[i] for i in range(k)}, False, "pieces")
+    bound_ties(False)
     for i in range(k):
         close_layers(h.get_state(B.DW_S_G, i), tr.traces[i].g, dims, RTOL_GRAD, "g[%d]" % i)
         close_layers(h.get_state(B.DW_S_HZ, i), tr.traces[i].hz, dims, RTOL_HV, "hz[%d]" % i)
@@ -56,7 +62,7 @@ def test_scaled_weights_scale_the_products_exactly(scale):
 
 @pytest.mark.parametrize("dims,batch", [((256, 96, 68, 10), 64), ((256, 96, 32, 10), 130)])
 def test_infinities_stay_infinite_and_nans_stay_nans(dims, batch):
-    """One input entry is inf: the units of the first layer are +-inf there, by the sign of their weight, and the
+    """The small-model kernel (the tiles: test_gpu_f32_redo.py).  One input entry is inf: the units of the first layer are +-inf there, by the sign of their weight, and the
     activation is inf or 0, as any fp32 sum gives it; a NaN input makes the sample's pre-activations NaN, which the
     ReLU's comparison turns into 0.  Other samples of the block are computed again on another instruction, so both are
     sums of the same K products in some order: within 2 K 2^-24 sum |x w| of each other."""
@@ -81,9 +87,10 @@ def test_infinities_stay_infinite_and_nans_stay_nans(dims, batch):
 
 @pytest.mark.parametrize("opt", [B.DW_OPT_SGD, B.DW_OPT_MOMENTUM])
 @pytest.mark.parametrize("dims,batch,k", [
-    ((260, 68, 132, 10), 65, 2),         # every forward product in the small-model kernel, contraction past a step of 32 k
+    ((260, 68, 132, 10), 65, 2),         # every forward product in the small-model kernel, contraction past a step of 32 k; data
+                                         # gradient in two slices
     ((64, 36, 4), 5, 1),                 # contractions of at most two steps
-    ((132, 1028, 260, 7), 256, 4),       # tiles of 64 x 64, whole and ragged; data gradient in slices
+    ((132, 1028, 260, 7), 256, 4),       # tiles of 64 x 64, whole and ragged
 ])
 def test_first_order_steps_compute_the_plain_products_alone(opt, dims, batch, k):
     print("first order", opt, dims, batch, k, flush=True)
