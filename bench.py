@@ -24,7 +24,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_HBM_GBS = 8000.0            # MI355X HBM3E
-PEAK_TFLOPS = {"f32": 2500.0 / 6, "bf16": 2500.0}   # dense MFMA; an fp32 product takes six bf16 instructions
+PEAK_TFLOPS = 2500.0             # dense bf16 MFMA; fp32 products run there too, see f32_instruction_flops
 PEAK_ALU_F32 = 157.3
 # HBM-side bytes per launch of the fused weight-gradient kernel at configuration 4 come from a counter run
 # (rocprofv3 --pmc FETCH_SIZE, then WRITE_SIZE, scaled by a plain copy kernel of known size); its summary under
@@ -64,6 +64,22 @@ def measured_traffic():
 def class_flops(w):
     """Multiply-add work (flop) per all-worker step for each GEMM class."""
     return {c: v * w.k for c, v in w.gemm_flops_by_class().items()}
+
+
+def f32_instruction_flops(w):
+    """class_flops as the bf16 matrix cores see them in fp32: a product of two matrices takes six bf16 products of their
+    pieces, one with the +-1 direction three.  A layer's forward pass and its data gradient have two of the former (one where
+    the input does not depend on the parameters) and one of the latter, a weight gradient has only the former."""
+    layers = [(w.batch * pos, 9 * ci, co) for (pos, ci, co) in w.conv_stages()]
+    layers += [(w.batch, w.dims[l - 1], w.dims[l]) for l in range(1, len(w.dims))]
+    out = {"gemm_fwd": 0.0, "gemm_wgrad": 0.0, "gemm_dgrad": 0.0}
+    for n, (m, fan_in, fan_out) in enumerate(layers):
+        one = 2.0 * m * fan_in * fan_out * w.k
+        full = 2 if n else 1
+        out["gemm_fwd"] += one * (6 * full + 3)
+        out["gemm_wgrad"] += one * 6 * (full + 1)
+        out["gemm_dgrad"] += one * (6 * full + 3) if n else 0.0
+    return out
 
 
 def fused_layers(w, fuse):
@@ -417,20 +433,24 @@ def main():
     value = w.k * args.steps / elapsed
 
     fl = class_flops(w)
+    ins = dict(fl) if w.bf16 else f32_instruction_flops(w)
     fused = fused_layers(w, not args.no_fuse)
     skipped = 0.0
     if args.samples > 1:
         fl = {c: v * args.samples for c, v in fl.items()}
+        ins = {c: v * args.samples for c, v in ins.items()}
         # the fused launches of the probes before the last leave out the plain product (2 B d_l d_{l-1} flop per worker)
         skipped = sum(2.0 * w.batch * w.dims[l] * w.dims[l - 1] for l in fused) * w.k * (args.samples - 1)
         if "gemm_wgrad" in fl:
             fl["gemm_wgrad"] -= skipped
+            ins["gemm_wgrad"] -= skipped * (1 if w.bf16 else 6)
         # and so do the large forward and data-gradient products of the probes after the first
         fwd_r, dgrad_r = r_only_products(w)
         for cls, layers in (("gemm_fwd", fwd_r), ("gemm_dgrad", dgrad_r)):
             less = sum(2.0 * w.batch * w.dims[l] * w.dims[l - 1] for l in layers) * w.k * (args.samples - 1)
             if cls in fl:
                 fl[cls] -= less
+                ins[cls] -= less * (1 if w.bf16 else 6)
                 skipped += less
     by = class_bytes(w, w.P, w.k, fused, part, args.samples)
     per_step = {"update": 1, "pull": 1.0 / w.tau, "gemm_wgrad": 1, "gather": 1}
@@ -454,6 +474,8 @@ def main():
     mfma = [c for c in fl if c in kernels and not (c == "gemm_wgrad" and fused)]
     gemm_ms = sum(kernels[c]["ms_per_step"] for c in mfma)
     gemm_fl = sum(fl[c] for c in mfma)
+    # fp32: the rate of these products at which the matrix cores would be busy all the time (416 to 555, by their mix)
+    peak_mfma = PEAK_TFLOPS * gemm_fl / sum(ins[c] for c in mfma) if mfma else PEAK_TFLOPS
     dominant = max(kernels, key=lambda c: kernels[c]["ms_per_step"])
     if dominant == "step":
         ach = kernels["step"]["TFLOP/s"]
@@ -464,8 +486,8 @@ def main():
     elif dominant in mfma:
         # one roofline entry for the GEMM family (one kernel template): all its launches of a step together
         ach = gemm_fl / (gemm_ms * 1e-3) / 1e12
-        roof = {"kernel": "dual_gemm (%s)" % dtype, "bound": "mfma", "achieved": ach, "peak": PEAK_TFLOPS[dtype],
-                "unit": "TFLOP/s", "frac": ach / PEAK_TFLOPS[dtype], "traffic": None,
+        roof = {"kernel": "dual_gemm (%s)" % dtype, "bound": "mfma", "achieved": ach, "peak": peak_mfma,
+                "unit": "TFLOP/s", "frac": ach / peak_mfma, "traffic": None,
                 "avg_ms_per_step": gemm_ms, "dominant_class": dominant}
     else:
         ach = kernels[dominant]["GB/s"]
@@ -485,8 +507,8 @@ def main():
     if gemm_ms > 0:
         ach_g = gemm_fl / (gemm_ms * 1e-3) / 1e12
         gemm_roof = {"kernel": "dual_gemm (%s): %s, all launches of a step" % (dtype, " + ".join(mfma)),
-                     "bound": "mfma", "achieved": ach_g, "peak": PEAK_TFLOPS[dtype], "unit": "TFLOP/s",
-                     "frac": ach_g / PEAK_TFLOPS[dtype], "ms_per_step": gemm_ms}
+                     "bound": "mfma", "achieved": ach_g, "peak": peak_mfma, "unit": "TFLOP/s",
+                     "frac": ach_g / peak_mfma, "ms_per_step": gemm_ms}
     del h
     torch.cuda.empty_cache()
 

@@ -230,6 +230,20 @@ def test_transposed_lds_reads_are_not_touched_before_their_wait():
     assert n >= 8 and found == []
 
 
+def test_bench_prices_fp32_products_by_their_bf16_instructions():
+    """Six bf16 instructions a product of two matrices, three with the +-1 direction: a later layer's forward pass and data
+    gradient are two and one of them, its weight gradient three of the former, the first layer's one and one, and two."""
+    import bench
+    w = W.scaled(W.C3, dims=(256, 512, 8), k=2, batch=16)
+    first, second = 2.0 * 16 * 256 * 512 * 2, 2.0 * 16 * 512 * 8 * 2
+    assert bench.f32_instruction_flops(w) == {"gemm_fwd": 9 * first + 15 * second, "gemm_wgrad": 12 * first + 18 * second,
+                                              "gemm_dgrad": 15 * second}
+    for w in (W.C2, W.C3, W.CNN):
+        fl, ins = bench.class_flops(w), bench.f32_instruction_flops(w)
+        assert ins["gemm_wgrad"] == pytest.approx(6 * fl["gemm_wgrad"]) and ins["gemm_dgrad"] == pytest.approx(5 * fl["gemm_dgrad"])
+        assert 4.5 * fl["gemm_fwd"] < ins["gemm_fwd"] < 5 * fl["gemm_fwd"]
+
+
 def test_bench_reads_the_traffic_figure_only_for_the_kernel_it_was_measured_on(tmp_path, monkeypatch):
     """bench.py takes roofline.traffic from the counter summary under profiles/ and drops it (None) as soon as the
     sources of the kernel differ from the digest recorded with the counters."""
