@@ -211,16 +211,17 @@ static hipError_t launch(const GemmArgs& a, hipStream_t s) {
 }  // namespace f32s
 
 // A forward product of M x N outputs and contraction K for each of k workers (the layout asks as well: such a product needs no
-// slices).  Against the 64 x 64 tiles, in slices where there are few of them:
-//   K      whole step, models K-N-10 with one to eight workers, few tiles: up to 784 faster here (784-512-10, four workers of 128
-//          samples: 76 us against 82); at 1024 even (1024-512-10: 81 / 90, 1024-64-10, one worker: 66 / 68, 1024-32-10, two of 200: 72 /
-//          69); from there on the one block per tile walks too long (2048-64-10: the product 30 against 15 us, 4096-64-10 50 against
-//          18, the step 89 against 68)
-//   tiles  up to 128 of them faster or even; from there to 256 even at whole sizes (512-1024-10, three of 256: 108 / 103;
-//          512-640-10, two of 512: 113 / 111) and still faster where the tiles hang over the edge (512-1036-10, five of 93: 101 / 111)
-//          and in first-order steps (69 / 79); more of them fill the chip
+// slices).  Against the 64 x 64 tiles, in slices where there are few of them, as the step of models K-N-10 here / there:
+//   K      up to 1152: faster or even (784-512, four workers of 128 samples: 76 / 82 us; 1036-340, five of 93: 77 / 83; 1036-256, two
+//          of 128: 67 / 72; 1036-256, six of 256: 97 / 96).  Longer ones take too long block by block (4096-64, one of 64: the
+//          product 50 / 18 us, the step 89 / 68; 1280-256, six of 256: 108 / 104) unless one block each is what most compute units
+//          get, 40 to 64 tiles, four blocks to a tile: then up to 2048 (1280-512, four of 128: 87 / 98; 2048-512: 111 / 116; at 4096 163 / 157)
+//   tiles  up to 128 of them as above; from there to 256 even at whole sizes (512-1024, three of 256: 108 / 103; 512-640, two of 512:
+//          113 / 111) and still faster where the tiles hang over the edge (512-1036, five of 93: 101 / 111) and in first-order
+//          steps (69 / 79); more of them fill the chip
 bool gemm_f32_short_shape(int64_t M, int64_t N, int64_t K, int k) {
-  return K <= 1024 && ((M + 63) / 64) * ((N + 63) / 64) * k < 256;
+  const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64) * k;
+  return tiles < 256 && K <= (tiles >= 40 && tiles <= 64 ? 2048 : 1152);
 }
 
 // Forward product, or data gradient through a layer of at most 32 outputs (the classes), of matrices in memory, no slices,

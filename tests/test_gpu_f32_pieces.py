@@ -30,6 +30,7 @@ def _inputs(dims, batch, k, seed):
                                          # products in the small-model kernel, 4 past a step of 32 k
     ((132, 192, 64, 3), 31, 3),          # minibatch shorter than a tile of 32 k
     ((1280, 256, 128, 16), 128, 2),      # whole tiles, the first forward product in slices
+    ((2048, 512, 10), 128, 4),           # the longest contraction of the small-model kernel
     ((132, 1028, 1036, 7), 193, 4),      # every hidden product in 64 x 64 tiles (272 of them): ragged rows, columns and last k-tile, with
                                          # and without the input's derivative
 ])
