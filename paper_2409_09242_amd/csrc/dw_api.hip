@@ -622,7 +622,7 @@ int dw_worker_step(dw_handle* h, const void* d_x, const int32_t* d_y, const uint
   const uint64_t active = mask_from(h_active, h->cfg.k);
   if (active == 0) { h->calls += 1; return DW_OK; }
   if (probes(h) > 1 && d_zbits) return DW_ERR_ARG;       // several probes per step come from the library's stream
-  // (a baseline's first-order step draws no z: the direction the network's R-parts then run along is whatever the
+  // (a baseline's first-order step draws no z: where the network still runs R-parts, the direction they run along is whatever the
   // sign-bit buffer holds, and their result is not used)
   if (!d_zbits && probes(h) == 1 && h->cfg.optimizer == DW_OPT_ADAHESSIAN && !tiny_step_ok(h->cfg, h->lay)) {
     const int st = draw_z(h, active, s);

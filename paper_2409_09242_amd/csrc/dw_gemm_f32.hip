@@ -16,12 +16,13 @@
 // Tiling: waves of 32 rows by 32 or 64 columns; tiles of 32 k are split into their pieces once per block while they are
 // stored to LDS (planes [row][32 k] of bf16, 64-byte rows, 16-byte units XOR-swizzled so that both the
 // reads of 8 consecutive rows and the stores of every fourth row spread over the banks); global loads are 16-byte and one
-// tile ahead in registers.  Before -> now: eight workers, 256 samples, 3072-1024-1024-1024: forward 295 / 135 -> 158 / 74 us
-// (first / later layers), data gradient 94 -> 62, fused weight gradients 346 / 154 -> 235 / 104; eight workers, 64 maps of
-// 26 x 26 x 32 -> 24 x 24 x 64: forward 328 -> 214, data gradient 465 -> 369, weight gradient 370 -> 240.  What bounds them now (64 x
-// 64 tiles, counters): matrix cores 25 to 35 % busy, vector arithmetic (splitting, 6 instructions per element and block that loads
-// it) 35 %, LDS 30 to 50 % (six bytes stored and read per element), and between them the two barriers a tile, with two blocks
-// a compute unit to hide them.  Two tiles in flight instead of one: no change.
+// tile ahead in registers.  On the fp32 matrix instruction -> now: eight workers, 256 samples, 3072-1024-1024-1024: forward
+// 295 / 135 -> 156 / 72 us (first / later layers), data gradient 94 -> 60, fused weight gradients 346 / 154 -> 226 / 101; eight
+// workers, 64 maps of 26 x 26 x 32 -> 24 x 24 x 64: forward 328 -> 211, data gradient 465 -> 376, weight gradient 370 -> 237.
+// What bounds them now (64 x 64 and 64 x 128 tiles of the first, by counters): matrix cores 30 to 36 % busy, vector arithmetic
+// (splitting, 6.5 instructions per element and block that loads it) 36 to 45 %, LDS instructions 40 to 47 % (six bytes stored and
+// read per element), and between them the two barriers a tile, with two blocks a compute unit to hide them; the convolutions
+// 20 to 38 %, 41 to 49 % and 31 to 56 %.  Two tiles in flight instead of one: no change.
 #include <cstddef>
 #include <type_traits>
 
