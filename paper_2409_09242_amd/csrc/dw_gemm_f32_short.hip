@@ -8,7 +8,7 @@
 // and keeps the next step's loads in flight), nothing goes through LDS and no barrier is met until the waves' partial
 // tiles are added in order of w and leave with the epilogue.  Against the tiles in slices over blocks with a second
 // launch that adds the slices (four workers, 128 samples): 784 -> 512 14.4 + 6.0 us, 512 -> 512 14.4 + 6.0, through 10
-// classes 11.7; here 15.7, 15.0 and 8.8.  What bounds it is the way of a row's 128-byte lines, one per row and step, through L1
+// classes 11.7; here 13.6, 14.4 and 9.4.  What bounds it is the way of a row's 128-byte lines, one per row and step, through L1
 // (k-steps of 16, half a line each: 28 us).
 #include <type_traits>
 
