@@ -6,11 +6,11 @@
 //   gather_kernel       each worker's minibatch: B uniform draws (with replacement) from its own D_j at its local
 //                       step, rows and labels copied from the resident data set into the step's input buffers.
 //
-// The permutation orders the points by (key, index), keys being 64-bit hashes of the index.  A large set is put into
-// buckets by the keys' leading bits first (about 16 to 32 points each) and a point is ranked within its bucket, so the
-// work is linear in n; a small one is ranked by comparing every pair.  Both are exact and independent of the order in
-// which threads run.  The gather is a plain row copy bound by HBM bandwidth.
+// The permutation orders the points by (key, index), keys being 64-bit hashes of the index.  The points are put into
+// buckets by the keys' leading bits first and ranked within their bucket, so the work is linear in n; exact and independent of
+// the order in which threads run.  The gather is a plain row copy bound by HBM bandwidth.
 #include <mutex>
+#include <type_traits>
 
 #include "dw_internal.h"
 
@@ -32,55 +32,20 @@ __host__ __device__ inline uint64_t mix64_d(uint64_t x) {      // SplitMix64 out
   return x;
 }
 
-__global__ __launch_bounds__(256) void partition_keys_kernel(uint64_t* keys, int32_t* rank, int64_t n, uint64_t k1) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  keys[i] = mix64_d(k1 + kGamma * (uint64_t)(i + 1));
-  rank[i] = 0;
-}
-
-// rank[i] += number of points j of this block row's slice with (key_j, j) < (key_i, i)
-__global__ __launch_bounds__(256) void partition_rank_kernel(const uint64_t* keys, int32_t* rank, int64_t n,
-                                                             int64_t slice) {
-  __shared__ uint64_t tile[256];
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const uint64_t mine = i < n ? keys[i] : 0;
-  const int64_t j0 = (int64_t)blockIdx.y * slice;
-  const int64_t j1 = j0 + slice < n ? j0 + slice : n;
-  int32_t cnt = 0;
-  for (int64_t base = j0; base < j1; base += 256) {            // uniform trip count: every thread reaches the barriers
-    const int64_t j = base + threadIdx.x;
-    __syncthreads();
-    tile[threadIdx.x] = j < j1 ? keys[j] : ~0ull;
-    __syncthreads();
-    const int lim = (int)(j1 - base < 256 ? j1 - base : 256);
-    for (int t = 0; t < lim; ++t) {
-      const uint64_t other = tile[t];
-      cnt += (other < mine || (other == mine && base + t < i)) ? 1 : 0;
-    }
-  }
-  if (i < n && cnt != 0) atomicAdd(&rank[i], cnt);
-}
-
 // where the point of rank r in the permutation goes: into every row when it is shared, else into its worker's
-__device__ __forceinline__ void partition_place(int32_t* index, int64_t i, int64_t r, int64_t o, int64_t s, int k) {
-  const int64_t m = o + s;
+// (at most DW_MAX_POINTS points and DW_MAX_K rows: 32-bit places)
+__device__ __forceinline__ void partition_place(int32_t* index, int32_t i, int32_t r, int32_t o, int32_t s, int k) {
+  const int32_t m = o + s;
   if (r < o) {
-    for (int j = 0; j < k; ++j) index[(int64_t)j * m + r] = (int32_t)i;
+    for (int j = 0; j < k; ++j) index[j * m + r] = i;
   } else if (s > 0) {
-    const int64_t q = r - o;
-    const int64_t j = q / s;
-    if (j < k) index[j * m + o + (q - j * s)] = (int32_t)i;
+    const int32_t q = r - o, j = (int32_t)((uint32_t)q / (uint32_t)s);
+    if (j < k) index[j * m + o + (q - j * s)] = i;
   }
 }
+static_assert((int64_t)DW_MAX_POINTS * DW_MAX_K < (1ll << 31), "places fit 32 bits");
 
-__global__ __launch_bounds__(256) void partition_scatter_kernel(const int32_t* rank, int32_t* index, int64_t n,
-                                                                int64_t o, int64_t s, int k) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) partition_place(index, i, rank[i], o, s, k);
-}
-
-// ---- the same through buckets: count, scan, fill, rank ---------------------------------------------------------------
+// ---- large sets: count, scan, fill, rank by buckets -------------------------------------------------------------------
 // Bucket of a point: the leading `bits` bits of its key (bits >= 1).  Keys are computed from the index wherever they are
 // needed (two 64-bit multiplies) instead of being stored, so that a point costs 8 bytes of scratch and a bucket 8.
 
@@ -137,14 +102,119 @@ __global__ __launch_bounds__(256) void bucket_rank_kernel(const int32_t* count, 
     const uint64_t key = mix64_d(k1 + kGamma * (uint64_t)((int64_t)other + 1));
     r += (key < mine || (key == mine && other < i)) ? 1 : 0;
   }
-  partition_place(index, i, r, o, s, k);
+  partition_place(index, i, r, (int32_t)o, (int32_t)s, k);
 }
 
-// Buckets are used from the size on that has scratch for the least number of them, 8 n + 8 * 1024 <= 12 n bytes: there
-// five short launches take as long as comparing every pair (whole call 33 us against 43 at n = 4000, 43 at n = 2000 for
-// the pairs), and then the pairs grow with n^2 (n = 60000: 0.945 ms -> 43 us, of which the kernels 28: counting and ranking
-// 10 each, bound by the atomics' and the bucket walk's latency; n = 2^21: 914 -> 0.41 ms).
-constexpr int64_t kBucketFrom = 2048;
+// ---- sets of up to 2^18 points: two launches ---------------------------------------------------------------------------
+// The five launches above cost more than their work at such sizes.  A block sorts a chunk of points by bucket in LDS
+// and writes them in that order together with where each bucket starts in the chunk; then a wave per bucket adds those starts
+// over the chunks (that is the number of points in the buckets before it), collects its points and ranks them.  No counter in
+// memory, so nothing is cleared.  Bound by latency: five dependent trips to memory.  n = 60000: the kernels 10 us, the whole call 26 (five launches: 28 and 43; buckets of
+// 64 to 128 points with four waves each 39, 20 of them comparing keys).
+
+constexpr int kChunkThreads = 1024, kMaxChunks = 64;
+
+// chunk c: the CH points from c * CH on, at points[c * CH ...] by bucket; edge[c * (nb + 1) + b]: the first of bucket b (b = 0 .. nb)
+template <int PER>
+__global__ __launch_bounds__(kChunkThreads) void chunk_sort_kernel(uint16_t* edge, int32_t* points, int64_t n, int bits, uint64_t k1) {
+  constexpr int CH = kChunkThreads * PER;
+  extern __shared__ int32_t first[];                           // [nb]: counts, then places
+  __shared__ int32_t waves[kChunkThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nb = 1 << bits;
+  uint16_t* edges = edge + (int64_t)blockIdx.x * (nb + 1);
+  const int64_t i0 = (int64_t)blockIdx.x * CH;
+  for (int b = tid; b < nb; b += kChunkThreads) first[b] = 0;
+  __syncthreads();
+  int bucket[PER], slot[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int64_t i = i0 + j * kChunkThreads + tid;
+    bucket[j] = i < n ? (int)(mix64_d(k1 + kGamma * (uint64_t)(i + 1)) >> (64 - bits)) : -1;
+    slot[j] = bucket[j] >= 0 ? atomicAdd(&first[bucket[j]], 1) : 0;      // a place in the bucket, in no particular order
+  }
+  __syncthreads();
+  const int per = (nb + kChunkThreads - 1) / kChunkThreads;    // buckets of a thread
+  int32_t sum = 0;
+  for (int j = 0; j < per; ++j) sum += tid * per + j < nb ? first[tid * per + j] : 0;
+  int32_t run = sum;                                           // inclusive over the wave
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int32_t t = __shfl_up(run, off);
+    if (lane >= off) run += t;
+  }
+  if (lane == 63) waves[wave] = run;
+  __syncthreads();
+  int32_t at = run - sum;
+  for (int w = 0; w < wave; ++w) at += waves[w];
+  for (int j = 0; j < per && tid * per + j < nb; ++j) {
+    const int b = tid * per + j;
+    const int32_t c = first[b];
+    first[b] = at;
+    edges[b] = (uint16_t)at;
+    at += c;
+  }
+  if (tid == kChunkThreads - 1) edges[nb] = (uint16_t)at;      // (the points of the chunk)
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < PER; ++j)
+    if (bucket[j] >= 0) points[i0 + first[bucket[j]] + slot[j]] = (int32_t)(i0 + j * kChunkThreads + tid);
+}
+
+// a wave per bucket: collect its points (a lane per chunk), rank them, place them
+template <int PER>
+__global__ __launch_bounds__(64) void chunk_rank_kernel(const uint16_t* edge, const int32_t* points, int nb, int chunks, int32_t* index,
+                                                        uint64_t k1, int32_t o, int32_t s, int k) {
+  constexpr int CH = kChunkThreads * PER, T = 64;
+  static_assert(kMaxChunks <= T, "a lane per chunk");
+  __shared__ uint64_t key[T];
+  __shared__ int32_t point[T];
+  const int lane = threadIdx.x, b = blockIdx.x;
+  // this lane's chunk: where the bucket starts in it, and how many points it has
+  const uint16_t* e = edge + (int64_t)lane * (nb + 1) + b;
+  const int lo = lane < chunks ? e[0] : 0, len = lane < chunks ? e[1] - lo : 0;
+  int32_t run = len, rank0 = lo;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int32_t t = __shfl_up(run, off);
+    if (lane >= off) run += t;
+    rank0 += __shfl_xor(rank0, off);
+  }
+  const int32_t total = __shfl(run, 63), at = run - len;       // at: the chunk's first point in the bucket's list
+  const int32_t* mine = points + (int64_t)lane * CH + lo;
+  auto stage = [&](int from) {                                 // list entries from .. from + T - 1 into LDS
+    for (int j = from > at ? from - at : 0; j < len && at + j < from + T; ++j) {
+      const int32_t i = mine[j];
+      point[at + j - from] = i;
+      key[at + j - from] = mix64_d(k1 + kGamma * (uint64_t)((int64_t)i + 1));
+    }
+  };
+  // (a list longer than the wave, more than five standard deviations above the mean, takes turns; two points never have the same key:
+  // the mixing function and the multiplication by an odd number are one to one)
+  for (int own = 0; own < total; own += T) {
+    __syncthreads();
+    stage(own);
+    __syncthreads();
+    const bool ok = own + lane < total;
+    const uint64_t me = ok ? key[lane] : 0;
+    const int32_t i = ok ? point[lane] : 0;
+    int32_t r = rank0;
+    for (int other = 0; other < total; other += T) {
+      if (total > T) {
+        __syncthreads();
+        stage(other);
+        __syncthreads();
+      }
+      const int m = total - other < T ? total - other : T;
+#pragma unroll 8
+      for (int j = 0; j < m; ++j) r += key[j] < me ? 1 : 0;
+    }
+    if (ok) partition_place(index, i, r, o, s, k);
+  }
+}
+
+// Above this size a chunk would need more points or the waves more lanes.
+constexpr int64_t kChunksTo = 4 * kMaxChunks * kChunkThreads;
 
 struct GatherKeys { uint64_t key[DW_MAX_K]; };
 
@@ -179,36 +249,38 @@ size_t partition_scratch_bytes(int64_t n) {
 
 hipError_t launch_partition(int64_t n, int64_t o, int k, uint64_t seed, int32_t* index, void* scratch, hipStream_t s) {
   const int64_t sz = (n - o) / k;
-  if (n >= kBucketFrom) {
-    int bits = 10;                                             // at least 1024 buckets, then 16 to 32 points a bucket
-    while ((n >> (bits + 1)) >= 16) bits += 1;
+  const uint64_t k1 = mix64_d(seed);
+  if (n <= kChunksTo) {
+    int bits = 5;                                              // 16 to 32 points a bucket (fewer of n < 512)
+    while (bits < 13 && (n >> (bits + 1)) >= 16) bits += 1;    // (8192 counters: 32 KB of LDS)
     const int nb = 1 << bits;
-    // 8 n + 8 nb bytes, nb <= n / 16: within the 12 n of partition_scratch_bytes
-    int32_t* count = reinterpret_cast<int32_t*>(scratch);
-    int32_t* start = count + nb;
-    int32_t* slot = start + nb;
-    int32_t* points = slot + n;
-    const unsigned blocks = (unsigned)((n + 255) / 256);
-    const uint64_t k1 = mix64_d(seed);
-    hipLaunchKernelGGL(bucket_clear_kernel, dim3((unsigned)(nb / 256)), dim3(256), 0, s, count, nb);
-    hipLaunchKernelGGL(bucket_count_kernel, dim3(blocks), dim3(256), 0, s, count, slot, n, bits, k1);
-    hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(1024), 0, s, count, start, nb);
-    hipLaunchKernelGGL(bucket_fill_kernel, dim3(blocks), dim3(256), 0, s, start, slot, points, n, bits, k1);
-    hipLaunchKernelGGL(bucket_rank_kernel, dim3(blocks), dim3(256), 0, s, count, start, points, index, n, bits, k1, o, sz, k);
+    auto launch = [&](auto per) {
+      constexpr int PER = decltype(per)::value, CH = kChunkThreads * PER;
+      const unsigned chunks = (unsigned)((n + CH - 1) / CH);   // kMaxChunks at most
+      // 4 n bytes of points, 2 chunks (nb + 1) <= 8 n of edges (nb <= n / 16, chunks <= 64; 66 when n < 512)
+      int32_t* points = reinterpret_cast<int32_t*>(scratch);
+      uint16_t* edge = reinterpret_cast<uint16_t*>(points + n);
+      hipLaunchKernelGGL(chunk_sort_kernel<PER>, dim3(chunks), dim3(kChunkThreads), nb * (int)sizeof(int32_t), s, edge, points, n, bits, k1);
+      hipLaunchKernelGGL(chunk_rank_kernel<PER>, dim3((unsigned)nb), dim3(64), 0, s, edge, points, nb, (int)chunks, index, k1, (int32_t)o,
+                         (int32_t)sz, k);
+    };
+    if (n <= kMaxChunks * kChunkThreads) launch(std::integral_constant<int, 1>{}); else launch(std::integral_constant<int, 4>{});
     return hipGetLastError();
   }
-  uint64_t* keys = reinterpret_cast<uint64_t*>(scratch);
-  int32_t* rank = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(scratch) + ((size_t)n * 8 + 255) / 256 * 256);
-  const unsigned nb = (unsigned)((n + 255) / 256);
-  hipLaunchKernelGGL(partition_keys_kernel, dim3(nb), dim3(256), 0, s, keys, rank, n, mix64_d(seed));
-  // enough block rows to fill the chip when n is small; each covers a slice of the points compared against
-  int64_t rows = 2048 / nb;
-  if (rows < 1) rows = 1;
-  if (rows > nb) rows = nb;
-  int64_t slice = ((n + rows - 1) / rows + 255) / 256 * 256;
-  rows = (n + slice - 1) / slice;
-  hipLaunchKernelGGL(partition_rank_kernel, dim3(nb, (unsigned)rows), dim3(256), 0, s, keys, rank, n, slice);
-  hipLaunchKernelGGL(partition_scatter_kernel, dim3(nb), dim3(256), 0, s, rank, index, n, o, sz, k);
+  int bits = 13;                                               // 16 to 32 points a bucket
+  while ((n >> (bits + 1)) >= 16) bits += 1;
+  const int nb = 1 << bits;
+  // 8 n + 8 nb bytes, nb <= n / 16: within the 12 n of partition_scratch_bytes
+  int32_t* count = reinterpret_cast<int32_t*>(scratch);
+  int32_t* start = count + nb;
+  int32_t* slot = start + nb;
+  int32_t* points = slot + n;
+  const unsigned blocks = (unsigned)((n + 255) / 256);
+  hipLaunchKernelGGL(bucket_clear_kernel, dim3((unsigned)(nb / 256)), dim3(256), 0, s, count, nb);
+  hipLaunchKernelGGL(bucket_count_kernel, dim3(blocks), dim3(256), 0, s, count, slot, n, bits, k1);
+  hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(1024), 0, s, count, start, nb);
+  hipLaunchKernelGGL(bucket_fill_kernel, dim3(blocks), dim3(256), 0, s, start, slot, points, n, bits, k1);
+  hipLaunchKernelGGL(bucket_rank_kernel, dim3(blocks), dim3(256), 0, s, count, start, points, index, n, bits, k1, o, sz, k);
   return hipGetLastError();
 }
 
