@@ -308,6 +308,7 @@ void fill_update_args(dw_handle* h, UpdateArgs& a, const float* g, const float* 
     a.bias.begin[l] = L.boff[l];
     a.bias.end[l] = L.boff[l] + c.dims[l + 1];
   }
+  a.loss = LossSlots{};
   a.fused.n = 0;
   if (fused_step) {
     for (int l = 0; l < c.n_layers; ++l) {
@@ -401,11 +402,11 @@ int run_step(dw_handle* h, const void* d_x, const int32_t* d_y, const uint32_t* 
       // probes after the first find the activations and the plain data gradients of this minibatch in the workspace
       if (h->lay.n_conv > 0) {
         // the window mean is linear: taken per probe on z_j*Hz_j, it gives the window mean of their mean
-        st = run_network_cnn(h->cfg, h->ws, h->lay, d_x, d_y, zb, zs, active, loss, s);
+        st = run_network_cnn(h->cfg, h->ws, h->lay, d_x, d_y, zb, zs, active, loss, s, &a.loss);
         if (st == DW_OK && h->cfg.conv_avg)
           DW_HIP(launch_conv_window_mean(h->at<float>(h->lay.hz), zb, h->lay.Pp, zs, h->lay, h->cfg.k, active, s));
       } else {
-        st = run_network(h->cfg, h->ws, h->lay, d_x, d_y, zj, zs, active, loss, fused ? &a : nullptr, true, s, nullptr,
+        st = run_network(h->cfg, h->ws, h->lay, d_x, d_y, zj, zs, active, loss, fused ? &a : nullptr, true, s, &a.loss, nullptr,
                          nullptr, nullptr, j > 0, pair ? j + 1 : 0, h->side);
       }
       if (st != DW_OK) return st;
@@ -447,12 +448,12 @@ int run_step(dw_handle* h, const void* d_x, const int32_t* d_y, const uint32_t* 
   // dw_elastic_sync call, no round is due; should a round come anyway, it measures the distances itself.
   const bool dist = !fused || h->last_tau <= 1 || (h->calls + 1) % h->last_tau == 0;
   if (h->lay.n_conv > 0) {
-    st = run_network_cnn(h->cfg, h->ws, h->lay, d_x, d_y, zb, zs, active, loss, s);
+    st = run_network_cnn(h->cfg, h->ws, h->lay, d_x, d_y, zb, zs, active, loss, s, &a.loss);
     if (st != DW_OK) return st;
     if (h->cfg.conv_avg)
       DW_HIP(launch_conv_window_mean(h->at<float>(h->lay.hz), zb, h->lay.Pp, zs, h->lay, h->cfg.k, active, s));
   } else {
-    st = run_network(h->cfg, h->ws, h->lay, d_x, d_y, zb, zs, active, loss, fu, dist, s, nullptr, nullptr, nullptr, false, 0,
+    st = run_network(h->cfg, h->ws, h->lay, d_x, d_y, zb, zs, active, loss, fu, dist, s, &a.loss, nullptr, nullptr, nullptr, false, 0,
                      h->side);
     if (st != DW_OK) return st;
   }

@@ -158,7 +158,7 @@ hipError_t launch_conv_window_mean(float* hz, const uint32_t* zbits, int64_t Pp,
 }
 
 int run_network_cnn(const dw_config& cfg, char* ws, const Layout& lay, const void* d_x, const int32_t* d_y,
-                    const uint32_t* zbits, int64_t z_stride, uint64_t active, float* d_loss, hipStream_t s) {
+                    const uint32_t* zbits, int64_t z_stride, uint64_t active, float* d_loss, hipStream_t s, LossSlots* slots) {
   const int nc = lay.n_conv, k = cfg.k, B = cfg.batch;
   float* theta = reinterpret_cast<float*>(ws + lay.theta);
   float* g = reinterpret_cast<float*>(ws + lay.g);
@@ -209,7 +209,7 @@ int run_network_cnn(const dw_config& cfg, char* ws, const Layout& lay, const voi
     if ((e = hipGetLastError()) != hipSuccess) return DW_ERR_HIP;
   }
   // the linear layers, forward and backward, down to the gradient with respect to the pooled map
-  const int st = run_network(cfg, ws, lay, f(lay.pool), d_y, zbits, z_stride, active, d_loss, nullptr, true, s,
+  const int st = run_network(cfg, ws, lay, f(lay.pool), d_y, zbits, z_stride, active, d_loss, nullptr, true, s, slots,
                              f(lay.rpool), f(lay.dpool), f(lay.rdpool));
   if (st != DW_OK) return st;
   // back through the pooling (the ReLU of the last convolution is already in the mask of that gradient: a pooled

@@ -181,6 +181,13 @@ __global__ __launch_bounds__(kUpdThreads) void update_kernel(UpdateArgs a) {
     const float d0 = t.x - c.x, d1 = t.y - c.y, d2 = t.z - c.z, d3 = t.w - c.w;
     nsum = (d0 * d0 + d1 * d1) + (d2 * d2 + d3 * d3);
   }
+  // the minibatch loss, by the last wave of the worker's first block: the slots 64 apart, then the lanes in a fixed tree, in 64 bits
+  if (a.loss.n > 0 && active && wave == kUpdThreads / 64 - 1 && (a.n_list > 0 ? blockIdx.x == 0 : slot == 0)) {
+    double t = 0.0;
+    for (int b = lane; b < a.loss.n; b += 64) t += (double)a.loss.part[(int64_t)i * a.loss.n + b];
+    t = wave_sum(t);
+    if (lane == 0) a.loss.loss[i] = (float)(t / (double)a.loss.B);
+  }
   __shared__ double wave_part[kUpdThreads / 64];
   const double ws = wave_sum((double)nsum);
   if (lane == 0) wave_part[wave] = ws;

@@ -37,6 +37,13 @@ struct FusedRanges {
   int64_t end[DW_MAX_LAYERS];
 };
 
+// losses of the output-layer kernels' blocks, one slot per 16 samples: loss[i] = (sum of worker i's n slots) / B; n = 0: nothing to add up
+struct LossSlots {
+  const float* part;                  // [k][n]
+  float* loss;                        // [k]
+  int n, B;
+};
+
 struct UpdateArgs {
   float* theta; float* m; float* v;   // [k][Pp]
   const float* g; const float* hz;    // [k][g_stride]
@@ -57,6 +64,7 @@ struct UpdateArgs {
   BiasRanges bias;
   FusedRanges fused;
   UpdateScalars sc;
+  LossSlots loss;                     // added up along with the update (a launch for it alone: 3 to 5 us of every step)
   // several probes per step with fused weight gradients (see FuseArgs): mode, first probe, running sum [k][Pp]
   int probe_mode, probe_first;
   float* dacc;
@@ -258,7 +266,7 @@ struct HeadArgs {                     // softmax cross-entropy on the output lay
 };
 hipError_t launch_head(const HeadArgs& a, hipStream_t s);
 // fp32 output layer and head in one kernel (dw_out_head_f32.hip): `a` as for the output layer's forward product
-// (its C and RC are not written), loss_part: k * ceil(M / 16) floats of scratch, slices: out_head_f32_slice_bytes of it
+// (its C and RC are not written; the losses go to loss_part alone: k slots for every 16 samples), slices: out_head_f32_slice_bytes of it
 bool out_head_f32_ok(const GemmArgs& a);
 int out_head_f32_slices(int64_t M, int64_t K, int k);
 size_t out_head_f32_slice_bytes(int64_t M, int64_t K, int k);
@@ -320,8 +328,9 @@ struct SideStream {
 // weight gradients (a fused weight gradient overwrites the W_l its layer's data gradient reads).
 int run_network(const dw_config& cfg, char* ws, const Layout& lay, const void* d_x, const int32_t* d_y,
                 const uint32_t* zbits, int64_t z_stride, uint64_t active, float* d_loss, const UpdateArgs* fuse,
-                bool fuse_dist, hipStream_t s, const void* in_ract = nullptr, void* d_in = nullptr,
+                bool fuse_dist, hipStream_t s, LossSlots* slots, const void* in_ract = nullptr, void* d_in = nullptr,
                 void* rd_in = nullptr, bool r_only = false, int pair_phase = 0, const SideStream* side = nullptr);
+// `slots`: receives what is left to add up for d_loss (n = 0: nothing is).
 // `r_only`: the same minibatch went through the network before (an earlier Hutchinson probe of this step), so the
 // activations and the plain data gradients are in the workspace; kernels that can then compute the R-parts alone.
 // `pair_phase` (lay.pair): 1 = the earlier of two probes: its R-quantities go to the buffers kept for it, the fused
@@ -336,7 +345,7 @@ int run_network(const dw_config& cfg, char* ws, const Layout& lay, const void* d
 // The same for a model with a convolutional front end: convolutions, pooling, then run_network on the pooled map,
 // then back through the pooling and the convolutions (fp32 only).
 int run_network_cnn(const dw_config& cfg, char* ws, const Layout& lay, const void* d_x, const int32_t* d_y,
-                    const uint32_t* zbits, int64_t z_stride, uint64_t active, float* d_loss, hipStream_t s);
+                    const uint32_t* zbits, int64_t z_stride, uint64_t active, float* d_loss, hipStream_t s, LossSlots* slots);
 // A small fp32 model's whole worker step in one kernel (dw_tiny.hip): can this configuration take it, and the launch.
 // `u`: the update's arguments of this step (step counts already advanced), keys_host: the workers' stream keys.
 bool tiny_step_ok(const dw_config& cfg, const Layout& lay);

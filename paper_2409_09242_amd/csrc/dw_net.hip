@@ -12,7 +12,6 @@
 #include "dw_internal.h"
 #include "dw_device_util.h"
 #include "dw_head_math.h"
-#include "dw_out_head.h"
 
 namespace dw {
 
@@ -63,27 +62,9 @@ hipError_t launch_head(const HeadArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// a wave per worker: every lane adds the slots 64 apart, then the lanes in a fixed tree, in 64 bits
-__global__ __launch_bounds__(64) void loss_sum_kernel(const float* loss_part, int n_slots, float* loss, int B,
-                                                      uint64_t active_mask) {
-  const int i = blockIdx.x;
-  if (!((active_mask >> i) & 1ull)) return;
-  double t = 0.0;
-  for (int b = threadIdx.x; b < n_slots; b += 64) t += (double)loss_part[(int64_t)i * n_slots + b];
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off);
-  if (threadIdx.x == 0) loss[i] = (float)(t / (double)B);
-}
-
-hipError_t launch_loss_sum(const float* loss_part, int n_slots, const HeadArgs& h, hipStream_t s) {
-  if (!h.loss) return hipSuccess;
-  hipLaunchKernelGGL(loss_sum_kernel, dim3((unsigned)h.k), dim3(64), 0, s, loss_part, n_slots, h.loss, h.B, h.active_mask);
-  return hipGetLastError();
-}
-
 int run_network(const dw_config& cfg, char* ws, const Layout& lay, const void* d_x, const int32_t* d_y,
                 const uint32_t* zbits, int64_t z_stride, uint64_t active, float* d_loss, const UpdateArgs* fuse,
-                bool fuse_dist, hipStream_t s, const void* in_ract, void* d_in, void* rd_in, bool r_only,
+                bool fuse_dist, hipStream_t s, LossSlots* slots, const void* in_ract, void* d_in, void* rd_in, bool r_only,
                 int pair_phase, const SideStream* side) {
   const bool b16 = cfg.dtype == DW_BF16;
   const int L = cfg.n_layers, k = cfg.k, B = cfg.batch;
@@ -130,6 +111,7 @@ int run_network(const dw_config& cfg, char* ws, const Layout& lay, const void* d
   hd.Rdelta_b16 = b16 ? reinterpret_cast<uint16_t*>(ws + lay.rdL16) : nullptr;
   hd.y = d_y; hd.loss = d_loss; hd.B = B; hd.C = cfg.dims[L]; hd.ld = HL; hd.k = k; hd.active_mask = active;
   bool head_done = false;
+  *slots = LossSlots{};
 
   // forward with R-forward
   for (int l = 1; l <= L; ++l) {
@@ -174,7 +156,9 @@ int run_network(const dw_config& cfg, char* ws, const Layout& lay, const void* d
   }
 
   // softmax cross-entropy head
-  if (!head_done) {
+  if (head_done) {
+    if (d_loss) *slots = LossSlots{reinterpret_cast<const float*>(ws + lay.sL), d_loss, (B + 15) / 16, B};
+  } else {
     if ((e = launch_head(hd, s)) != hipSuccess) return DW_ERR_HIP;
   }
 

@@ -16,7 +16,7 @@ template <int NW>
 __device__ __forceinline__ void out_head_rows(const float (&part)[NW][2][DW_MAX_CLASSES][DW_MAX_CLASSES + 1], const GemmArgs& a,
                                               const HeadArgs& h, float* loss_part, int worker, int row0, const uint32_t* zb) {
   __shared__ float row_loss[DW_MAX_CLASSES];
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x;
   const int m = tid >> 4, n = tid & 15;                   // one 16-lane group per sample, one lane per class
   float s = 0.f, rs = 0.f;
   if (n < a.N) {
@@ -26,25 +26,18 @@ __device__ __forceinline__ void out_head_rows(const float (&part)[NW][2][DW_MAX_
     s += a.bias[(int64_t)worker * a.bias_wstride + n];
     rs += ((zb[bi >> 5] >> (bi & 31)) & 1u) ? 1.f : -1.f;
   }
-  // every lane of the group gathers the sample's logits and runs the head on them; it keeps its own class
-  float sv[DW_MAX_CLASSES], rsv[DW_MAX_CLASSES], d[DW_MAX_CLASSES], rd[DW_MAX_CLASSES];
-  const int base = lane & 48;
-#pragma unroll
-  for (int c = 0; c < DW_MAX_CLASSES; ++c) { sv[c] = __shfl(s, base + c); rsv[c] = __shfl(rs, base + c); }
   const int row = row0 + m;
   const int yrow = row < a.M ? row : a.M - 1;
   const int y = h.y[(int64_t)worker * h.B + yrow];
-  const float lrow = head_row(sv, rsv, y, h.C, 1.0f / (float)h.B, d, rd);
-  float dn = 0.f, rdn = 0.f;
-#pragma unroll
-  for (int c = 0; c < DW_MAX_CLASSES; ++c) { if (c == n) { dn = d[c]; rdn = rd[c]; } }
+  float dn, rdn, rest, sy;
+  head_lanes(s, rs, n, y, h.C, 1.0f / (float)h.B, dn, rdn, rest, sy);
   if (row < a.M && n < h.ld) {
     const int64_t o = ((int64_t)worker * h.B + row) * h.ld + n;
     h.delta[o] = dn;
     h.Rdelta[o] = rdn;
     if (h.delta_b16) { h.delta_b16[o] = f32_to_bf16_rne(dn); h.Rdelta_b16[o] = f32_to_bf16_rne(rdn); }
   }
-  if (n == 0) row_loss[m] = row < a.M ? lrow : 0.f;
+  if (n == 0) row_loss[m] = row < a.M ? log1pf(rest) - sy : 0.f;
   __syncthreads();
   if (tid == 0) {
     double t = 0.0;                                       // (16 sums in fp32 would be off by a last bit or two)
@@ -53,8 +46,5 @@ __device__ __forceinline__ void out_head_rows(const float (&part)[NW][2][DW_MAX_
     loss_part[(int64_t)worker * gridDim.x + blockIdx.x] = (float)t;
   }
 }
-
-// loss[i] = (sum of worker i's slots) / B for the active workers, when the caller wants it
-hipError_t launch_loss_sum(const float* loss_part, int n_slots, const HeadArgs& h, hipStream_t s);
 
 }  // namespace dw

@@ -7,7 +7,7 @@
 // 16 x 16 x 4 MFMA, every lane loading 16 bytes (4 consecutive k) of A, RA and W per step, and the four partial tiles
 // are added in wave order through LDS.  A 16-lane group then holds one sample's 16 logits, gathers them by shuffles
 // and runs the head's arithmetic on them.  The loss of the block's samples goes to one slot per (worker, block);
-// loss_sum_kernel adds a worker's slots in index order when the caller wants the loss.
+// the update's kernel adds a worker's slots when the caller wants the loss.
 //
 // Few samples and a long contraction leave a handful of blocks walking all of it.  There the contraction is cut into slices
 // over the grid, whose partial logits go to scratch, and a second launch adds them in order and runs the head
@@ -170,7 +170,7 @@ bool out_head_f32_ok(const GemmArgs& a) {
   return true;
 }
 
-// loss_part: at least k * ceil(M / 16) floats; h.loss may be nullptr (then the slots are not added up); slices: scratch of
+// loss_part: at least k * ceil(M / 16) floats; slices: scratch of
 // out_head_f32_slice_bytes
 hipError_t launch_out_head_f32(const GemmArgs& a, const HeadArgs& h, float* loss_part, float* slices, hipStream_t s) {
   KernelScope ks(KC_HEAD, s);
@@ -183,9 +183,7 @@ hipError_t launch_out_head_f32(const GemmArgs& a, const HeadArgs& h, float* loss
   } else {
     hipLaunchKernelGGL(f32o::out_head_f32_kernel<false>, grid, dim3(f32o::NT), 0, s, a, h, loss_part, slices);
   }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !h.loss) return e;
-  return launch_loss_sum(loss_part, n_slots, h, s);
+  return hipGetLastError();
 }
 
 }  // namespace dw
