@@ -204,7 +204,7 @@ int validate(const dw_config* c, Layout* lay) {
     for (int l = 2; l <= L; ++l) {
       const int64_t n = c->dims[l - 1], kk = c->dims[l];
       const int64_t tiles = n <= 32 ? (B + 127) / 128 : B <= 32 ? (n + 127) / 128 : ((B + 63) / 64) * ((n + 63) / 64);
-      int64_t split = tiles * k < 256 ? 1024 / (tiles * k) : 1;
+      int64_t split = tiles * k < 256 && !gemm_f32_short_shape(B, n, kk, k) ? 1024 / (tiles * k) : 1;
       if (split > kk / 64) split = kk / 64;
       if (split > 64) split = 64;
       lay->dgSplit[l - 1] = (int)(split < 1 ? 1 : split);
@@ -243,6 +243,7 @@ int validate(const dw_config* c, Layout* lay) {
     int64_t blocks = 0;                                   // 64 x 64 output tiles of all weight gradients
     for (int l = 1; l <= L; ++l) blocks += (int64_t)((c->dims[l] + 63) / 64) * ((c->dims[l - 1] + 63) / 64) * k;
     lay->overlap_wgrad = blocks < 4096 && !tiny_step_ok(*c, *lay);
+    if (c->dtype == DW_F32) { lay->group_wgrad = wgrad_group_f32_ok(*c); lay->overlap_wgrad = lay->overlap_wgrad && !lay->group_wgrad; }
   }
   lay->u_ring = take((size_t)k * (DW_MAX_P + 1) * sizeof(double));
   lay->score = take((size_t)k * 4 * sizeof(double));

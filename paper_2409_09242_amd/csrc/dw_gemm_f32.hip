@@ -328,10 +328,14 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
   constexpr bool HAS_C = FM != 1;                            // the plain product is computed
   constexpr bool HAS_R = HAS_RX || RYM != RY_NONE;           // the R-companion is
   constexpr bool STAGED = X_KC && Y_KC && BM == 64 && BN == 64;
-  const int worker = nth_active_worker(a.active_mask, blockIdx.y);    // grid y covers the active workers
-
-  const int tiles_m = (a.M + BM - 1) / BM;
-  const int tm = blockIdx.x % tiles_m, tn = blockIdx.x / tiles_m;
+  // consecutive blocks of an XCD: the row tiles of a column tile (its W panel is read once), then the next column tile, the next slice,
+  // the next worker
+  const unsigned tiles_m = (a.M + BM - 1) / BM, tiles = tiles_m * ((a.N + BN - 1) / BN);
+  const unsigned slices = a.ksplit > 1 ? a.ksplit : 1, logical = xcd_unit(), slot = logical / (tiles * slices);
+  if (slot >= (unsigned)active_count(a.active_mask, a.k)) return;
+  const int worker = nth_active_worker(a.active_mask, slot);
+  const unsigned in_worker = logical - slot * (tiles * slices), in_slice = in_worker % tiles;
+  const int slice = in_worker / tiles, tm = in_slice % tiles_m, tn = in_slice / tiles_m;
   const int row0 = tm * BM, col0 = tn * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm0 = (wave % WM) * (BM / WM), wn0 = (wave / WM) * (BN / WN);
@@ -354,7 +358,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
   // the slice of the contraction this block covers (all of it unless the product is cut along k)
   const bool sliced = (EPI == EPI_WGRAD || EPI == EPI_RELU || EPI == EPI_MASK) && a.ksplit > 1;
   const int kchunk = sliced ? ((a.K + a.ksplit - 1) / a.ksplit + BK - 1) / BK * BK : a.K;
-  const int kbeg = sliced ? (int)blockIdx.z * kchunk : 0;
+  const int kbeg = sliced ? slice * kchunk : 0;
   const int kend = sliced ? (kbeg + kchunk < a.K ? kbeg + kchunk : a.K) : a.K;
   const int nkt = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
 
@@ -523,7 +527,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
           if (HAS_RX) hzb += part[(8 + q) * BM + tid];
         }
         if (sliced) {
-          float* pb = a.part_b + (((int64_t)blockIdx.z * a.k + worker) * 2) * a.M;
+          float* pb = a.part_b + (((int64_t)slice * a.k + worker) * 2) * a.M;
           pb[m] = gb;
           if (HAS_RX) pb[a.M + m] = hzb;
         } else {
@@ -580,7 +584,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
   float* C = reinterpret_cast<float*>(a.C) + (int64_t)worker * a.c_wstride;
   float* RC = reinterpret_cast<float*>(a.RC) + (int64_t)worker * a.c_wstride;
   if (sliced) {
-    C = a.part + (((int64_t)blockIdx.z * a.k + worker) * 2) * a.part_stride;
+    C = a.part + (((int64_t)slice * a.k + worker) * 2) * a.part_stride;
     RC = C + a.part_stride;
   }
 #pragma unroll
@@ -623,6 +627,212 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void dual_gemm_f32(GemmArgs a) {
       }
     }
   }
+}
+
+// ---- weight gradients of all layers of a small MLP in one launch ------------------------------------------------------------
+// gW_l = d_l^T a_{l-1}, HzW_l = Rd_l^T a_{l-1} + d_l^T Ra_{l-1} and the bias gradients as above, 64 x 64 tiles of W_l, the layers' tiles
+// behind each other.  Each layer's product alone fills a fraction of the chip and lasts as long as its trips to memory; together they
+// last hardly longer than the longest, and the host has one launch to make instead of a launch and two events a layer.  Two
+// tiles of 32 samples are on their way while one is multiplied.  784-512-512-10, four workers of 128 samples: 24 us for the three
+// layers (13 to 14 each, two of them beside the data gradients on a second stream, and 20 us of the host's time for its
+// events); a wave per 32 x 32 tile with its operands straight from memory 29: four times the loads and twice the splitting.
+namespace f32g {
+
+constexpr int EDGE = 64, NT = 256;
+
+struct Layer {
+  const float* x; const float* rx;                           // d_l, Rd_l of worker 0 [B][ldx]
+  const float* y; const float* ry;                           // a_{l-1}, Ra_{l-1} (nullptr: the input) [B][N]
+  int64_t x_wstride, y_wstride, woff, boff;                  // offsets in a row of g and of hz
+  int ldx, M, N, tiles_m, first;                             // W_l is [M][N]; its first tile
+};
+struct Args {
+  Layer layer[DW_MAX_LAYERS];
+  int n, tiles, B, workers;                                  // workers: the active ones
+  float* g; float* hz; int64_t Pp;                           // [k][Pp]
+  uint64_t active_mask;
+};
+
+template <bool HAS_R, bool HAS_RY>
+__device__ __forceinline__ void run_tile(const Args& a, const Layer& y, int tile, int worker, char* lds) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, lhalf = lane >> 5;
+  const int tm = tile % y.tiles_m, tn = tile / y.tiles_m, row0 = tm * EDGE, col0 = tn * EDGE;
+  const int wm0 = (wave & 1) * 32, wn0 = (wave >> 1) * 32;
+  using LX = TileLoader<NT, EDGE, false, HAS_R ? 2 : 1, VIEW_NONE>;
+  using LY = TileLoader<NT, EDGE, false, HAS_RY ? 2 : 1, VIEW_NONE>;
+  char* Xl = lds;
+  char* Yl = Xl + 3 * (HAS_R ? 2 : 1) * LX::PLANE;
+  const float* X = y.x + worker * y.x_wstride;
+  const float* RX = HAS_R ? y.rx + worker * y.x_wstride : nullptr;
+  const float* Y = y.y + worker * y.y_wstride;
+  const float* RY = HAS_RY ? y.ry + worker * y.y_wstride : nullptr;
+  const int K = a.B, nkt = (K + BK - 1) / BK;
+  const int xat = unit_at(wm0 + l32, lhalf), yat = unit_at(wn0 + l32, lhalf);   // of k-step 0
+  const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  floatx16 acc, racc, t, tr;
+  float sums[LX::NU][4], none[LY::NU][4];
+  const ConvView no_view{};
+
+  auto contract = [&](auto halves) {
+    constexpr bool HALVES = decltype(halves)::value;
+    LX lx[2]; LY ly[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      lx[h].begin(X, RX, y.ldx, row0, y.M, 0, no_view, tid);
+      ly[h].begin(Y, RY, y.N, col0, y.N, 0, no_view, tid);
+    }
+    acc = zero; racc = zero; t = zero; tr = zero;
+#pragma unroll
+    for (int u = 0; u < LX::NU; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sums[u][r] = 0.f;
+    auto fetch = [&](int h, int kt) {
+      if ((kt + 1) * BK <= K) { lx[h].template load<true>(kt * BK, K, tid); ly[h].template load<true>(kt * BK, K, tid); }
+      else { lx[h].template load<false>(kt * BK, K, tid); ly[h].template load<false>(kt * BK, K, tid); }
+    };
+    // FETCH: the tile after the next one exists and is asked for
+    auto step = [&](auto which, int kt, auto fetch_next) {
+      constexpr int h = decltype(which)::value;
+      lx[h].template split_store<HALVES>(Xl, tid, tn == 0, sums);
+      ly[h].template split_store<HALVES>(Yl, tid, false, none);
+      __syncthreads();
+      if constexpr (decltype(fetch_next)::value) fetch(h, kt + 2);
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        bf16x8 x[3], rx[3], yv[3], ry[3];
+        auto piece = [](const char* at) { return *reinterpret_cast<const bf16x8*>(at); };
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          x[c] = piece(Xl + c * LX::PLANE + (xat ^ (s * 32)));
+          yv[c] = piece(Yl + c * LY::PLANE + (yat ^ (s * 32)));
+          if (HAS_R) rx[c] = piece(Xl + (3 + c) * LX::PLANE + (xat ^ (s * 32)));
+          if (HAS_RY) ry[c] = piece(Yl + (3 + c) * LY::PLANE + (yat ^ (s * 32)));
+        }
+        if constexpr (HALVES) {
+          mfma_whole(x, yv, acc);
+          if (HAS_R) mfma_whole(rx, yv, racc);
+          if (HAS_RY) mfma_whole(x, ry, racc);
+        } else {
+          mfma6(x, yv, acc, t);
+          if (HAS_R) mfma6(rx, yv, racc, tr);
+          if (HAS_RY) mfma6(x, ry, racc, tr);
+        }
+      }
+      __syncthreads();
+    };
+    using Even = std::integral_constant<int, 0>;
+    using Odd = std::integral_constant<int, 1>;
+    fetch(0, 0);
+    if (nkt > 1) fetch(1, 1);
+    int kt = 0;
+    for (; kt + 3 < nkt; kt += 2) {
+      step(Even{}, kt, std::true_type{});
+      step(Odd{}, kt + 1, std::true_type{});
+    }
+    if (kt + 2 < nkt) {                                      // three left
+      step(Even{}, kt, std::true_type{});
+      step(Odd{}, kt + 1, std::false_type{});
+      step(Even{}, kt + 2, std::false_type{});
+    } else {
+      step(Even{}, kt, std::false_type{});
+      if (kt + 1 < nkt) step(Odd{}, kt + 1, std::false_type{});
+    }
+    bool finite = true;
+    if constexpr (!HALVES) {
+      finite &= join_chains(acc, t);
+      if (HAS_R) finite &= join_chains(racc, tr);
+    }
+    return !finite;
+  };
+  const bool again = __syncthreads_or(contract(std::false_type{}));      // (see dual_gemm_f32)
+  if (again | (K < kWholeBelow)) contract(std::true_type{});
+
+  float* g = a.g + worker * a.Pp;
+  float* hz = a.hz + worker * a.Pp;
+  if (tn == 0) {                                             // bias gradients: the sums of eight threads, in order of k
+    float* part = reinterpret_cast<float*>(lds);             // [operand][8][EDGE]
+#pragma unroll
+    for (int u = 0; u < LX::NU; ++u) {
+      int op, w;
+      if (!LX::unit(u, tid, op, w)) continue;
+      const int rg = w % (EDGE / 4), kq = w / (EDGE / 4);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) part[(op * 8 + kq) * EDGE + rg * 4 + r] = sums[u][r];
+    }
+    __syncthreads();
+    const int m = row0 + tid;
+    if (tid < EDGE && m < y.M) {
+      float gb = 0.f, hzb = 0.f;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        gb += part[q * EDGE + tid];
+        if (HAS_R) hzb += part[(8 + q) * EDGE + tid];
+      }
+      g[y.boff + m] = gb;
+      if (HAS_R) hz[y.boff + m] = hzb;
+    }
+  }
+  const int n = col0 + wn0 + l32;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int m = row0 + wm0 + (r >> 2) * 8 + lhalf * 4 + (r & 3);
+    if (n >= y.N || m >= y.M) continue;
+    const int64_t o = y.woff + (int64_t)m * y.N + n;
+    g[o] = acc[r];
+    if (HAS_R) hz[o] = racc[r];
+  }
+}
+
+// PLAIN: a first-order step, g alone
+template <bool PLAIN>
+__global__ __launch_bounds__(NT, 2) void wgrad_group_f32(Args a) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  const unsigned logical = xcd_unit(), slot = logical / (unsigned)a.tiles;
+  if (slot >= (unsigned)a.workers) return;
+  const int worker = nth_active_worker(a.active_mask, slot), t = logical - slot * a.tiles;
+  int l = 0;
+  for (int j = 1; j < a.n; ++j)
+    if (t >= a.layer[j].first) l = j;
+  const Layer& y = a.layer[l];
+  if constexpr (PLAIN) run_tile<false, false>(a, y, t - y.first, worker, lds);
+  else if (y.ry) run_tile<true, true>(a, y, t - y.first, worker, lds);
+  else run_tile<true, false>(a, y, t - y.first, worker, lds);
+}
+
+}  // namespace f32g
+
+// Meant for models whose weight gradients last about as long as a launch: 64 x 64 tiles of all layers and workers, times the samples.
+// Larger ones have the layers' own launches run beside the data gradients on the side stream.  Step of each, grouped / not:
+// 512-512-512-10, 16 workers of 64 samples (139 thousand) 187 / 201 us, 3072-1024-512-10, four of 64 (231) 236 / 241, 512-512-512-10, eight of
+// 256 or four of 512 (278) 207 / 197 and 201 / 191; first-order steps, four of 256 (139) 98 / 108, four of 512 (278) 142 / 142.
+bool wgrad_group_f32_ok(const dw_config& c) {
+  int64_t tiles = 0;
+  for (int l = 1; l <= c.n_layers; ++l) tiles += (int64_t)((c.dims[l] + 63) / 64) * ((c.dims[l - 1] + 63) / 64);
+  return tiles * c.k < 4096 && tiles * c.k * c.batch < 250000;
+}
+
+hipError_t launch_wgrad_group_f32(const GemmArgs* layers, int n, hipStream_t s) {
+  KernelScope ks(KC_GEMM_WGRAD, s);
+  f32g::Args a{};
+  a.n = n; a.B = layers[0].K; a.Pp = layers[0].c_wstride; a.active_mask = layers[0].active_mask;
+  a.workers = active_count(a.active_mask, layers[0].k);
+  a.g = reinterpret_cast<float*>(layers[0].C); a.hz = reinterpret_cast<float*>(layers[0].RC);
+  for (int j = 0; j < n; ++j) {
+    const GemmArgs& in = layers[j];
+    f32g::Layer& y = a.layer[j];
+    y.x = reinterpret_cast<const float*>(in.X); y.rx = reinterpret_cast<const float*>(in.RX);
+    y.y = reinterpret_cast<const float*>(in.Y); y.ry = reinterpret_cast<const float*>(in.RY);
+    y.x_wstride = in.x_wstride; y.y_wstride = in.y_wstride;
+    y.woff = reinterpret_cast<float*>(in.C) - a.g; y.boff = in.gb - a.g;         // (from the first layer's W)
+    y.ldx = in.ldx; y.M = in.M; y.N = in.N; y.tiles_m = (in.M + f32g::EDGE - 1) / f32g::EDGE;
+    y.first = a.tiles;
+    a.tiles += y.tiles_m * ((in.N + f32g::EDGE - 1) / f32g::EDGE);
+  }
+  const dim3 grid = xcd_grid((int64_t)a.tiles * a.workers);
+  const int smem = 3 * f32g::EDGE * kRowBytes * (layers[0].plain ? 2 : 4);       // 48 KB: three blocks to a compute unit
+  if (layers[0].plain) hipLaunchKernelGGL(f32g::wgrad_group_f32<true>, grid, dim3(f32g::NT), smem, s, a);
+  else hipLaunchKernelGGL(f32g::wgrad_group_f32<false>, grid, dim3(f32g::NT), smem, s, a);
+  return hipGetLastError();
 }
 
 // c = the sum over the slices of p[slice * step], rc the same of p[slice * step + second], added in slice order.  One load at
@@ -698,9 +908,10 @@ static hipError_t launch_instance(const GemmArgs& a, dim3 grid, hipStream_t s) {
 
 template <int BM, int BN, int WM, int WN>
 static hipError_t launch_shape(const GemmArgs& a, hipStream_t s) {
-  const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
+  const int64_t tiles = (int64_t)((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
   const bool sliced = a.ksplit > 1;
-  const dim3 grid((unsigned)tiles, (unsigned)active_count(a.active_mask, a.k), (unsigned)(sliced ? a.ksplit : 1));
+  const int workers = active_count(a.active_mask, a.k);
+  const dim3 grid = xcd_grid(tiles * (sliced ? a.ksplit : 1) * workers);
   const bool rx = a.RX != nullptr;
   hipError_t e;
 #define DW_GO(...) e = launch_instance<BM, BN, WM, WN, __VA_ARGS__>(a, grid, s)
@@ -739,7 +950,7 @@ static hipError_t launch_shape(const GemmArgs& a, hipStream_t s) {
   if (e != hipSuccess) return e;
   if (sliced) {
     const int64_t n_out = (int64_t)a.M * a.ldc;
-    hipLaunchKernelGGL(sum_slices_kernel, dim3((unsigned)((n_out + 255) / 256), grid.y), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(sum_slices_kernel, dim3((unsigned)((n_out + 255) / 256), (unsigned)workers), dim3(256), 0, s, a);
   }
   return hipGetLastError();
 }
@@ -749,7 +960,7 @@ static hipError_t launch_shape(const GemmArgs& a, hipStream_t s) {
 constexpr int kFuseBM = 64, kFuseBN = 128;
 template <int FM>
 static hipError_t launch_fused_wgrad_mode(const GemmArgs& a, hipStream_t s) {
-  const dim3 grid((unsigned)((a.M / kFuseBM) * (a.N / kFuseBN)), (unsigned)active_count(a.active_mask, a.k));
+  const dim3 grid = xcd_grid((int64_t)(a.M / kFuseBM) * (a.N / kFuseBN) * active_count(a.active_mask, a.k));
   if (a.RY) return launch_instance<kFuseBM, kFuseBN, 2, 2, false, false, true, RY_MEM, EPI_WGRAD_FUSED, FM>(a, grid, s);
   return launch_instance<kFuseBM, kFuseBN, 2, 2, false, false, true, RY_NONE, EPI_WGRAD_FUSED, FM>(a, grid, s);
 }

@@ -1,15 +1,16 @@
-// fp32 dual products of small models: forward products (and the data gradient through the output layer) with too few
-// 64 x 64 tiles to fill the chip.
+// fp32 dual products of small models: forward products and data gradients with too few 64 x 64 tiles to fill the chip.
 //
 // Same computation as dual_gemm_f32 (C = X*Y, RC = RX*Y + X*RY of Section IV-B's forward and backward passes, products in
 // three bf16 pieces).  Such a product lasts as long as the chain of its own latencies, so the contraction is cut among the
 // waves of a block instead of among blocks: a block owns a 32 x 32 tile, wave w of NW takes the k-steps of 32 number w, w + NW,
-// ... with its operands straight from memory (the lane that multiplies a row's or column's k loads them, splits them
-// and keeps the next step's loads in flight), nothing goes through LDS and no barrier is met until the waves' partial
-// tiles are added in order of w and leave with the epilogue.  Against the tiles in slices over blocks with a second
-// launch that adds the slices (four workers, 128 samples): 784 -> 512 14.4 + 6.0 us, 512 -> 512 14.4 + 6.0, through 10
-// classes 11.7; here 13.6, 14.4 and 9.4.  What bounds it is the way of a row's 128-byte lines, one per row and step, through L1
-// (k-steps of 16, half a line each: 28 us).
+// ..., and no barrier is met until the waves' partial tiles are added in order of w and leave with the epilogue.  A wave loads
+// whole 128-byte lines, eight lanes each (two steps in flight), and turns them in a region of LDS of its own so that a lane gets
+// the 16 k of the row it multiplies; k-major operands (W in the data gradient) come as 32 columns of 32 k and are read by columns.
+// Four workers, 128 samples: forward 784 -> 512 14.1 us, 512 -> 512 12.6 (each lane loading its own row, a line per lane and step:
+// 14.9 both), data gradient 512 -> 512 12.3 (64 x 64 tiles in slices and a launch that adds them 13.3 + 5.5), first-order 7.9 (8.7 + 4.8).
+// Where 12.6 us go, by clock readings in a block of eight waves: until the first loads are out 1.1 us, until they are all there 3,
+// the two steps of each wave 4.5 (splitting and multiplying by turns, two waves to a SIMD), joining the partial tiles 1.2, the rest
+// is launch and drain.  Loads arrive at 24 bytes a clock and compute unit, a third of what L1 passes on when it hits.
 #include <type_traits>
 
 #include "dw_internal.h"
@@ -20,100 +21,168 @@ namespace dw {
 namespace f32s {
 
 constexpr int kEdge = 32;
-
 constexpr int kStep = 32;                                    // k per step: half 0 of a wave has the first 16, half 1 the others
 constexpr int kLane = kStep / 2;
 
-// a lane's 16 k of one row (X, and Y when its k is contiguous: a row's 32 k are the 128 bytes of a cache line) or column
-// (k-major Y)
-struct Operand {
-  const float* p;                                            // k contiguous: the row; else the column at k = 0
-  // WHOLE: the step has all its k (loads without conditions go out together)
-  template <bool WHOLE>
-  __device__ __forceinline__ void load_row(float (&v)[kLane], int k, int K) const {
-#pragma unroll
-    for (int q = 0; q < kLane / 4; ++q) {
-      const float4 a = WHOLE || k + 4 * q < K ? *reinterpret_cast<const float4*>(p + k + 4 * q) : make_float4(0.f, 0.f, 0.f, 0.f);
-      v[4 * q] = a.x; v[4 * q + 1] = a.y; v[4 * q + 2] = a.z; v[4 * q + 3] = a.w;
-    }
-  }
-  template <bool WHOLE>
-  __device__ __forceinline__ void load_column(float (&v)[kLane], int k, int K, int ld) const {
-#pragma unroll
-    for (int j = 0; j < kLane; ++j) v[j] = WHOLE || k + j < K ? p[(int64_t)(k + j) * ld] : 0.f;
-  }
-};
+// 32 x 32 floats of an operand on their way through a wave's LDS.  In memory and in LDS lines of 32 floats: a row's 32 k (k
+// contiguous), or 32 columns of one k.
+// Rows: 16-byte unit u of row r sits at place u ^ (r & 7), so that eight rows' units of the same number use different banks.
+constexpr int kRowsFloats = kEdge * kStep;
+__device__ __forceinline__ int row_unit(int row, int unit) { return row * kStep + ((unit ^ (row & 7)) << 2); }
+// Columns: the second half's 16 k start 32 banks further on, so that the two halves of a wave read different banks
+constexpr int kColumnsFloats = kEdge * kStep + kEdge;
+__device__ __forceinline__ int column_line(int k) { return k * kEdge + (k >= kLane ? kEdge : 0); }
+
+constexpr int wave_floats(bool y_kc, bool has_rx, bool has_v) {
+  return kRowsFloats * (has_rx ? 2 : 1) + (y_kc ? kRowsFloats : kColumnsFloats + (has_v ? kStep : 0));
+}
+
+// what a wave has written to its region is there for its reads
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // HAS_V: the +-1 operand takes part (RC += X*V); FM == 1: the R-products alone (C is in memory from an earlier probe)
 template <int NW, bool Y_KC, bool HAS_RX, bool HAS_V, int EPI, int FM>
 __global__ __launch_bounds__(NW * 64) void short_gemm_f32(GemmArgs a) {
   constexpr bool HAS_C = FM != 1, HAS_R = HAS_RX || HAS_V;
-  const int worker = nth_active_worker(a.active_mask, blockIdx.y);
-  const int tiles_m = (a.M + kEdge - 1) / kEdge;
-  const int row0 = (blockIdx.x % tiles_m) * kEdge, col0 = (blockIdx.x / tiles_m) * kEdge;
+  const unsigned tiles_m = (a.M + kEdge - 1) / kEdge, tiles = tiles_m * ((a.N + kEdge - 1) / kEdge), logical = xcd_unit();
+  const unsigned slot = logical / tiles, tile = logical - slot * tiles;
+  if (slot >= (unsigned)active_count(a.active_mask, a.k)) return;
+  const int worker = nth_active_worker(a.active_mask, slot);
+  const int row0 = (tile % tiles_m) * kEdge, col0 = (tile / tiles_m) * kEdge;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, lhalf = lane >> 5;
+  const int line = lane >> 3, unit = lane & 7;               // loads: line 8 i + `line` of 32, 16-byte unit of the line
   const int K = a.K, steps = (K + kStep - 1) / kStep;
 
-  // rows and columns past the end repeat the last ones (never stored)
-  const int row = row0 + l32 < a.M ? row0 + l32 : a.M - 1, col = col0 + l32 < a.N ? col0 + l32 : a.N - 1;
-  const Operand X{reinterpret_cast<const float*>(a.X) + (int64_t)worker * a.x_wstride + (int64_t)row * a.ldx};
-  const Operand RX{HAS_RX ? reinterpret_cast<const float*>(a.RX) + (int64_t)worker * a.x_wstride + (int64_t)row * a.ldx : nullptr};
-  const Operand Y{reinterpret_cast<const float*>(a.Y) + (int64_t)worker * a.y_wstride + (Y_KC ? (int64_t)col * a.ldy : (int64_t)col)};
-  const uint32_t* zb = a.zbits + (int64_t)worker * a.z_stride;
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  float* Xl = lds + wave * wave_floats(Y_KC, HAS_RX, HAS_V);
+  float* RXl = Xl + kRowsFloats;
+  float* Yl = Xl + kRowsFloats * (HAS_RX ? 2 : 1);
+  uint32_t* Vl = reinterpret_cast<uint32_t*>(Yl + kColumnsFloats);
 
-  struct Step { float x[kLane], rx[kLane], y[kLane]; uint32_t v; };
-  auto load_step = [&](Step& s, int step, auto whole) {
+  // rows and columns past the end repeat the last ones (never stored); operands of a worker have fewer than 2^31 elements
+  const float* X = reinterpret_cast<const float*>(a.X) + (int64_t)worker * a.x_wstride;
+  const float* RX = HAS_RX ? reinterpret_cast<const float*>(a.RX) + (int64_t)worker * a.x_wstride : nullptr;
+  const float* Y = reinterpret_cast<const float*>(a.Y) + (int64_t)worker * a.y_wstride;
+  const uint32_t* zb = a.zbits + (int64_t)worker * a.z_stride;
+  int xo[4], yo[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = row0 + 8 * i + line, c = col0 + 8 * i + line;
+    xo[i] = (r < a.M ? r : a.M - 1) * a.ldx + unit * 4;
+    yo[i] = (c < a.N ? c : a.N - 1) * a.ldy + unit * 4;
+  }
+  const int ycol = col0 + unit * 4 < a.N ? col0 + unit * 4 : a.N - 4;           // k-major: this lane's four columns (N is a multiple of 4)
+  const int col = col0 + l32 < a.N ? col0 + l32 : a.N - 1;
+
+  struct Step { float4 x[4], rx[4], y[4]; uint32_t v0, v1; int sh; };
+  auto load_step = [&](Step& s, int k0, auto whole) {
     constexpr bool WHOLE = decltype(whole)::value;
-    const int k = step * kStep + lhalf * kLane;
-    X.template load_row<WHOLE>(s.x, k, K);
-    if (HAS_RX) RX.template load_row<WHOLE>(s.rx, k, K);
-    if (Y_KC) Y.template load_row<WHOLE>(s.y, k, K); else Y.template load_column<WHOLE>(s.y, k, K, a.ldy);
-    if (HAS_V) {
-      // bits of k past the end are not read: X is zero there
-      uint32_t v = 0;
+    const bool ok = WHOLE || k0 + unit * 4 < K;              // (K is a multiple of 4 where k is contiguous)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s.x[i] = ok ? *reinterpret_cast<const float4*>(X + xo[i] + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
+      if (HAS_RX) s.rx[i] = ok ? *reinterpret_cast<const float4*>(RX + xo[i] + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
       if (Y_KC) {
-        const int64_t o = a.z_off + (int64_t)col * a.ldy;    // groups of four bits lie in one word
-#pragma unroll
-        for (int q = 0; q < kLane / 4; ++q) {
-          const int64_t b = o + (WHOLE || k + 4 * q < K ? k + 4 * q : K - 4);
-          v |= ((zb[b >> 5] >> (b & 31)) & 0xFu) << (4 * q);
-        }
+        s.y[i] = ok ? *reinterpret_cast<const float4*>(Y + yo[i] + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
       } else {
-#pragma unroll
-        for (int j = 0; j < kLane; ++j) {
-          const int64_t b = a.z_off + (int64_t)(WHOLE || k + j < K ? k + j : K - 1) * a.ldy + col;
-          v |= ((zb[b >> 5] >> (b & 31)) & 1u) << j;
-        }
+        const int k = k0 + 8 * i + line;
+        s.y[i] = WHOLE || k < K ? *reinterpret_cast<const float4*>(Y + (int64_t)k * a.ldy + ycol) : make_float4(0.f, 0.f, 0.f, 0.f);
       }
-      s.v = v;
+    }
+    if (HAS_V) {
+      // the words that hold a lane's signs: 16 of its row (k contiguous), or 32 of line `l32` (the bits after the last are not
+      // read; X is zero for k past the end)
+      int64_t first, last;
+      if (Y_KC) {
+        const int k = k0 + lhalf * kLane, kf = WHOLE || k < K ? k : K - 4;
+        first = a.z_off + (int64_t)col * a.ldy + kf;
+        last = first + (WHOLE || kf + kLane <= K ? kLane : K - kf) - 1;
+      } else {
+        const int k = WHOLE || k0 + l32 < K ? k0 + l32 : K - 1;
+        first = a.z_off + (int64_t)k * a.ldy + col0;
+        last = first + (col0 + kEdge <= a.N ? kEdge : a.N - col0) - 1;
+      }
+      s.v0 = zb[first >> 5]; s.v1 = zb[last >> 5];
+      s.sh = (int)(first & 31);
     }
   };
   auto load = [&](Step& s, int step) {
-    if ((step + 1) * kStep <= K) load_step(s, step, std::true_type{});      // (uniform)
-    else load_step(s, step, std::false_type{});
+    if ((step + 1) * kStep <= K) load_step(s, step * kStep, std::true_type{});      // (uniform)
+    else load_step(s, step * kStep, std::false_type{});
+  };
+  // a step's lines into the wave's LDS; returns the signs of this lane's 16 k
+  auto turn = [&](const Step& s) {
+    wave_lds_fence();                                        // (the last step's reads are done)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int at = row_unit(8 * i + line, unit);
+      *reinterpret_cast<float4*>(Xl + at) = s.x[i];
+      if (HAS_RX) *reinterpret_cast<float4*>(RXl + at) = s.rx[i];
+      *reinterpret_cast<float4*>(Yl + (Y_KC ? at : column_line(8 * i + line) + unit * 4)) = s.y[i];
+    }
+    uint32_t v = 0;
+    if (HAS_V) {
+      v = __builtin_amdgcn_alignbit(s.v1, s.v0, s.sh);
+      if (!Y_KC && lhalf == 0) Vl[l32] = v;
+    }
+    wave_lds_fence();
+    if (HAS_V && !Y_KC) {
+      v = 0;
+#pragma unroll
+      for (int q = 0; q < kLane / 4; ++q) {
+        const uint4 w = *reinterpret_cast<const uint4*>(Vl + lhalf * kLane + 4 * q);
+        v |= ((w.x >> l32) & 1u) << (4 * q) | ((w.y >> l32) & 1u) << (4 * q + 1) | ((w.z >> l32) & 1u) << (4 * q + 2) | ((w.w >> l32) & 1u) << (4 * q + 3);
+      }
+    }
+    return v;
+  };
+  // eight of a lane's k, from number h on: of row, column l32
+  struct Operands { float x[8], rx[8], y[8]; };
+  auto read8 = [&](Operands& o, int h) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int at = row_unit(l32, lhalf * 4 + (h >> 2) + q);
+      auto get = [&](const float* l, float (&f)[8]) {
+        const float4 t = *reinterpret_cast<const float4*>(l + at);
+        f[4 * q] = t.x; f[4 * q + 1] = t.y; f[4 * q + 2] = t.z; f[4 * q + 3] = t.w;
+      };
+      get(Xl, o.x);
+      if (HAS_RX) get(RXl, o.rx);
+      if (Y_KC) {
+        get(Yl, o.y);
+      } else {
+#pragma unroll
+        for (int j = 4 * q; j < 4 * q + 4; ++j) o.y[j] = Yl[column_line(lhalf * kLane + h + j) + l32];
+      }
+    }
   };
   const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   floatx16 acc, racc, t, tr;
-  // eight of a lane's k, from number h on
-  auto multiply8 = [&](const Step& s, int h, auto whole) {
+  auto multiply8 = [&](int h, uint32_t signs, auto whole) {
+    Operands s;
+    read8(s, h);
     bf16x8 v;
     if (HAS_V) {
-      const uint32_t b = s.v >> h;
+      const uint32_t b = signs >> h;
       v = __builtin_bit_cast(bf16x8, make_uint4(sign_pair(b, b >> 1), sign_pair(b >> 2, b >> 3), sign_pair(b >> 4, b >> 5), sign_pair(b >> 6, b >> 7)));
     }
     if constexpr (decltype(whole)::value) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        if (HAS_C) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(s.x[h + j], s.y[h + j], acc, 0, 0, 0);
-        if (HAS_RX) racc = __builtin_amdgcn_mfma_f32_32x32x2f32(s.rx[h + j], s.y[h + j], racc, 0, 0, 0);
-        if (HAS_V) racc = __builtin_amdgcn_mfma_f32_32x32x2f32(s.x[h + j], (float)v[j] * (1.f / kScale), racc, 0, 0, 0);
+        if (HAS_C) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(s.x[j], s.y[j], acc, 0, 0, 0);
+        if (HAS_RX) racc = __builtin_amdgcn_mfma_f32_32x32x2f32(s.rx[j], s.y[j], racc, 0, 0, 0);
+        if (HAS_V) racc = __builtin_amdgcn_mfma_f32_32x32x2f32(s.x[j], (float)v[j] * (1.f / kScale), racc, 0, 0, 0);
       }
     } else {
-      auto pieces = [&](const float (&f)[kLane], bf16x8 (&o)[3]) {
+      auto pieces = [&](const float (&f)[8], bf16x8 (&o)[3]) {
         uint32_t p[3][4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) split_pair<false>(f[h + 2 * q], f[h + 2 * q + 1], p[0][q], p[1][q], p[2][q]);
+        for (int q = 0; q < 4; ++q) split_pair<false>(f[2 * q], f[2 * q + 1], p[0][q], p[1][q], p[2][q]);
 #pragma unroll
         for (int c = 0; c < 3; ++c) o[c] = __builtin_bit_cast(bf16x8, make_uint4(p[c][0], p[c][1], p[c][2], p[c][3]));
       };
@@ -129,17 +198,33 @@ __global__ __launch_bounds__(NW * 64) void short_gemm_f32(GemmArgs a) {
       }
     }
   };
-  auto multiply = [&](const Step& s, auto whole) { multiply8(s, 0, whole); multiply8(s, 8, whole); };
+  auto multiply = [&](uint32_t signs, auto whole) { multiply8(0, signs, whole); multiply8(8, signs, whole); };
   auto contract = [&](auto whole) {
     acc = zero; racc = zero; t = zero; tr = zero;
-    Step s[2];
-    if (wave < steps) load(s[0], wave);
-    for (int i = wave; i < steps; i += 2 * NW) {
-      if (i + NW < steps) load(s[1], i + NW);
-      multiply(s[0], whole);
-      if (i + NW < steps) {
-        if (i + 2 * NW < steps) load(s[0], i + 2 * NW);
-        multiply(s[1], whole);
+    Step s0, s1;
+    const int n = wave < steps ? (steps - wave + NW - 1) / NW : 0;         // steps of this wave (uniform)
+    if constexpr (decltype(whole)::value) {
+      for (int i = 0; i < n; ++i) { load(s0, wave + i * NW); multiply(turn(s0), whole); }
+    } else if (n == 1) {
+      load(s0, wave);
+      multiply(turn(s0), whole);
+    } else if (n > 1) {
+      // two steps in flight, and no condition between their loads: the wait for the older step then leaves the younger one's out
+      load(s0, wave); load(s1, wave + NW);
+      auto next = [&](Step& r, int i) {                      // step i of the wave, and ask for step i + 2
+        const uint32_t signs = turn(r);
+        load(r, wave + (i + 2) * NW);
+        multiply(signs, whole);
+      };
+      int i = 0;
+      for (; i + 3 < n; i += 2) { next(s0, i); next(s1, i + 1); }
+      if (i + 2 < n) {                                       // three left
+        next(s0, i);
+        multiply(turn(s1), whole);
+        multiply(turn(s0), whole);
+      } else {
+        multiply(turn(s0), whole);
+        multiply(turn(s1), whole);
       }
     }
     bool finite = true;
@@ -152,7 +237,8 @@ __global__ __launch_bounds__(NW * 64) void short_gemm_f32(GemmArgs a) {
   if (K < kWholeBelow || __syncthreads_or(contract(std::false_type{}))) contract(std::true_type{});    // (see dw_f32_pieces.h)
 
   // partial tiles: [wave][C, RC][32][32]; lane holds column l32, rows (r/4)*8 + lhalf*4 + r%4
-  extern __shared__ __attribute__((aligned(16))) float part[];
+  __syncthreads();                                           // (the waves' regions of LDS)
+  float* part = lds;
   constexpr int kTile = kEdge * kEdge, kSets = (HAS_C ? 1 : 0) + (HAS_R ? 1 : 0);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
@@ -196,47 +282,50 @@ __global__ __launch_bounds__(NW * 64) void short_gemm_f32(GemmArgs a) {
 
 template <int NW, bool Y_KC, bool HAS_RX, bool HAS_V, int EPI, int FM>
 static hipError_t launch(const GemmArgs& a, hipStream_t s) {
-  constexpr int smem = NW * ((FM != 1 ? 1 : 0) + (HAS_RX || HAS_V ? 1 : 0)) * kEdge * kEdge * (int)sizeof(float);
+  constexpr int parts = ((FM != 1 ? 1 : 0) + (HAS_RX || HAS_V ? 1 : 0)) * kEdge * kEdge, turns = wave_floats(Y_KC, HAS_RX, HAS_V);
+  constexpr int smem = NW * (parts > turns ? parts : turns) * (int)sizeof(float);
   auto kern = short_gemm_f32<NW, Y_KC, HAS_RX, HAS_V, EPI, FM>;
   if (smem > 64 * 1024) {
     static LdsLimitOnce lim;
     const hipError_t e = lim.raise(reinterpret_cast<const void*>(kern), smem);
     if (e != hipSuccess) return e;
   }
-  const unsigned tiles = (unsigned)(((a.M + kEdge - 1) / kEdge) * ((a.N + kEdge - 1) / kEdge));
-  hipLaunchKernelGGL(kern, dim3(tiles, (unsigned)active_count(a.active_mask, a.k)), dim3(NW * 64), smem, s, a);
+  const int64_t tiles = (int64_t)((a.M + kEdge - 1) / kEdge) * ((a.N + kEdge - 1) / kEdge);
+  hipLaunchKernelGGL(kern, xcd_grid(tiles * active_count(a.active_mask, a.k)), dim3(NW * 64), smem, s, a);
   return hipGetLastError();
 }
 
 }  // namespace f32s
 
-// A forward product of M x N outputs and contraction K for each of k workers (the layout asks as well: such a product needs no
-// slices).  Against the 64 x 64 tiles, in slices where there are few of them, as the step of models K-N-10 here / there:
-//   K      up to 1152: faster or even (784-512, four workers of 128 samples: 76 / 82 us; 1036-340, five of 93: 77 / 83; 1036-256, two
-//          of 128: 67 / 72; 1036-256, six of 256: 97 / 96).  Longer ones take too long block by block (4096-64, one of 64: the
-//          product 50 / 18 us, the step 89 / 68; 1280-256, six of 256: 108 / 104) unless one block each is what most compute units
-//          get, 40 to 64 tiles, four blocks to a tile: then up to 2048 (1280-512, four of 128: 87 / 98; 2048-512: 111 / 116; at 4096 163 / 157)
-//   tiles  up to 128 of them as above; from there to 256 even at whole sizes (512-1024, three of 256: 108 / 103; 512-640, two of 512:
-//          113 / 111) and still faster where the tiles hang over the edge (512-1036, five of 93: 101 / 111) and in first-order
-//          steps (69 / 79); more of them fill the chip
+// A product of M x N outputs and contraction K for each of k workers (the layout asks as well: such a product needs no slices).
+// Against the 64 x 64 tiles, in slices where there are few of them, as the step here / there:
+//   K      up to 1152: faster or even at any number of tiles (128-128, two workers of 64 samples 38 / 74 us, all its products; 1036-340, five
+//          of 93 75 / 92).  Longer ones block by block take too long where few blocks walk them (4096-64, one of 64, one tile:
+//          61 / 48; data gradient 1500 -> 256, two of 64, eight: 123 / 110) and less from 32 tiles on, four blocks to a tile
+//          (1280-256, six of 256, 96 tiles: 92 / 96; 3072-512, four of 128, 64: 141 / 154; 3072-1024, two of 64, 32: 168 / 174)
+//          and not more than 128 (1200-1200-1200, three of 200, 228 tiles: 388 / 330)
+//   tiles  up to 256 of them (1100-1100, three of 200, 228: 156 / 164); more of them fill the chip and share their operands among more
+//          outputs (512-1024, four of 256, 256 tiles: 119 / 106; 784-768, six of 300, 360: 175 / 145)
 bool gemm_f32_short_shape(int64_t M, int64_t N, int64_t K, int k) {
   const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64) * k;
-  return tiles < 256 && K <= (tiles >= 40 && tiles <= 64 ? 2048 : 1152);
+  return tiles < 256 && K <= (tiles >= 32 && tiles <= 128 ? 4096 : 1152);
 }
 
-// Forward product, or data gradient through a layer of at most 32 outputs (the classes), of matrices in memory, no slices,
-// whose 64 x 64 tiles over all workers would leave compute units idle.  Longer data gradients stay with the tiles: their
-// k-major operand comes in 4-byte loads here (512 -> 512: 24 us against 11.7 + 6.0).  (Whichever workers are active: the
-// choice must not depend on who steps.)
+// Forward product or data gradient of matrices in memory, no slices, whose 64 x 64 tiles over all workers would leave compute
+// units idle.  (Whichever workers are active: the choice must not depend on who steps.)
 bool gemm_f32_short_ok(const GemmArgs& a) {
   if (a.x_view != VIEW_NONE || a.y_view != VIEW_NONE || a.ksplit > 1 || !(a.ry_bits || a.plain)) return false;
-  if (a.epi == EPI_MASK ? a.K > f32s::kStep || (!a.plain && !a.RX) : a.epi != EPI_RELU) return false;
+  if (a.epi == EPI_MASK ? !a.plain && !a.RX : a.epi != EPI_RELU) return false;
   return gemm_f32_short_shape(a.M, a.N, a.K, a.k);
 }
 
 template <int NW>
-static hipError_t launch_forward(const GemmArgs& a, hipStream_t s) {
+static hipError_t launch_short(const GemmArgs& a, hipStream_t s) {
   using namespace f32s;
+  if (a.epi == EPI_MASK) {
+    if (a.plain) return launch<NW, false, false, false, EPI_MASK, 0>(a, s);
+    return a.r_only ? launch<NW, false, true, true, EPI_MASK, 1>(a, s) : launch<NW, false, true, true, EPI_MASK, 0>(a, s);
+  }
   const bool rx = a.RX != nullptr;
   if (a.plain) return launch<NW, true, false, false, EPI_RELU, 0>(a, s);
   if (a.r_only) return rx ? launch<NW, true, true, true, EPI_RELU, 1>(a, s) : launch<NW, true, false, true, EPI_RELU, 1>(a, s);
@@ -244,14 +333,9 @@ static hipError_t launch_forward(const GemmArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_gemm_f32_short(const GemmArgs& a, hipStream_t s) {
-  using namespace f32s;
   KernelScope ks(a.epi == EPI_MASK ? KC_GEMM_DGRAD : KC_GEMM_FWD, s);
-  if (a.epi == EPI_MASK) {
-    // one step, the first wave's; the others only help to write the tile (two waves 8.8 us, one 11.0)
-    if (a.plain) return launch<2, false, false, false, EPI_MASK, 0>(a, s);
-    return a.r_only ? launch<2, false, true, true, EPI_MASK, 1>(a, s) : launch<2, false, true, true, EPI_MASK, 0>(a, s);
-  }
-  return a.K > 2 * kStep ? launch_forward<8>(a, s) : launch_forward<2>(a, s);
+  // (up to 64 k: a step each for two waves, or one for the first; the second then only helps to write the tile: 8.8 us, alone 11.0)
+  return a.K > 2 * f32s::kStep ? launch_short<8>(a, s) : launch_short<2>(a, s);
 }
 
 }  // namespace dw

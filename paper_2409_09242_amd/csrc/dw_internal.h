@@ -223,6 +223,19 @@ __device__ __forceinline__ int nth_active_worker(uint64_t mask, int j) {
   return __builtin_ctzll(mask);
 }
 
+// Blocks go to the eight XCDs in turn, and each XCD has an L2 of its own: what blocks on several of them read comes from memory once
+// for each.  A launch whose blocks share operands is numbered so that every XCD works through consecutive units.  `units` of
+// them: the grid (a dimension holds fewer than 2^32 threads), and a block's number (units and more: nothing to do).
+inline dim3 xcd_grid(int64_t units) {
+  constexpr int64_t kRow = 1 << 21;                          // (a multiple of eight)
+  const int64_t n = (units + 7) / 8 * 8;
+  return n <= kRow ? dim3((unsigned)n) : dim3((unsigned)kRow, (unsigned)((n + kRow - 1) / kRow));
+}
+__device__ __forceinline__ unsigned xcd_unit() {
+  const unsigned b = blockIdx.y * gridDim.x + blockIdx.x;
+  return (b & 7u) * ((gridDim.x * gridDim.y) >> 3) + (b >> 3);
+}
+
 // Raises the dynamic-LDS limit of a kernel the first time it is launched on a device (the attribute belongs to the
 // device's code object).  One instance per kernel instantiation, as a function-local static of its launcher.  Host
 // threads may race to the first launch: the flag is atomic and setting the attribute twice is harmless.
@@ -241,8 +254,11 @@ struct LdsLimitOnce {
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s);
 bool gemm_f32_short_ok(const GemmArgs& a);                       // small-model kernel usable and meant for this product?
-bool gemm_f32_short_shape(int64_t M, int64_t N, int64_t K, int k);   // the part of the answer that a forward product's sizes give
+bool gemm_f32_short_shape(int64_t M, int64_t N, int64_t K, int k);   // the part of the answer that the sizes give
 hipError_t launch_gemm_f32_short(const GemmArgs& a, hipStream_t s);
+// the weight gradients (EPI_WGRAD, not fused) of n layers of a small fp32 MLP in one launch; meant for this model?
+bool wgrad_group_f32_ok(const dw_config& cfg);
+hipError_t launch_wgrad_group_f32(const GemmArgs* layers, int n, hipStream_t s);
 // can the bf16 weight-gradient kernel of a layer W[n_out][n_in] (bit/parameter offset woff) apply the update itself,
 // and how many partial-sum slots (tiles) does it then write per worker when a step has n_samples Hutchinson probes?
 bool gemm_bf16_wgrad_fusable(int n_out, int n_in, int k, int avg_block, float hpow, int64_t woff);
@@ -293,7 +309,8 @@ struct Layout {            // byte offsets into the workspace, all multiples of 
   size_t zbits_p = 0, ract_p[DW_MAX_LAYERS] = {0}, rdelta_p[DW_MAX_LAYERS] = {0};
   int fwdSplit[DW_MAX_LAYERS] = {0};   // fp32: slices of layer l+1's forward contraction (0 or 1: not cut)
   int dgSplit[DW_MAX_LAYERS] = {0};    // fp32: slices of the data gradient through W_{l+1} (0 or 1: not cut)
-  bool overlap_wgrad = false;          // small model without fused layers: weight gradients on the handle's side stream
+  bool group_wgrad = false;            // small fp32 model without fused layers: all weight gradients in one launch
+  bool overlap_wgrad = false;          // small bf16 model without fused layers: weight gradients on the handle's side stream
   int fuse_base[DW_MAX_LAYERS] = {0};  // first partial-sum slot of layer l+1's fused weight gradient, -1: not fused
   int n_fuse_slots = 0;
   size_t partials_f = 0;              // [k][n_fuse_slots] doubles

@@ -170,7 +170,7 @@ int run_network(const dw_config& cfg, char* ws, const Layout& lay, const void* d
       dl = ws + lay.delta[l]; rdl = rdelta_buf(l); ldd = cfg.dims[l]; dstride = act_stride(l);
     }
   };
-  auto weight_gradient = [&](int l, hipStream_t st) -> hipError_t {   // and its R-companion: contraction over the minibatch
+  auto weight_gradient_args = [&](int l) -> GemmArgs {   // and its R-companion: contraction over the minibatch
     const void* dl; const void* rdl; int ldd; int64_t dstride;
     delta_of(l, dl, rdl, ldd, dstride);
     GemmArgs a{};
@@ -183,10 +183,14 @@ int run_network(const dw_config& cfg, char* ws, const Layout& lay, const void* d
     a.gb = g + lay.boff[l - 1]; a.hzb = hz + lay.boff[l - 1];
     a.epi = EPI_WGRAD; a.k = k; a.active_mask = active;
     if (plain) { a.plain = 1; a.RX = nullptr; a.RY = nullptr; }
+    return a;
+  };
+  auto weight_gradient = [&](int l, hipStream_t st) -> hipError_t {
+    GemmArgs a = weight_gradient_args(l);
     if (fuse != nullptr && lay.fuse_base[l - 1] >= 0 && keep) {
       // left to the later probe's launch; the bias part of this probe's Hz is the column sum of Rd_l
       KernelScope ks(KC_GEMM_WGRAD, st);
-      return launch_col_sums_bf16(reinterpret_cast<const uint16_t*>(rdl), B, cfg.dims[l], hz + lay.boff[l - 1], lay.Pp, k,
+      return launch_col_sums_bf16(reinterpret_cast<const uint16_t*>(a.RX), B, cfg.dims[l], hz + lay.boff[l - 1], lay.Pp, k,
                                   active, st);
     }
     if (fuse != nullptr && lay.fuse_base[l - 1] >= 0) {
@@ -249,6 +253,11 @@ int run_network(const dw_config& cfg, char* ws, const Layout& lay, const void* d
       if ((e = gemm(a)) != hipSuccess) return DW_ERR_HIP;
     }
     if (overlap && l - 1 >= 2 && fork_wgrad(l - 1) != hipSuccess) return DW_ERR_HIP;
+  }
+  if (lay.group_wgrad) {
+    GemmArgs all[DW_MAX_LAYERS];
+    for (int l = 1; l <= L; ++l) all[l - 1] = weight_gradient_args(l);
+    return launch_wgrad_group_f32(all, L, s) == hipSuccess ? DW_OK : DW_ERR_HIP;
   }
   // weight gradients (with the side stream: only the first layer's is left; then the caller's stream waits for the others)
   for (int l = overlap ? 1 : L; l >= 1; --l)
