@@ -162,6 +162,11 @@ int validate(const dw_config* c, Layout* lay) {
       if (j == 0) lay->cP[j] = take((size_t)k * M * lay->cK[j] * 4);   // (the later convolutions read the map itself)
       const size_t out = (size_t)k * M * lay->cC[j + 1] * 4;
       lay->cA[j] = take(out); lay->cRA[j] = take(out); lay->cD[j] = take(out); lay->cRD[j] = take(out);
+      lay->cSlab[j] = j > 0 && conv_f32_ok(lay->cH[j], lay->cW[j], lay->cC[j], lay->cC[j + 1]);
+      if (lay->cSlab[j]) {
+        lay->cFragF[j] = take((size_t)k * conv_f32_frag_bytes(lay->cC[j + 1], lay->cC[j]));
+        lay->cFragG[j] = take((size_t)k * conv_f32_frag_bytes(lay->cC[j], lay->cC[j + 1]));
+      }
     }
     // weight gradients of the convolutions contract over all output positions of the minibatch and have few output
     // tiles: cut the contraction so that about 1024 blocks exist, slices of at least 512 positions

@@ -167,6 +167,16 @@ int run_network_cnn(const dw_config& cfg, char* ws, const Layout& lay, const voi
   auto rows = [&](int j) { return (int64_t)B * lay.cH[j + 1] * lay.cW[j + 1]; };   // patches / output positions of convolution j
   hipError_t e;
 
+  auto on_slabs = [&](int j) {
+    ConvF32 c{};
+    c.cv.H = lay.cH[j]; c.cv.W = lay.cW[j]; c.cv.Cin = lay.cC[j]; c.cv.Cout = lay.cC[j + 1];
+    c.B = B; c.k = k; c.active_mask = active;
+    c.w = theta + lay.cwoff[j]; c.w_wstride = lay.Pp; c.bias = theta + lay.cboff[j];
+    c.zbits = zbits; c.z_stride = z_stride; c.z_off = lay.cwoff[j]; c.zb_off = lay.cboff[j];
+    c.fwd_frags = ws + lay.cFragF[j]; c.grad_frags = ws + lay.cFragG[j];
+    return c;
+  };
+
   // forward through the convolutions
   for (int j = 0; j < nc; ++j) {
     const float* in = j == 0 ? reinterpret_cast<const float*>(d_x) : f(lay.cA[j - 1]);
@@ -182,6 +192,12 @@ int run_network_cnn(const dw_config& cfg, char* ws, const Layout& lay, const voi
         hipLaunchKernelGGL(im2col3x3_kernel<1>, dim3(blocks_for(M * lay.cK[j]), (unsigned)k), dim3(256), 0, s, in, rin,
                            f(lay.cP[j]), nullptr, B, lay.cH[j], lay.cW[j], lay.cC[j], lay.cK[j], active);
       if ((e = hipGetLastError()) != hipSuccess) return DW_ERR_HIP;
+    }
+    if (lay.cSlab[j]) {
+      ConvF32 c = on_slabs(j);
+      c.in = in; c.rin = rin; c.out = f(lay.cA[j]); c.rout = f(lay.cRA[j]);
+      if (launch_conv_f32_frags(c, s) != hipSuccess || launch_conv_f32(c, true, s) != hipSuccess) return DW_ERR_HIP;
+      continue;
     }
     GemmArgs a{};
     if (j == 0) {
@@ -251,7 +267,11 @@ int run_network_cnn(const dw_config& cfg, char* ws, const Layout& lay, const voi
       if ((e = launch_gemm_f32(a, s)) != hipSuccess) return DW_ERR_HIP;
     }
     if (j == 0) break;
-    {
+    if (lay.cSlab[j]) {
+      ConvF32 c = on_slabs(j);
+      c.in = f(lay.cD[j]); c.rin = f(lay.cRD[j]); c.out = f(lay.cD[j - 1]); c.rout = f(lay.cRD[j - 1]); c.mask = f(lay.cA[j - 1]);
+      if (launch_conv_f32(c, false, s) != hipSuccess) return DW_ERR_HIP;
+    } else {
       // dA[q][ci] = sum over (tap, co) of D[q - tap][co] * W[co][tap][ci] for every position q of the map below
       GemmArgs a{};
       a.X = f(lay.cD[j]); a.RX = f(lay.cRD[j]); a.x_wstride = M * lay.cC[j + 1]; a.x_kcontig = 1; a.x_view = VIEW_SHIFTED;

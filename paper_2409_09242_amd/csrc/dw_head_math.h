@@ -64,8 +64,15 @@ template <int CTRL>
 __device__ __forceinline__ float row_move(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
 }
-// the sum and the largest of a row's 16, the same bits in all its lanes
-__device__ __forceinline__ float row_sum(float x) {
+// the sum (in 64 bits: rounded once, whichever order) and the largest of a row's 16, the same bits in all its lanes
+template <int CTRL>
+__device__ __forceinline__ double row_move(double x) {
+  const uint2 u = __builtin_bit_cast(uint2, x);
+  return __builtin_bit_cast(double, make_uint2((uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.x, CTRL, 0xF, 0xF, false),
+                                               (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.y, CTRL, 0xF, 0xF, false)));
+}
+__device__ __forceinline__ double row_sum(float f) {
+  double x = (double)f;
   x += row_move<kRowTurn + 8>(x); x += row_move<kRowTurn + 4>(x); x += row_move<kRowTurn + 2>(x);
   return x + row_move<kRowTurn + 1>(x);
 }
@@ -94,10 +101,11 @@ __device__ __forceinline__ void head_lanes(float s, float rs, int n, int y, int 
   const int amax = mx > -INFINITY ? __builtin_ctz(at_max) : 0;         // the first one
   const float e = n < C ? expf(s - mx) : 0.f;
   // sums that leave the largest term, exactly 1, or the label's out, as in head_row
-  rest = row_sum(n == amax ? 0.f : e);
-  const float rest_y = row_sum(n == y ? 0.f : e);
-  sy = row_sum(n == y ? s - mx : 0.f);
-  const float inv = 1.0f / (1.0f + rest), p = e * inv;
+  const double others = row_sum(n == amax ? 0.f : e);
+  rest = (float)others;
+  const float rest_y = (float)row_sum(n == y ? 0.f : e);
+  sy = (float)row_sum(n == y ? s - mx : 0.f);
+  const float inv = 1.0f / (float)(1.0 + others), p = e * inv;
   const float ctr = row_centred(p, rs, std::make_integer_sequence<int, DW_MAX_CLASSES>{});
   d = n < C ? (n == y ? -(rest_y * inv) : p) * invB : 0.f;
   rd = n < C ? p * ctr * invB : 0.f;

@@ -253,6 +253,19 @@ struct LdsLimitOnce {
 
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s);
+// A 3x3 convolution on slabs of the map in LDS (dw_conv_f32.hip), workers in order of the active ones.
+struct ConvF32 {
+  ConvView cv; int B, k; uint64_t active_mask;
+  const float* in; const float* rin;                    // the map (forward) or the gradient map, worker 0, and its companion
+  float* out; float* rout; const float* mask;           // mask: data gradient, keep where mask > 0
+  const float* w; int64_t w_wstride; const float* bias; // theta + offset of W and of the bias (stride w_wstride)
+  const uint32_t* zbits; int64_t z_stride, z_off, zb_off;
+  char* fwd_frags; char* grad_frags;                    // conv_f32_frag_bytes(Cout, Cin) and (Cin, Cout) per worker
+};
+bool conv_f32_ok(int H, int W, int Cin, int Cout);      // do slabs of such maps fit?
+size_t conv_f32_frag_bytes(int N, int C);
+hipError_t launch_conv_f32_frags(const ConvF32& c, hipStream_t s);   // the weights of both directions; then:
+hipError_t launch_conv_f32(const ConvF32& c, bool forward, hipStream_t s);
 bool gemm_f32_short_ok(const GemmArgs& a);                       // small-model kernel usable and meant for this product?
 bool gemm_f32_short_shape(int64_t M, int64_t N, int64_t K, int k);   // the part of the answer that the sizes give
 hipError_t launch_gemm_f32_short(const GemmArgs& a, hipStream_t s);
@@ -323,6 +336,8 @@ struct Layout {            // byte offsets into the workspace, all multiples of 
   size_t cA[DW_MAX_CONV] = {0}, cRA[DW_MAX_CONV] = {0};         // outputs a_j, Ra_j [k][M_j][C_j]
   size_t cD[DW_MAX_CONV] = {0}, cRD[DW_MAX_CONV] = {0};         // their gradients
   int cSplit[DW_MAX_CONV] = {0};                                // slices of the weight gradient's contraction (1: none)
+  bool cSlab[DW_MAX_CONV] = {false};                            // products on slabs of the map (else patches as operand views)
+  size_t cFragF[DW_MAX_CONV] = {0}, cFragG[DW_MAX_CONV] = {0};  // their weights, forward and data gradient
   size_t cPart = 0, cPartB = 0;                                 // scratch of the sliced weight gradients
   size_t pool = 0, rpool = 0, dpool = 0, rdpool = 0, pidx = 0;  // pooled map [k][B][d_0] (+R, gradients), selection bytes
   size_t partials = 0, u_ring = 0, score = 0, omh1 = 0, h2 = 0, loss = 0;
