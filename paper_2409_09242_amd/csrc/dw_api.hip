@@ -190,34 +190,28 @@ int validate(const dw_config* c, Layout* lay) {
   if (L > 0 && c->dtype == DW_F32) {
     // fp32 forward products of hidden layers with a long contraction and a handful of output tiles (the first linear
     // layer behind a convolutional front end) that the small-model kernel does not take: same cut, slices of at least 64
+    // (the small-model kernel takes more of these shapes than scratch is left out for: a workspace's size does not
+    // depend on which of the two kernels is the faster one)
     const int64_t B = c->batch;
-    for (int l = 1; l < L; ++l) {
-      const int64_t n = c->dims[l], kk = c->dims[l - 1];
+    auto cut = [&](int64_t n, int64_t kk, bool reserved) {       // slices of a product of B x n outputs
       const int64_t tiles = n <= 32 ? (B + 127) / 128 : B <= 32 ? (n + 127) / 128 : ((B + 63) / 64) * ((n + 63) / 64);
-      int64_t split = tiles * k < 256 && !gemm_f32_short_shape(B, n, kk, k) ? 1024 / (tiles * k) : 1;
+      int64_t split = tiles * k < 256 ? 1024 / (tiles * k) : 1;
       if (split > kk / 64) split = kk / 64;
       if (split > 64) split = 64;
-      lay->fwdSplit[l - 1] = (int)(split < 1 ? 1 : split);
-      if (lay->fwdSplit[l - 1] > 1) {
-        const size_t need = (size_t)lay->fwdSplit[l - 1] * k * 2 * B * n * 4;
+      if (split > 1 && reserved) {
+        const size_t need = (size_t)split * k * 2 * B * n * 4;
         part = need > part ? need : part;
       }
+      return split > 1 && !gemm_f32_short_shape(B, n, kk, k) ? (int)split : 1;
+    };
+    for (int l = 1; l < L; ++l) {
+      const int64_t n = c->dims[l], kk = c->dims[l - 1], tiles = ((B + 63) / 64) * ((n + 63) / 64) * k;
+      lay->fwdSplit[l - 1] = cut(n, kk, tiles >= 256 || kk > (tiles >= 40 && tiles <= 64 ? 2048 : 1152));
     }
     const size_t head = out_head_f32_slice_bytes(B, c->dims[L - 1], k);
     part = head > part ? head : part;
     // and the data gradients through W_l (B x d_{l-1} outputs, contraction d_l) of the same kind
-    for (int l = 2; l <= L; ++l) {
-      const int64_t n = c->dims[l - 1], kk = c->dims[l];
-      const int64_t tiles = n <= 32 ? (B + 127) / 128 : B <= 32 ? (n + 127) / 128 : ((B + 63) / 64) * ((n + 63) / 64);
-      int64_t split = tiles * k < 256 && !gemm_f32_short_shape(B, n, kk, k) ? 1024 / (tiles * k) : 1;
-      if (split > kk / 64) split = kk / 64;
-      if (split > 64) split = 64;
-      lay->dgSplit[l - 1] = (int)(split < 1 ? 1 : split);
-      if (lay->dgSplit[l - 1] > 1) {
-        const size_t need = (size_t)lay->dgSplit[l - 1] * k * 2 * B * n * 4;
-        part = need > part ? need : part;
-      }
-    }
+    for (int l = 2; l <= L; ++l) lay->dgSplit[l - 1] = cut(c->dims[l - 1], c->dims[l], true);
   }
   if (part > 0) { lay->cPart = take(part); lay->cPartB = take(part_b > 0 ? part_b : 256); }
   lay->partials = take((size_t)k * lay->n_upd_blocks * sizeof(double));
