@@ -11,10 +11,11 @@
 // are the three products of Section IV-B's Hessian-vector product with B*(H-2)*(W-2) rows instead of B.  ReLU and
 // max-pool pass the directional derivative through their selections (their curvature is zero almost everywhere).
 // Only the first convolution (one input channel in the paper's model: 9 columns) has its patch matrix in memory.
-// The others read the map itself: the GEMM's loader takes the patch matrix as a view of the map (OperandView), and
-// the data gradient is the same product written from the input positions' side, dA = sum over taps of the shifted
-// gradient map times W's tap, so that the nine contributions of a map entry are added inside the contraction and
-// no patch-shaped gradient is ever stored.
+// The others read the map itself, and their data gradient is the same product written from the input positions' side,
+// dA = sum over taps of the shifted gradient map times W's tap, so that the nine contributions of a map entry are added
+// inside the contraction and no patch-shaped gradient is ever stored.  Forward and data gradient run on slabs of the map
+// in LDS that all nine taps share (dw_conv_f32.hip) where conv_f32_ok; the weight gradient, and the shapes that kernel
+// does not take, on the GEMM, whose loader takes the patch matrix as a view of the map (OperandView).
 // This file holds the data movement around those products (patch extraction for the first convolution, pooling and
 // its adjoint, the 3x3 window mean of the Hutchinson estimate) and the order of the launches.
 #include "dw_internal.h"

@@ -323,7 +323,7 @@ struct Layout {            // byte offsets into the workspace, all multiples of 
   int fwdSplit[DW_MAX_LAYERS] = {0};   // fp32: slices of layer l+1's forward contraction (0 or 1: not cut)
   int dgSplit[DW_MAX_LAYERS] = {0};    // fp32: slices of the data gradient through W_{l+1} (0 or 1: not cut)
   bool group_wgrad = false;            // small fp32 model without fused layers: all weight gradients in one launch
-  bool overlap_wgrad = false;          // small bf16 model without fused layers: weight gradients on the handle's side stream
+  bool overlap_wgrad = false;          // small model without fused layers or grouped weight gradients: they go to the handle's side stream
   int fuse_base[DW_MAX_LAYERS] = {0};  // first partial-sum slot of layer l+1's fused weight gradient, -1: not fused
   int n_fuse_slots = 0;
   size_t partials_f = 0;              // [k][n_fuse_slots] doubles

@@ -13,7 +13,7 @@
 // instruction, a wave each, in chains of at most a quarter of the contraction (TileSums); four k of an operand come with
 // one LDS read.  A thread owns up to four groups of four consecutive parameters: it loads a group, draws its four signs from the stream
 // (no sign words pass through LDS), puts both into LDS and applies the group's update at the end; the loads of the update go
-// out with the first ones.  Barriers wait for LDS alone.  32-64-10, four workers of 16 samples: kernel 20.7 -> 11.7 us, 2 of them
+// out with the first ones.  Barriers wait for LDS alone.  32-64-10, four workers of 16 samples: kernel 20.7 -> 12.2 us, 2 of them
 // until the first loads are there (products as multiply-add loops, one output per thread with 4-byte reads and one sample per thread in
 // the head: 20.7; four samples a thread, 16-byte reads and 16 lanes per sample: 12.4).
 //
