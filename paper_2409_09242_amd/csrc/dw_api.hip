@@ -159,7 +159,14 @@ int validate(const dw_config* c, Layout* lay) {
     const int64_t B = c->batch;
     for (int j = 0; j < lay->n_conv; ++j) {
       const size_t M = (size_t)B * lay->cH[j + 1] * lay->cW[j + 1];
-      if (j == 0) lay->cP[j] = take((size_t)k * M * lay->cK[j] * 4);   // (the later convolutions read the map itself)
+      if (j == 0) {
+        ConvF32 first{};
+        first.cv.H = lay->cH[0]; first.cv.W = lay->cW[0]; first.cv.Cin = lay->cC[0]; first.cv.Cout = lay->cC[1];
+        first.B = c->batch; first.k = k;
+        lay->cFirst = conv_first_ok(first);
+        if (lay->cFirst) part = conv_first_part_bytes(first);
+        else lay->cP[j] = take((size_t)k * M * lay->cK[j] * 4);          // (the later convolutions read the map itself)
+      }
       const size_t out = (size_t)k * M * lay->cC[j + 1] * 4;
       lay->cA[j] = take(out); lay->cRA[j] = take(out); lay->cD[j] = take(out); lay->cRD[j] = take(out);
       lay->cSlab[j] = j > 0 && conv_f32_ok(lay->cH[j], lay->cW[j], lay->cC[j], lay->cC[j + 1]);

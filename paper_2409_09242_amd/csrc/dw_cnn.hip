@@ -10,7 +10,8 @@
 //   data grad    dP = D W,                RdP = RD W + D V,   then summed back onto the map ("col2im")
 // are the three products of Section IV-B's Hessian-vector product with B*(H-2)*(W-2) rows instead of B.  ReLU and
 // max-pool pass the directional derivative through their selections (their curvature is zero almost everywhere).
-// Only the first convolution (one input channel in the paper's model: 9 columns) has its patch matrix in memory.
+// Only the first convolution has its patch matrix in memory, and that not where images have one channel: nine products an output
+// need no tiles (dw_conv_first.hip).
 // The others read the map itself, and their data gradient is the same product written from the input positions' side,
 // dA = sum over taps of the shifted gradient map times W's tap, so that the nine contributions of a map entry are added
 // inside the contraction and no patch-shaped gradient is ever stored.  Forward and data gradient run on slabs of the map
@@ -180,6 +181,12 @@ int run_network_cnn(const dw_config& cfg, char* ws, const Layout& lay, const voi
 
   // forward through the convolutions
   for (int j = 0; j < nc; ++j) {
+    if (j == 0 && lay.cFirst) {
+      ConvF32 c = on_slabs(0);
+      c.in = reinterpret_cast<const float*>(d_x); c.out = f(lay.cA[0]); c.rout = f(lay.cRA[0]);
+      if (launch_conv_first(c, s) != hipSuccess) return DW_ERR_HIP;
+      continue;
+    }
     const float* in = j == 0 ? reinterpret_cast<const float*>(d_x) : f(lay.cA[j - 1]);
     const float* rin = j == 0 ? nullptr : f(lay.cRA[j - 1]);
     const int64_t M = rows(j);
@@ -246,6 +253,13 @@ int run_network_cnn(const dw_config& cfg, char* ws, const Layout& lay, const voi
   for (int j = nc - 1; j >= 0; --j) {
     const int64_t M = rows(j);
     const int64_t in_stride = (int64_t)B * lay.cH[j] * lay.cW[j] * lay.cC[j];
+    if (j == 0 && lay.cFirst) {
+      ConvF32 c = on_slabs(0);
+      c.in = reinterpret_cast<const float*>(d_x); c.out = f(lay.cD[0]); c.rout = f(lay.cRD[0]);
+      if (launch_conv_first_grad(c, reinterpret_cast<double*>(ws + lay.cPart), g + lay.cwoff[0], hz + lay.cwoff[0], g + lay.cboff[0],
+                                 hz + lay.cboff[0], s) != hipSuccess) return DW_ERR_HIP;
+      break;
+    }
     {
       GemmArgs a{};
       a.X = f(lay.cD[j]); a.RX = f(lay.cRD[j]); a.x_wstride = M * lay.cC[j + 1]; a.x_kcontig = 0; a.ldx = lay.cC[j + 1];

@@ -266,6 +266,11 @@ bool conv_f32_ok(int H, int W, int Cin, int Cout);      // do slabs of such maps
 size_t conv_f32_frag_bytes(int N, int C);
 hipError_t launch_conv_f32_frags(const ConvF32& c, hipStream_t s);   // the weights of both directions; then:
 hipError_t launch_conv_f32(const ConvF32& c, bool forward, hipStream_t s);
+// The first convolution of images with one channel (dw_conv_first.hip); the fields of the weights' fragments are not used.
+bool conv_first_ok(const ConvF32& c);
+size_t conv_first_part_bytes(const ConvF32& c);         // scratch of the gradient, all workers
+hipError_t launch_conv_first(const ConvF32& c, hipStream_t s);
+hipError_t launch_conv_first_grad(const ConvF32& c, double* part, float* g, float* hz, float* gb, float* hzb, hipStream_t s);
 bool gemm_f32_short_ok(const GemmArgs& a);                       // small-model kernel usable and meant for this product?
 bool gemm_f32_short_shape(int64_t M, int64_t N, int64_t K, int k);   // the part of the answer that the sizes give
 hipError_t launch_gemm_f32_short(const GemmArgs& a, hipStream_t s);
@@ -332,7 +337,8 @@ struct Layout {            // byte offsets into the workspace, all multiples of 
   int cH[DW_MAX_CONV + 1] = {0}, cW[DW_MAX_CONV + 1] = {0}, cC[DW_MAX_CONV + 1] = {0};   // maps: input, then each output
   int cK[DW_MAX_CONV] = {0};                                    // padded row length of W_j: 9*C_in rounded up to 4
   int64_t cwoff[DW_MAX_CONV] = {0}, cboff[DW_MAX_CONV] = {0};
-  size_t cP[DW_MAX_CONV] = {0};                                 // patches [k][M_0][K_0] of the first convolution
+  bool cFirst = false;                                          // first convolution straight from the images (else from patches)
+  size_t cP[DW_MAX_CONV] = {0};                                 // patches [k][M_0][K_0] of the first convolution, unless cFirst
   size_t cA[DW_MAX_CONV] = {0}, cRA[DW_MAX_CONV] = {0};         // outputs a_j, Ra_j [k][M_j][C_j]
   size_t cD[DW_MAX_CONV] = {0}, cRD[DW_MAX_CONV] = {0};         // their gradients
   int cSplit[DW_MAX_CONV] = {0};                                // slices of the weight gradient's contraction (1: none)
