@@ -9,6 +9,7 @@
 #include <new>
 
 #include "dw_internal.h"
+#include "dw_partition_plan.h"
 
 using namespace dw;
 

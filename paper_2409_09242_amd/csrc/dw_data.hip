@@ -13,9 +13,9 @@
 #include <type_traits>
 
 #include "dw_internal.h"
+#include "dw_partition_plan.h"
 
-// Scratch of dw_overlap_partition_static: keys and ranks of up to DW_STATIC_MAX_POINTS points, in the layout
-// partition_scratch_bytes describes.  Every device the library runs on holds its own copy at its own address until the
+// Scratch of dw_overlap_partition_static: what up to DW_STATIC_MAX_POINTS points need (dw_partition_plan.h).  Every device the library runs on holds its own copy at its own address until the
 // process ends; host code reaches it only through the address hipGetSymbolAddress returns for the current device.
 static __device__ __align__(256) unsigned char scratch[(size_t)DW_STATIC_MAX_POINTS * 12];
 
@@ -112,9 +112,7 @@ __global__ __launch_bounds__(256) void bucket_rank_kernel(const int32_t* count, 
 // memory, so nothing is cleared.  Bound by latency: five dependent trips to memory.  n = 60000: the kernels 10 us, the whole call 26 (five launches: 28 and 43; buckets of
 // 64 to 128 points with four waves each 39, 20 of them comparing keys).
 
-constexpr int kChunkThreads = 1024, kMaxChunks = 64;
-
-// chunk c: the CH points from c * CH on, at points[c * CH ...] by bucket; edge[c * (nb + 1) + b]: the first of bucket b (b = 0 .. nb)
+// chunk c: the CH points from c * CH on, at points[c * CH ...] by bucket; edge[c * nb + b]: the first of bucket b
 template <int PER>
 __global__ __launch_bounds__(kChunkThreads) void chunk_sort_kernel(uint16_t* edge, int32_t* points, int64_t n, int bits, uint64_t k1) {
   constexpr int CH = kChunkThreads * PER;
@@ -122,7 +120,7 @@ __global__ __launch_bounds__(kChunkThreads) void chunk_sort_kernel(uint16_t* edg
   __shared__ int32_t waves[kChunkThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int nb = 1 << bits;
-  uint16_t* edges = edge + (int64_t)blockIdx.x * (nb + 1);
+  uint16_t* edges = edge + (int64_t)blockIdx.x * nb;
   const int64_t i0 = (int64_t)blockIdx.x * CH;
   for (int b = tid; b < nb; b += kChunkThreads) first[b] = 0;
   __syncthreads();
@@ -154,7 +152,6 @@ __global__ __launch_bounds__(kChunkThreads) void chunk_sort_kernel(uint16_t* edg
     edges[b] = (uint16_t)at;
     at += c;
   }
-  if (tid == kChunkThreads - 1) edges[nb] = (uint16_t)at;      // (the points of the chunk)
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < PER; ++j)
@@ -163,16 +160,17 @@ __global__ __launch_bounds__(kChunkThreads) void chunk_sort_kernel(uint16_t* edg
 
 // a wave per bucket: collect its points (a lane per chunk), rank them, place them
 template <int PER>
-__global__ __launch_bounds__(64) void chunk_rank_kernel(const uint16_t* edge, const int32_t* points, int nb, int chunks, int32_t* index,
-                                                        uint64_t k1, int32_t o, int32_t s, int k) {
+__global__ __launch_bounds__(64) void chunk_rank_kernel(const uint16_t* edge, const int32_t* points, int64_t n, int nb, int chunks,
+                                                        int32_t* index, uint64_t k1, int32_t o, int32_t s, int k) {
   constexpr int CH = kChunkThreads * PER, T = 64;
   static_assert(kMaxChunks <= T, "a lane per chunk");
   __shared__ uint64_t key[T];
   __shared__ int32_t point[T];
   const int lane = threadIdx.x, b = blockIdx.x;
-  // this lane's chunk: where the bucket starts in it, and how many points it has
-  const uint16_t* e = edge + (int64_t)lane * (nb + 1) + b;
-  const int lo = lane < chunks ? e[0] : 0, len = lane < chunks ? e[1] - lo : 0;
+  // this lane's chunk: where the bucket starts in it, and how many points it has (the last bucket ends where the chunk does)
+  const uint16_t* e = edge + (int64_t)lane * nb + b;
+  const int left = (int)(n - (int64_t)lane * CH), end = left < CH ? left : CH;
+  const int lo = lane < chunks ? e[0] : 0, len = lane < chunks ? (b + 1 < nb ? e[1] : end) - lo : 0;
   int32_t run = len, rank0 = lo;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
@@ -213,9 +211,6 @@ __global__ __launch_bounds__(64) void chunk_rank_kernel(const uint16_t* edge, co
   }
 }
 
-// Above this size a chunk would need more points or the waves more lanes.
-constexpr int64_t kChunksTo = 4 * kMaxChunks * kChunkThreads;
-
 struct GatherKeys { uint64_t key[DW_MAX_K]; };
 
 // block (b, j): draw b of worker j, one row of row_vecs 16-byte pieces
@@ -241,36 +236,24 @@ __global__ __launch_bounds__(256) void gather_kernel(const uint4* data, const in
 
 }  // namespace
 
-size_t partition_scratch_bytes(int64_t n) {
-  const size_t keys = ((size_t)n * 8 + 255) / 256 * 256;
-  const size_t rank = ((size_t)n * 4 + 255) / 256 * 256;
-  return keys + rank;
-}
-
 hipError_t launch_partition(int64_t n, int64_t o, int k, uint64_t seed, int32_t* index, void* scratch, hipStream_t s) {
   const int64_t sz = (n - o) / k;
   const uint64_t k1 = mix64_d(seed);
-  if (n <= kChunksTo) {
-    int bits = 5;                                              // 16 to 32 points a bucket (fewer of n < 512)
-    while (bits < 13 && (n >> (bits + 1)) >= 16) bits += 1;    // (8192 counters: 32 KB of LDS)
-    const int nb = 1 << bits;
+  const PartitionPlan plan = partition_plan(n);
+  const int bits = plan.bits, nb = plan.nb;
+  if (plan.chunks > 0) {
     auto launch = [&](auto per) {
-      constexpr int PER = decltype(per)::value, CH = kChunkThreads * PER;
-      const unsigned chunks = (unsigned)((n + CH - 1) / CH);   // kMaxChunks at most
-      // 4 n bytes of points, 2 chunks (nb + 1) <= 8 n of edges (nb <= n / 16, chunks <= 64; 66 when n < 512)
+      constexpr int PER = decltype(per)::value;
       int32_t* points = reinterpret_cast<int32_t*>(scratch);
       uint16_t* edge = reinterpret_cast<uint16_t*>(points + n);
-      hipLaunchKernelGGL(chunk_sort_kernel<PER>, dim3(chunks), dim3(kChunkThreads), nb * (int)sizeof(int32_t), s, edge, points, n, bits, k1);
-      hipLaunchKernelGGL(chunk_rank_kernel<PER>, dim3((unsigned)nb), dim3(64), 0, s, edge, points, nb, (int)chunks, index, k1, (int32_t)o,
+      hipLaunchKernelGGL(chunk_sort_kernel<PER>, dim3((unsigned)plan.chunks), dim3(kChunkThreads), nb * (int)sizeof(int32_t), s, edge, points, n,
+                         bits, k1);
+      hipLaunchKernelGGL(chunk_rank_kernel<PER>, dim3((unsigned)nb), dim3(64), 0, s, edge, points, n, nb, plan.chunks, index, k1, (int32_t)o,
                          (int32_t)sz, k);
     };
-    if (n <= kMaxChunks * kChunkThreads) launch(std::integral_constant<int, 1>{}); else launch(std::integral_constant<int, 4>{});
+    if (plan.per == 1) launch(std::integral_constant<int, 1>{}); else launch(std::integral_constant<int, 4>{});
     return hipGetLastError();
   }
-  int bits = 13;                                               // 16 to 32 points a bucket
-  while ((n >> (bits + 1)) >= 16) bits += 1;
-  const int nb = 1 << bits;
-  // 8 n + 8 nb bytes, nb <= n / 16: within the 12 n of partition_scratch_bytes
   int32_t* count = reinterpret_cast<int32_t*>(scratch);
   int32_t* start = count + nb;
   int32_t* slot = start + nb;

@@ -127,7 +127,6 @@ hipError_t launch_col_sums_bf16(const uint16_t* src, int B, int n, float* out, i
 int note_hip_error(hipError_t e);
 
 // ---- data side ---------------------------------------------------------------------------------------
-size_t partition_scratch_bytes(int64_t n);
 // index [k][o + s], s = floor((n-o)/k): row j = the shared points then worker j's own, in permutation order
 hipError_t launch_partition(int64_t n, int64_t o, int k, uint64_t seed, int32_t* index, void* scratch, hipStream_t s);
 // x [k][B][row_bytes], y [k][B]: draw b of worker j is row index[j][floor(u*m/2^64)], u = mix(key_j + GAMMA*(b+1))

@@ -1,6 +1,10 @@
-"""The overlap partition at the edges of its chunks, of the sizes that one chunk size takes and of the two-launch form, bit for bit."""
+"""The overlap partition at the edges of its chunks, of the sizes that one chunk size takes and of the two-launch form, bit for bit, and
+with scratch of exactly the stated size."""
+import ctypes
+
 import numpy as np
 import pytest
+import torch
 
 from oracle import dw_data as OD
 from paper_2409_09242_amd import binding as B
@@ -21,3 +25,24 @@ def test_partition_in_chunks_matches_the_oracle(n, o, k):
     for seed in (1, (1 << 62) + 3 * n):
         got = B.overlap_partition(n, o, k, seed, "cuda:0").cpu().numpy()
         np.testing.assert_array_equal(got, OD.worker_datasets(n, o, k, seed))
+
+
+@pytest.mark.parametrize("n", [1, 1000, 1 << 16, (1 << 16) + 1, (1 << 18) + 1])
+def test_nothing_is_written_beside_the_scratch_or_the_index(n):
+    """Exactly the bytes that dw_partition_scratch_bytes states, between guard words, and so the index: the guards stay as they are.
+    (n = 2^16 uses the scratch to its last byte.)"""
+    print("partition guards", n, flush=True)
+    o, k, seed, guard = n // 5, 3, 11, 4096
+    m, nbytes = o + (n - o) // k, B.lib().dw_partition_scratch_bytes(n)
+    scratch = torch.full((guard + nbytes + guard,), 0xA5, dtype=torch.uint8, device="cuda:0")
+    index = torch.full((guard + k * m + guard,), -7, dtype=torch.int32, device="cuda:0")
+    assert scratch.data_ptr() % 256 == 0
+    s = B.lib().dw_overlap_partition(n, o, k, seed, ctypes.c_void_p(index.data_ptr() + 4 * guard), ctypes.c_void_p(scratch.data_ptr() + guard),
+                                     nbytes, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert s == (n - o) // k
+    np.testing.assert_array_equal(index[guard:guard + k * m].cpu().numpy().reshape(k, m), OD.worker_datasets(n, o, k, seed))
+    for edge in (scratch[:guard], scratch[guard + nbytes:]):
+        assert bool((edge == 0xA5).all())
+    for edge in (index[:guard], index[guard + k * m:]):
+        assert bool((edge == -7).all())
