@@ -177,8 +177,9 @@ int validate(const dw_config* c, Layout* lay) {
       }
     }
     // weight gradients of the convolutions contract over all output positions of the minibatch and have few output
-    // tiles: cut the contraction so that about 1024 blocks exist, slices of at least 512 positions
-    for (int j = 0; j < lay->n_conv; ++j) {
+    // tiles: cut the contraction so that about 1024 blocks exist, slices of at least 512 positions (the first
+    // convolution of one-channel images has a kernel of its own, without slices)
+    for (int j = lay->cFirst ? 1 : 0; j < lay->n_conv; ++j) {
       const int64_t M = B * lay->cH[j + 1] * lay->cW[j + 1];
       const int64_t blocks = (int64_t)((lay->cC[j + 1] + 63) / 64) * ((lay->cK[j] + 63) / 64) * k;
       int64_t split = 1024 / blocks;
@@ -198,28 +199,23 @@ int validate(const dw_config* c, Layout* lay) {
   if (L > 0 && c->dtype == DW_F32) {
     // fp32 forward products of hidden layers with a long contraction and a handful of output tiles (the first linear
     // layer behind a convolutional front end) that the small-model kernel does not take: same cut, slices of at least 64
-    // (the small-model kernel takes more of these shapes than scratch is left out for: a workspace's size does not
-    // depend on which of the two kernels is the faster one)
     const int64_t B = c->batch;
-    auto cut = [&](int64_t n, int64_t kk, bool reserved) {       // slices of a product of B x n outputs
+    auto cut = [&](int64_t n, int64_t kk) {                      // slices of a product of B x n outputs
+      if (gemm_f32_short_shape(B, n, kk, k)) return 1;
       const int64_t tiles = n <= 32 ? (B + 127) / 128 : B <= 32 ? (n + 127) / 128 : ((B + 63) / 64) * ((n + 63) / 64);
       int64_t split = tiles * k < 256 ? 1024 / (tiles * k) : 1;
       if (split > kk / 64) split = kk / 64;
       if (split > 64) split = 64;
-      if (split > 1 && reserved) {
-        const size_t need = (size_t)split * k * 2 * B * n * 4;
-        part = need > part ? need : part;
-      }
-      return split > 1 && !gemm_f32_short_shape(B, n, kk, k) ? (int)split : 1;
+      if (split <= 1) return 1;
+      const size_t need = (size_t)split * k * 2 * B * n * 4;
+      part = need > part ? need : part;
+      return (int)split;
     };
-    for (int l = 1; l < L; ++l) {
-      const int64_t n = c->dims[l], kk = c->dims[l - 1], tiles = ((B + 63) / 64) * ((n + 63) / 64) * k;
-      lay->fwdSplit[l - 1] = cut(n, kk, tiles >= 256 || kk > (tiles >= 40 && tiles <= 64 ? 2048 : 1152));
-    }
+    for (int l = 1; l < L; ++l) lay->fwdSplit[l - 1] = cut(c->dims[l], c->dims[l - 1]);
     const size_t head = out_head_f32_slice_bytes(B, c->dims[L - 1], k);
     part = head > part ? head : part;
     // and the data gradients through W_l (B x d_{l-1} outputs, contraction d_l) of the same kind
-    for (int l = 2; l <= L; ++l) lay->dgSplit[l - 1] = cut(c->dims[l - 1], c->dims[l], true);
+    for (int l = 2; l <= L; ++l) lay->dgSplit[l - 1] = cut(c->dims[l - 1], c->dims[l]);
   }
   if (part > 0) { lay->cPart = take(part); lay->cPartB = take(part_b > 0 ? part_b : 256); }
   lay->partials = take((size_t)k * lay->n_upd_blocks * sizeof(double));

@@ -266,10 +266,11 @@ def test_bench_reads_the_traffic_figure_only_for_the_kernel_it_was_measured_on(t
 
 
 @pytest.mark.parametrize("dims", [(784, 512, 10), (1152, 256, 132, 7), (1156, 256, 10), (2048, 512, 10),
-                                  (2052, 512, 10), (64, 3072, 64, 10)])
+                                  (2052, 512, 10), (64, 3072, 64, 10), (4096, 260, 10), (4100, 256, 10), (1156, 64, 10),
+                                  (784, 512, 512, 10)])
 def test_a_small_fp32_model_has_scratch_for_the_slices_that_are_written(dims):
-    """Few output tiles: forward products with a contraction of at most 1152 (2048 with 40 to 64 tiles) run without slices, longer
-    ones in slices of at least 64, as all data gradients do; the logits stay in the output layer's kernel.  So beside parameters,
+    """Few output tiles: forward products and data gradients with a contraction of at most 1152 (4096 with 32 to 128 tiles) run
+    without slices, longer ones in slices of at least 64; the logits stay in the output layer's kernel.  So beside parameters,
     moments, gradients, sign bits and activations there are three arrays of 16 floats a sample, those slices and the per-worker
     scalars."""
     k, batch = 4, 128
@@ -278,11 +279,11 @@ def test_a_small_fp32_model_has_scratch_for_the_slices_that_are_written(dims):
 
     def slice_bytes(n, contraction):                          # a product of batch x n outputs
         tiles = (batch + 63) // 64 * ((n + 63) // 64)
+        if tiles * k < 256 and contraction <= (4096 if 32 <= tiles * k <= 128 else 1152):
+            return 0
         cut = max(1, min(1024 // (tiles * k), contraction // 64, 64)) if tiles * k < 256 else 1
         return cut * k * 2 * batch * n * 4 if cut > 1 else 0
-    longest = {n: 2048 if 40 <= (batch + 63) // 64 * ((n + 63) // 64) * k <= 64 else 1152 for n in dims[1:-1]}
-    slices = max([slice_bytes(n, kk) for kk, n in zip(dims[:-2], dims[1:-1]) if kk > longest[n]] +
-                 [slice_bytes(n, kk) for n, kk in zip(dims[1:-1], dims[2:])])
+    slices = max([slice_bytes(n, kk) for kk, n in zip(dims[:-2], dims[1:-1])] + [slice_bytes(n, kk) for n, kk in zip(dims[1:-1], dims[2:])])
     params = 5 * k * P * 4 + P * 4 + k * P // 8
     hidden = 4 * k * batch * sum(dims[1:-1]) * 4
     head = 3 * k * batch * 16 * 4
