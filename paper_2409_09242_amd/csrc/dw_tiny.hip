@@ -464,15 +464,35 @@ int tiny_lds_floats(const dw_config& c, const Layout& lay) {
   return total > (1 << 30) ? (1 << 30) : (int)total;
 }
 
+// What the step of a model this size touches, in floats: parameters and signs with rows of an odd length, the minibatch, activations and
+// errors with their companions, g and Hz of all layers, the sign words
+int64_t tiny_size(const dw_config& c, const Layout& lay) {
+  int64_t rows = 0, hidden = 0, dmax = DW_MAX_CLASSES;
+  for (int l = 1; l <= c.n_layers; ++l) {
+    rows += (int64_t)c.dims[l] * (c.dims[l - 1] + 2);
+    if (l < c.n_layers) { hidden += c.dims[l]; if (c.dims[l] > dmax) dmax = c.dims[l]; }
+  }
+  const int64_t B = c.batch;
+  return 2 * rows + B * c.dims[0] + 2 * B * hidden + 4 * B * dmax + 2 * ((lay.P + 3) / 4 * 4) + 2 * ((lay.P + 63) / 64) + B + 64;
+}
+
 }  // namespace
 
 // A model takes this path when it is fp32 without a convolutional front end, one Hutchinson probe per step, the
-// AdaHessian step, an averaging block inside one wave's reach, four groups of four parameters for every thread, and everything listed above fits in LDS.
+// AdaHessian step, an averaging block inside one wave's reach, four groups of four parameters for every thread, and its size at most
+// kTinyMaxSize (it then fits in LDS, which the last line makes sure of).
+// The kernel could hold models up to a third larger, since g and Hz of the first layer lie where its parameters were.  Those keep to the
+// launches of a layer each, because the sums there, in bf16 pieces, are closer to the 64-bit ones than the fp32 instruction's.  Relative
+// error of g and Hz, worst layer, here / there, and the step with a round: 64-96-16, one worker of 16 samples: 11.3e-8 / 7.8e-8, 22 / 35 us;
+// 252-60-5, one of 8: 16.7e-8 / 8.9e-8, 20 / 33; 512-16-100-15, one of one: 25e-8 / 8.1e-8; without a hidden layer they are slower too
+// (80-14, one of 256: 21e-8 / 12e-8, 37 / 31 us).  Smaller models gain more by the one launch (32-64-10, one of 64: 11.8e-8 / 7.9e-8,
+// 23.5 / 34 us; one of 16: 14.8 / 33).
+constexpr int64_t kTinyMaxSize = 39 * 1024;
 bool tiny_step_ok(const dw_config& c, const Layout& lay) {
   if (c.n_layers < 1 || c.dtype != DW_F32 || c.n_conv != 0 || c.n_samples > 1 || c.optimizer != DW_OPT_ADAHESSIAN)
     return false;
   if (c.avg_block > 64 || lay.P > 4 * kTinyGroups * kTinyThreads || c.batch > 1024) return false;
-  return tiny_lds_floats(c, lay) <= kTinyMaxLdsFloats;
+  return tiny_size(c, lay) <= kTinyMaxSize && tiny_lds_floats(c, lay) <= kTinyMaxLdsFloats;
 }
 
 hipError_t launch_tiny_step(const dw_config& c, char* ws, const Layout& lay, const void* d_x, const int32_t* d_y,

@@ -33,6 +33,22 @@ def test_update_of_small_models(dims, batch, k, avg_block, hpow):
     N.test_small_models_take_the_whole_step_in_one_kernel(dims, batch, k, avg_block, hpow)
 
 
+@pytest.mark.parametrize("dims,batch,k,one_kernel", [
+    ((32, 64, 10), 68, 2, True), ((32, 64, 10), 69, 2, False), ((80, 14), 243, 1, True), ((80, 14), 244, 1, False),
+    ((64, 96, 16), 12, 2, True), ((64, 96, 16), 13, 2, False), ((512, 16, 100, 15), 1, 2, False), ((124, 124, 7), 4, 2, False),
+])
+def test_models_past_the_size_of_the_one_kernel_step_take_the_launches_of_a_layer_each(dims, batch, k, one_kernel):
+    """The largest minibatches that the one kernel takes and the next ones, and models that would fit in LDS but are more exact in
+    pieces."""
+    print("tiny size", dims, batch, k, one_kernel, flush=True)
+    h = B.Handle(B.make_config(dims=dims, k=k, batch=batch), np.zeros(B.param_count(B.make_config(dims=dims, k=k, batch=batch)), dtype=np.float32))
+    h.profile(True)
+    h.worker_step(torch.zeros((k, batch, dims[0]), device="cuda"), torch.zeros((k, batch), dtype=torch.int32, device="cuda"))
+    prof = h.profile_read()
+    assert (prof["step"][0], prof["update"][0]) == ((1, 0) if one_kernel else (0, 1))
+    N.test_gradient_and_hvp_match_the_oracle(dims, batch, k)
+
+
 def test_a_logit_that_is_infinite_or_no_number():
     """A bias of +inf makes its worker's loss infinite or no number, as softmax in fp32 does, and leaves the other worker's step alone."""
     dims, batch = (8, 12, 5), 6
