@@ -200,8 +200,8 @@ int validate(const dw_config* c, Layout* lay) {
     // fp32 forward products of hidden layers with a long contraction and a handful of output tiles (the first linear
     // layer behind a convolutional front end) that the small-model kernel does not take: same cut, slices of at least 64
     const int64_t B = c->batch;
-    auto cut = [&](int64_t n, int64_t kk) {                      // slices of a product of B x n outputs
-      if (gemm_f32_short_shape(B, n, kk, k)) return 1;
+    auto cut = [&](int64_t n, int64_t kk, ShortProduct what) {   // slices of a product of B x n outputs
+      if (gemm_f32_short_shape(B, n, kk, k, what)) return 1;
       const int64_t tiles = n <= 32 ? (B + 127) / 128 : B <= 32 ? (n + 127) / 128 : ((B + 63) / 64) * ((n + 63) / 64);
       int64_t split = tiles * k < 256 ? 1024 / (tiles * k) : 1;
       if (split > kk / 64) split = kk / 64;
@@ -211,11 +211,15 @@ int validate(const dw_config* c, Layout* lay) {
       part = need > part ? need : part;
       return (int)split;
     };
-    for (int l = 1; l < L; ++l) lay->fwdSplit[l - 1] = cut(c->dims[l], c->dims[l - 1]);
+    const bool plain = lay->n_conv == 0 && c->optimizer != DW_OPT_ADAHESSIAN;
+    for (int l = 1; l < L; ++l)
+      lay->fwdSplit[l - 1] = cut(c->dims[l], c->dims[l - 1], plain ? SHORT_PLAIN : l == 1 && lay->n_conv == 0 ? SHORT_FIRST : SHORT_LATER);
     const size_t head = out_head_f32_slice_bytes(B, c->dims[L - 1], k);
     part = head > part ? head : part;
-    // and the data gradients through W_l (B x d_{l-1} outputs, contraction d_l) of the same kind
-    for (int l = 2; l <= L; ++l) lay->dgSplit[l - 1] = cut(c->dims[l - 1], c->dims[l]);
+    // and the data gradients through W_l (B x d_{l-1} outputs, contraction d_l) of the same kind (to the pooled map, many columns
+    // wide, only with a contraction that the small-model kernel leaves out)
+    for (int l = lay->n_conv > 0 && c->dims[1] > 896 ? 1 : 2; l <= L; ++l)
+      lay->dgSplit[l - 1] = cut(c->dims[l - 1], c->dims[l], plain ? SHORT_PLAIN_GRAD : SHORT_GRAD);
   }
   if (part > 0) { lay->cPart = take(part); lay->cPartB = take(part_b > 0 ? part_b : 256); }
   lay->partials = take((size_t)k * lay->n_upd_blocks * sizeof(double));

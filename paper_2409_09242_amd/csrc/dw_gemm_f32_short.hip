@@ -298,17 +298,31 @@ static hipError_t launch(const GemmArgs& a, hipStream_t s) {
 }  // namespace f32s
 
 // A product of M x N outputs and contraction K for each of k workers (the layout asks as well: such a product needs no slices).
-// Against the 64 x 64 tiles, in slices where there are few of them, as the step here / there:
-//   K      up to 1152: faster or even at any number of tiles (128-128, two workers of 64 samples 38 / 74 us, all its products; 1036-340, five
-//          of 93 75 / 92).  Longer ones block by block take too long where few blocks walk them (4096-64, one of 64, one tile:
-//          61 / 48; data gradient 1500 -> 256, two of 64, eight: 123 / 110) and less from 32 tiles on, four blocks to a tile
-//          (1280-256, six of 256, 96 tiles: 92 / 96; 3072-512, four of 128, 64: 141 / 154; 3072-1024, two of 64, 32: 168 / 174)
-//          and not more than 128 (1200-1200-1200, three of 200, 228 tiles: 388 / 330)
-//   tiles  up to 256 of them (1100-1100, three of 200, 228: 156 / 164); more of them fill the chip and share their operands among more
-//          outputs (512-1024, four of 256, 256 tiles: 119 / 106; 784-768, six of 300, 360: 175 / 145)
-bool gemm_f32_short_shape(int64_t M, int64_t N, int64_t K, int k) {
-  const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64) * k;
-  return tiles < 256 && K <= (tiles >= 32 && tiles <= 128 ? 4096 : 1152);
+// Against the 64 x 64 tiles, in slices where there are few of them; times of a class of products a step, here / there, us.  `tiles`: the
+// 64 x 64 ones of all workers; `blocks`: this kernel's, of which 256 run at a time.
+//   tiles  256 and more fill the chip and share their operands among more outputs (512-1024, four of 256: the step 119 / 106)
+//   K      up to 1152, forward: faster as a rule (128-128, two workers of 64: the step 38 / 74; 1036-340, five of 93: 75 / 92; but 100 -> 3200,
+//          four of 64: 32 / 25)
+//          up to 1152, data gradient: up to 512 blocks, two rounds (512 -> 2048, four of 64: 0.84 of the tiles' time; 64 -> 2048: 0.89), but
+//          few blocks take too long over a long contraction (1024 -> 256, four of 64: 29.7 / 28.0; 768 -> 256: 0.92).  The third round
+//          pays in the middle (256 -> 3072: 0.90; 140: 1.01; 10: 1.40; 768: 1.01), further ones don't (140 -> 3200: 39 / 34; 10 -> 3200: 1.41;
+//          1024 -> 3200: 78 / 61).  Without the companion's products the third round takes 512 -> 3072: 0.94, 1024: 1.05, and short
+//          contractions of up to 320 pay as a rule (64 -> 4000: 0.84; 256: 0.93; 140: 1.07; 512: 1.04, -> 3200 1.13)
+//          longer: one round (2048 -> 1024, four of 64: 0.87, 2048 -> 1280: 1.18) that is not too empty (3072 -> 512: 1.13, 2048 -> 512: 1.03,
+//          4096 -> 1024 0.95).  The first layer, which has no companion: 32 to 128 tiles (1280-256, six of 256, 96: the step 92 / 96;
+//          2048 -> 2048, four of 64, 128: 0.85; 4096-64, one of 64, one: the step 61 / 48)
+bool gemm_f32_short_shape(int64_t M, int64_t N, int64_t K, int k, ShortProduct what) {
+  const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64) * k, blocks = ((M + 31) / 32) * ((N + 31) / 32) * k;
+  if (tiles >= 256) return false;
+  if (K > 1152) {
+    if (what == SHORT_FIRST) return K <= 4096 && tiles >= 32 && tiles <= 128;
+    return tiles >= 32 && blocks <= 256 && K <= (tiles < 48 ? 2048 : 4096);
+  }
+  if (what != SHORT_GRAD && what != SHORT_PLAIN_GRAD) return true;
+  const bool plain = what == SHORT_PLAIN_GRAD;
+  if (blocks <= 512) return plain || blocks >= 128 || K <= 896;
+  if (blocks <= 768) return K <= 640 && (plain || K >= 192);
+  return plain && K <= 320;
 }
 
 // Forward product or data gradient of matrices in memory, no slices, whose 64 x 64 tiles over all workers would leave compute
@@ -316,7 +330,8 @@ bool gemm_f32_short_shape(int64_t M, int64_t N, int64_t K, int k) {
 bool gemm_f32_short_ok(const GemmArgs& a) {
   if (a.x_view != VIEW_NONE || a.y_view != VIEW_NONE || a.ksplit > 1 || !(a.ry_bits || a.plain)) return false;
   if (a.epi == EPI_MASK ? !a.plain && !a.RX : a.epi != EPI_RELU) return false;
-  return gemm_f32_short_shape(a.M, a.N, a.K, a.k);
+  const ShortProduct what = a.epi == EPI_MASK ? (a.plain ? SHORT_PLAIN_GRAD : SHORT_GRAD) : a.plain ? SHORT_PLAIN : a.RX ? SHORT_LATER : SHORT_FIRST;
+  return gemm_f32_short_shape(a.M, a.N, a.K, a.k, what);
 }
 
 template <int NW>

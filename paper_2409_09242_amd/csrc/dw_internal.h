@@ -271,7 +271,10 @@ size_t conv_first_part_bytes(const ConvF32& c);         // scratch of the gradie
 hipError_t launch_conv_first(const ConvF32& c, hipStream_t s);
 hipError_t launch_conv_first_grad(const ConvF32& c, double* part, float* g, float* hz, float* gb, float* hzb, hipStream_t s);
 bool gemm_f32_short_ok(const GemmArgs& a);                       // small-model kernel usable and meant for this product?
-bool gemm_f32_short_shape(int64_t M, int64_t N, int64_t K, int k);   // the part of the answer that the sizes give
+// the part of the answer that the sizes and the operands give: forward product of the first layer (no companion comes in), of a later one,
+// data gradient, and the same without companions (a first-order step)
+enum ShortProduct { SHORT_FIRST, SHORT_LATER, SHORT_GRAD, SHORT_PLAIN, SHORT_PLAIN_GRAD };
+bool gemm_f32_short_shape(int64_t M, int64_t N, int64_t K, int k, ShortProduct what);
 hipError_t launch_gemm_f32_short(const GemmArgs& a, hipStream_t s);
 // the weight gradients (EPI_WGRAD, not fused) of n layers of a small fp32 MLP in one launch; meant for this model?
 bool wgrad_group_f32_ok(const dw_config& cfg);

@@ -246,7 +246,7 @@ int run_network(const dw_config& cfg, char* ws, const Layout& lay, const void* d
     if (!b16 && gemm_f32_short_ok(a)) {
       if ((e = launch_gemm_f32_short(a, s)) != hipSuccess) return DW_ERR_HIP;
     } else {
-      if (!b16 && l > 1 && lay.dgSplit[l - 1] > 1) {      // long contraction, few output tiles
+      if (!b16 && lay.dgSplit[l - 1] > 1) {      // long contraction, few output tiles
         a.ksplit = lay.dgSplit[l - 1]; a.part = reinterpret_cast<float*>(ws + lay.cPart);
         a.part_stride = (int64_t)B * a.ldc; a.part_b = nullptr;
       }

@@ -5,9 +5,13 @@ import numpy as np
 import pytest
 import torch
 
+import test_gpu_cnn as N
 import test_gpu_f32_pieces as P
+from oracle import dw_cnn as OC
+from oracle import dw_oracle as O
 from paper_2409_09242_amd import binding as B
-from parity import RTOL_GRAD
+from paper_2409_09242_amd import workloads as W
+from parity import RTOL_GRAD, close_layers, oracle_config
 
 pytestmark = pytest.mark.gpu
 
@@ -22,6 +26,37 @@ pytestmark = pytest.mark.gpu
 ])
 def test_steps_and_tiles_follow_the_oracle(dims, batch, k):
     P.test_tile_and_chain_edges_follow_the_oracle(dims, batch, k)
+
+
+@pytest.mark.parametrize("dims,batch,k", [
+    ((32, 2048, 64, 5), 64, 4), ((32, 2052, 64, 5), 64, 4),        # data gradient: 512 blocks of 32 x 32, then 520 in 64 x 64 tiles
+    ((32, 3072, 256, 5), 64, 4), ((32, 3076, 256, 5), 64, 4),      # 768 blocks, then 776 in slices of the tiles
+    ((32, 256, 896, 5), 64, 4), ((32, 256, 900, 5), 64, 4),        # few blocks: up to 896 columns, then slices
+    ((16, 2048, 1024, 5), 64, 4), ((16, 2048, 1028, 5), 64, 4),    # later layer's forward product: 256 blocks, then 264 in slices
+    ((1156, 2048, 5), 64, 4), ((1156, 508, 5), 64, 4),             # first layer's: 128 tiles of 64 x 64, then 32
+])
+def test_products_on_either_side_of_the_rules_lines(dims, batch, k):
+    P.test_tile_and_chain_edges_follow_the_oracle(dims, batch, k)
+
+
+def test_data_gradient_to_the_pooled_map_in_slices(monkeypatch):
+    """A long contraction over few columns of the pooled map."""
+    name = "few columns, long contraction"
+    monkeypatch.setitem(N.SPECS, name, (OC.CnnSpec(img=(12, 10, 1), conv=(8,), fc=(1028, 7)), 5, 2))
+    N.test_cnn_step_matches_the_oracle(name, 0)
+
+
+@pytest.mark.parametrize("dims,batch,k", [((32, 2052, 64, 5), 64, 4), ((32, 3072, 256, 5), 64, 4), ((32, 2052, 644, 5), 64, 4),
+                                          ((16, 2048, 1028, 5), 64, 4), ((1156, 2048, 5), 64, 4)])
+def test_first_order_steps_on_either_side_of_the_rules_lines(dims, batch, k):
+    theta0, x, y = P._inputs(dims, batch, k, 80)
+    w = W.scaled(W.C2, k=k, dims=dims, batch=batch, input_dist="normal", optimizer=B.DW_OPT_SGD, seed=80)
+    h = B.Handle(B.config_from_workload(w), theta0)
+    tr = O.OracleTrainer(oracle_config(w), theta0.astype(np.float64))
+    h.worker_step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda())
+    tr.worker_step(x, y)
+    for i in range(k):
+        close_layers(h.get_state(B.DW_S_G, i), tr.traces[i].g, dims, RTOL_GRAD, "g[%d]" % i)
 
 
 @pytest.mark.parametrize("dims,batch,k", [((516, 260, 68, 5), 31, 1), ((768, 100, 772, 9), 64, 2), ((128, 64, 1300, 10), 160, 1)])

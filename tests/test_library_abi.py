@@ -267,23 +267,34 @@ def test_bench_reads_the_traffic_figure_only_for_the_kernel_it_was_measured_on(t
 
 @pytest.mark.parametrize("dims", [(784, 512, 10), (1152, 256, 132, 7), (1156, 256, 10), (2048, 512, 10),
                                   (2052, 512, 10), (64, 3072, 64, 10), (4096, 260, 10), (4100, 256, 10), (1156, 64, 10),
-                                  (784, 512, 512, 10)])
+                                  (784, 512, 512, 10), (64, 2048, 256, 256, 10),
+                                  (64, 1600, 1024, 10), (64, 128, 1024, 10)])
 def test_a_small_fp32_model_has_scratch_for_the_slices_that_are_written(dims):
-    """Few output tiles: forward products and data gradients with a contraction of at most 1152 (4096 with 32 to 128 tiles) run
-    without slices, longer ones in slices of at least 64; the logits stay in the output layer's kernel.  So beside parameters,
+    """Few output tiles: forward products with a contraction of at most 1152 (the first layer's of 4096 with 32 to 128 tiles, the others'
+    where 32 x 32 blocks of 32 tiles and more run all at once) run without slices, so do most data gradients, longer ones in slices of at
+    least 64; the logits stay in the output layer's kernel.  So beside parameters,
     moments, gradients, sign bits and activations there are three arrays of 16 floats a sample, those slices and the per-worker
     scalars."""
     k, batch = 4, 128
     cfg = B.make_config(dims=dims, k=k, batch=batch)
     P = B.param_count(cfg)
 
-    def slice_bytes(n, contraction):                          # a product of batch x n outputs
+    def slice_bytes(n, contraction, what):                    # a product of batch x n outputs
         tiles = (batch + 63) // 64 * ((n + 63) // 64)
-        if tiles * k < 256 and contraction <= (4096 if 32 <= tiles * k <= 128 else 1152):
+        blocks = (batch + 31) // 32 * ((n + 31) // 32) * k
+        if contraction > 1152:
+            whole = 32 <= tiles * k <= 128 if what == "first" else tiles * k >= 32 and blocks <= 256
+            whole = whole and contraction <= (4096 if what == "first" or tiles * k >= 48 else 2048)
+        elif what != "grad" or blocks <= 512:
+            whole = what != "grad" or blocks >= 128 or contraction <= 896
+        else:
+            whole = blocks <= 768 and 192 <= contraction <= 640
+        if tiles * k < 256 and whole:
             return 0
         cut = max(1, min(1024 // (tiles * k), contraction // 64, 64)) if tiles * k < 256 else 1
         return cut * k * 2 * batch * n * 4 if cut > 1 else 0
-    slices = max([slice_bytes(n, kk) for kk, n in zip(dims[:-2], dims[1:-1])] + [slice_bytes(n, kk) for n, kk in zip(dims[1:-1], dims[2:])])
+    slices = max([slice_bytes(n, kk, "later" if l else "first") for l, (kk, n) in enumerate(zip(dims[:-2], dims[1:-1]))] +
+                 [slice_bytes(n, kk, "grad") for n, kk in zip(dims[1:-1], dims[2:])])
     params = 5 * k * P * 4 + P * 4 + k * P // 8
     hidden = 4 * k * batch * sum(dims[1:-1]) * 4
     head = 3 * k * batch * 16 * 4
