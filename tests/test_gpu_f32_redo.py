@@ -10,11 +10,12 @@ from paper_2409_09242_amd import binding as B
 from paper_2409_09242_amd import workloads as W
 from parity import RTOL_GRAD, RTOL_HV, close, per_layer
 from test_gpu_cnn import _inputs as cnn_inputs
+from test_gpu_conv_slabs import second_convolution_on_slabs
 
 pytestmark = pytest.mark.gpu
 
 TILES = ((132, 1028, 1036, 7), 193, 4)       # hidden products of 272 tiles of 64 x 64, no size a multiple of a tile
-SLICES = ((260, 68, 132, 10), 65, 2)         # few tiles: forward in the small-model kernel, data gradient in slices
+SLICES = ((260, 68, 132, 10), 65, 2)         # few tiles: forward and data gradient in the small-model kernel
 
 
 def _inputs(dims, batch, k, seed, **kw):
@@ -147,19 +148,28 @@ def _smooth_cnn(spec, batch, k, seed):
     return theta, x, rng.integers(0, spec.fc[-1], size=(k, batch)).astype(np.int32)
 
 
+# The second convolution's forward product and data gradient on slabs of the map, its weight gradient in tiles
 CNNS = {
-    "paper_shape": (OC.CnnSpec(img=(28, 28, 1), conv=(32, 64), fc=(128, 10)), 16, 2),      # second convolution in 64 x 64 tiles
-    "many_rows": (OC.CnnSpec(img=(14, 12, 1), conv=(36, 36), fc=(24, 7)), 128, 7),         # in 128 x 64 tiles
+    "paper_shape": (OC.CnnSpec(img=(28, 28, 1), conv=(32, 64), fc=(128, 10)), 16, 2),
+    "many_rows": (OC.CnnSpec(img=(14, 12, 1), conv=(36, 36), fc=(24, 7)), 128, 7),
+}
+# maps too wide for slabs: all products in tiles on views of the map, 128 x 32, 64 x 64 and (from 512 blocks of rows on) 128 x 64
+VIEWS = {
+    "few_channels": (OC.CnnSpec(img=(30, 30, 1), conv=(8, 8), fc=(12, 5)), 3, 2),
+    "wide": (OC.CnnSpec(img=(8, 78, 1), conv=(36, 36), fc=(16, 7)), 5, 2),
+    "wide_many_rows": (OC.CnnSpec(img=(8, 78, 1), conv=(36, 36), fc=(16, 7)), 40, 6),
 }
 
 
-@pytest.mark.parametrize("name", list(CNNS))
-@pytest.mark.parametrize("where", ["forward", "backward"])
+@pytest.mark.parametrize("name,where", [(n, w) for n in CNNS for w in ("forward", "backward")] +
+                         [(n, w) for n in VIEWS for w in ("in range", "forward", "backward")])
 def test_convolutions_beyond_the_pieces_range(name, where):
     """The second convolution's forward product (first kernels and biases times 2^84, the first linear layer's weights 2^-84) and
-    its data and weight gradients (output weights times 2^95) are computed again; against the 64-bit oracle."""
-    spec, batch, k = CNNS[name]
+    its data and weight gradients (output weights times 2^95) are computed again; against the 64-bit oracle.  On maps too wide for
+    slabs also with operands that need no second pass."""
+    spec, batch, k = {**CNNS, **VIEWS}[name]
     print("redo cnn", name, where, flush=True)
+    assert second_convolution_on_slabs(spec, batch, k) == (name in CNNS)
     theta0, x, y = cnn_inputs(spec, batch, k, 100) if name == "paper_shape" else _smooth_cnn(spec, batch, k, 100)
     theta0 = theta0.copy()
     offs, _ = spec.offsets()
@@ -168,7 +178,7 @@ def test_convolutions_beyond_the_pieces_range(name, where):
             theta0[w:b] *= s
         for (_, b, shape) in offs[:2]:
             theta0[b:b + shape[0]] *= 2.0 ** 84
-    else:
+    elif where == "backward":
         w, b, _ = offs[-1]
         theta0[w:b] *= 2.0 ** 95
     idx, P_lib = B.conv_param_index(spec.img, spec.conv, spec.fc)
