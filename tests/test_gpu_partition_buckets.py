@@ -1,4 +1,5 @@
-"""The bucketed ranking of the overlap partition at the edges of its range and of its bucket counts, bit for bit."""
+"""The overlap partition at sizes of the two-launch form inside its range, and of the five-launch form at the edges of its bucket counts,
+bit for bit."""
 import numpy as np
 import pytest
 
@@ -9,11 +10,13 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("n,o,k", [
-    (2047, 5, 3),                    # the last size that compares every pair
-    (2048, 0, 2), (2049, 2049, 1),   # the first ones with buckets, 1024 of them
-    (32767, 100, 7), (32768, 0, 64), # 1024 buckets, then 2048
-    (1 << 17, 1000, 5),              # the largest set of the form with a fixed scratch array
-    (1 << 21, 12345, 16),            # DW_MAX_POINTS
+    (2047, 5, 3), (2048, 0, 2), (2049, 2049, 1),          # two launches: 64 buckets, then 128
+    (32767, 100, 7), (32768, 0, 64),                      # 1024 buckets, then 2048
+    (1 << 17, 1000, 5),                                   # the largest set of the form with a fixed scratch array
+    ((1 << 18) + 1, 99, 4),                               # five launches from here on: 2^14 buckets
+    ((1 << 19) - 1, 0, 8), (1 << 19, 7777, 3),            # and 2^15
+    ((1 << 20) - 1, 1 << 19, 2), (1 << 20, 0, 16),        # and 2^16
+    (1 << 21, 12345, 16),                                 # DW_MAX_POINTS
 ])
 def test_bucketed_partition_matches_the_oracle(n, o, k):
     print("bucketed partition", n, o, k, flush=True)
