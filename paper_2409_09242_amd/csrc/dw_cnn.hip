@@ -7,7 +7,7 @@
 // innermost, as in the map, so that patches are cut and put back with contiguous accesses), and
 //   forward      S  = P W^T + b,          RS  = RP W^T + P V^T + c         (P patches, V = z reshaped like W)
 //   weight grad  gW = D^T P,              HzW = RD^T P + D^T RP
-//   data grad    dP = D W,                RdP = RD W + D V,   then summed back onto the map ("col2im")
+//   data grad    dP = D W,                RdP = RD W + D V,   summed over the patches that hold a map entry
 // are the three products of Section IV-B's Hessian-vector product with B*(H-2)*(W-2) rows instead of B.  ReLU and
 // max-pool pass the directional derivative through their selections (their curvature is zero almost everywhere).
 // Only the first convolution has its patch matrix in memory, and that not where images have one channel: nine products an output

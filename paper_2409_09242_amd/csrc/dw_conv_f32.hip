@@ -11,7 +11,7 @@
 // compute unit, 256 positions by 32 outputs or 128 by 64, and goes on to further positions: the map's entries for the next slab are on
 // their way while this one is multiplied.
 // The data gradient is the same convolution of the gradient map, with a border of two, the taps in reverse and W transposed.
-// Eight workers, 64 maps of 26 x 26 x 32 <-> 24 x 24 x 64: forward 207 -> 165 us, data gradient 384 -> 188 (as products on patches / now; the matrix
+// Eight workers, 64 maps of 26 x 26 x 32 <-> 24 x 24 x 64: forward 207 -> 166 us, data gradient 384 -> 187 (as products on patches / now; the matrix
 // instructions alone are 71 and 83 at 2.2 GHz).  By clock readings a slab of 36 k-steps for the two waves of a SIMD takes 27 thousand
 // cycles, 17.3 of them matrix instructions, 3 the splitting, 1.5 the barriers, 5 waits inside; a block's end another 5.  Blocks of four waves, two to a
 // compute unit, 16 channels a slab: 164 and 226 (each line of the map fetched twice, and both blocks split at the same time).

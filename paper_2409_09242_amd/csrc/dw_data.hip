@@ -15,8 +15,8 @@
 #include "dw_internal.h"
 #include "dw_partition_plan.h"
 
-// Scratch of dw_overlap_partition_static: what up to DW_STATIC_MAX_POINTS points need (dw_partition_plan.h).  Every device the library runs on holds its own copy at its own address until the
-// process ends; host code reaches it only through the address hipGetSymbolAddress returns for the current device.
+// Scratch of dw_overlap_partition_static: what up to DW_STATIC_MAX_POINTS points need (dw_partition_plan.h).  Every device the library
+// runs on holds its own copy at its own address until the process ends; host code reaches it only through the address hipGetSymbolAddress returns for the current device.
 static __device__ __align__(256) unsigned char scratch[(size_t)DW_STATIC_MAX_POINTS * 12];
 
 namespace dw {

@@ -17,9 +17,9 @@
 // stored to LDS (planes [row][32 k] of bf16, 64-byte rows, 16-byte units XOR-swizzled so that both the
 // reads of 8 consecutive rows and the stores of every fourth row spread over the banks); global loads are 16-byte and one
 // tile ahead in registers.  On the fp32 matrix instruction -> now: eight workers, 256 samples, 3072-1024-1024-1024: forward
-// 295 / 135 -> 156 / 72 us (first / later layers), data gradient 94 -> 60, fused weight gradients 346 / 154 -> 226 / 101; eight
-// workers, 64 maps of 26 x 26 x 32 -> 24 x 24 x 64: weight gradient 370 -> 237 (forward 207 and data gradient 384 through
-// this kernel's views of the map, 165 and 188 on slabs of it, dw_conv_f32.hip, which takes all maps whose slabs fit in LDS).
+// 295 / 135 -> 147 / 74 us (first / later layers), data gradient 94 -> 59, fused weight gradients 346 / 154 -> 233 / 103; eight
+// workers, 64 maps of 26 x 26 x 32 -> 24 x 24 x 64: weight gradient 370 -> 255 (forward 207 and data gradient 384 through
+// this kernel's views of the map, 166 and 187 on slabs of it, dw_conv_f32.hip, which takes all maps whose slabs fit in LDS).
 // What bounds them now (64 x 64 and 64 x 128 tiles of the first, by counters): matrix cores 30 to 36 % busy, vector arithmetic
 // (splitting, 6.5 instructions per element and block that loads it) 36 to 45 %, LDS instructions 40 to 47 % (six bytes stored and
 // read per element), and between them the two barriers a tile, with two blocks a compute unit to hide them; the convolutions

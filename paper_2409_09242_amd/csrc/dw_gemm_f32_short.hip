@@ -82,7 +82,7 @@ __global__ __launch_bounds__(NW * 64) void short_gemm_f32(GemmArgs a) {
   struct Step { float4 x[4], rx[4], y[4]; uint32_t v0, v1; int sh; };
   auto load_step = [&](Step& s, int k0, auto whole) {
     constexpr bool WHOLE = decltype(whole)::value;
-    const bool ok = WHOLE || k0 + unit * 4 < K;              // (K is a multiple of 4 where k is contiguous)
+    const bool ok = WHOLE || k0 + unit * 4 < K;              // (rows end at a multiple of 4: the widths are, and the output layer's errors have zeros from the last class to 16)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       s.x[i] = ok ? *reinterpret_cast<const float4*>(X + xo[i] + k0) : make_float4(0.f, 0.f, 0.f, 0.f);

@@ -173,7 +173,7 @@ struct ConvView { int H, W, Cin, Cout; };   // the convolution's input map and c
 // LINEAR: an output layer.  WGRAD_FUSED: template instance of the fp32 kernel for EPI_WGRAD with fu.on
 enum Epilogue { EPI_RELU = 0, EPI_LINEAR = 1, EPI_MASK = 2, EPI_WGRAD = 3, EPI_WGRAD_FUSED = 4 };
 
-// One "dual-number" GEMM: C = X*Y and RC = RX*Y + X*RY for all workers (grid y = worker).
+// One "dual-number" GEMM: C = X*Y and RC = RX*Y + X*RY for all workers (numbered into the grid, see xcd_unit).
 // Element strides describe how the logical operands X[M][K], Y[K][N] sit in memory.
 struct GemmArgs {
   const void* X; const void* RX;      // RX == nullptr: that term is absent
@@ -193,7 +193,7 @@ struct GemmArgs {
   float* gb; float* hzb;                              // EPI_WGRAD: bias-gradient outputs (g + b_off, hz + b_off)
   FuseArgs fu;                                        // EPI_WGRAD: fu.on != 0 replaces the stores of C and RC by the update
   // fp32 forward product, data or weight gradient with a long contraction and few output tiles: the contraction is cut into ksplit slices
-  // (grid z), slice s of worker i writes its partial products to part + ((s*k + i)*2 + {0,1})*part_stride and its
+  // (numbered like the workers), slice s of worker i writes its partial products to part + ((s*k + i)*2 + {0,1})*part_stride and its
   // partial bias sums (weight gradient) to part_b + ((s*k + i)*2 + {0,1})*M; a second kernel adds the slices in order and
   // applies the epilogue (bias, ReLU) into C, RC, gb, hzb
   int ksplit; float* part; int64_t part_stride; float* part_b;

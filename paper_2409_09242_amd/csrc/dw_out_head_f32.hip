@@ -5,8 +5,8 @@
 // small models this replaces three short launches in a row (a product with a handful of tiles, the sum of its slices,
 // the head) by one.  A block owns 16 samples; its four waves take a quarter of the contraction each with the
 // 16 x 16 x 4 MFMA, every lane loading 16 bytes (4 consecutive k) of A, RA and W per step, and the four partial tiles
-// are added in wave order through LDS.  A 16-lane group then holds one sample's 16 logits, gathers them by shuffles
-// and runs the head's arithmetic on them.  The loss of the block's samples goes to one slot per (worker, block);
+// are added in wave order through LDS.  A 16-lane group then holds one sample's 16 logits, a class each, and runs the head
+// on them together (head_lanes).  The loss of the block's samples goes to one slot per (worker, block);
 // the update's kernel adds a worker's slots when the caller wants the loss.
 //
 // Few samples and a long contraction leave a handful of blocks walking all of it.  There the contraction is cut into slices
